@@ -4,8 +4,8 @@
 // evaluator).  Each workgroup stages the function's <= 16-entry tables in LDS
 // once, then each thread loads U float4 vectors (128-bit, coalesced: lane i of
 // a wave touches bytes [16 i, 16 i + 16) of a contiguous 1 KiB span), evaluates
-// the 4U elements and stores U float4 vectors.  Pointers that are not 16-byte
-// aligned, and ragged tails, go through a scalar grid-stride kernel.
+// the 4U elements and stores U float4 vectors.  One launch takes any length and
+// any pointers aligned to their element.
 #include <hip/hip_runtime.h>
 
 #include <stdio.h>
@@ -85,33 +85,113 @@ constexpr int QFLUSH = QCAP / 2;            // flush when the queue is fuller th
 #ifndef CR_NT
 #define CR_NT 1
 #endif
-typedef float v4f_t __attribute__((ext_vector_type(4)));
-typedef double v2d_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ float4 ld_stream(const float4* p) {
-  if (!CR_NT) return *p;
-  v4f_t v = __builtin_nontemporal_load(reinterpret_cast<const v4f_t*>(p));
+// The vector types carry the alignment of one element only: gfx950 takes 128-bit
+// global accesses at any 4-byte address, so a slice of an array, a cosine block
+// behind an odd number of sines and an aligned buffer all run the same kernel.
+typedef float v4f_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef double v2d_t __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ float4 ld_stream4(const float* p) {
+  const v4f_t* q = reinterpret_cast<const v4f_t*>(p);
+  v4f_t v = CR_NT ? __builtin_nontemporal_load(q) : *q;
   return make_float4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ void st_stream(float4* p, float4 a) {
-  if (!CR_NT) {
-    *p = a;
-    return;
-  }
+__device__ __forceinline__ void st_stream4(float* p, float4 a) {
   v4f_t v = {a.x, a.y, a.z, a.w};
-  __builtin_nontemporal_store(v, reinterpret_cast<v4f_t*>(p));
+  v4f_t* q = reinterpret_cast<v4f_t*>(p);
+  if (CR_NT)
+    __builtin_nontemporal_store(v, q);
+  else
+    *q = v;
 }
-__device__ __forceinline__ double2 ld_stream(const double2* p) {
-  if (!CR_NT) return *p;
-  v2d_t v = __builtin_nontemporal_load(reinterpret_cast<const v2d_t*>(p));
+__device__ __forceinline__ double2 ld_stream2(const double* p) {
+  const v2d_t* q = reinterpret_cast<const v2d_t*>(p);
+  v2d_t v = CR_NT ? __builtin_nontemporal_load(q) : *q;
   return make_double2(v.x, v.y);
 }
-__device__ __forceinline__ void st_stream(double2* p, double2 a) {
-  if (!CR_NT) {
-    *p = a;
-    return;
-  }
+__device__ __forceinline__ void st_stream2(double* p, double2 a) {
   v2d_t v = {a.x, a.y};
-  __builtin_nontemporal_store(v, reinterpret_cast<v2d_t*>(p));
+  v2d_t* q = reinterpret_cast<v2d_t*>(p);
+  if (CR_NT)
+    __builtin_nontemporal_store(v, q);
+  else
+    *q = v;
+}
+
+// Tiles of the map kernels.  T is float or double, VN elements make a 128-bit
+// vector, and a tile is U vectors per thread (vector u of thread t at element
+// VN (t + u BLOCK) of the tile).  `full` (the whole tile lies below n) is the
+// same for every thread, so whole tiles pay no bounds check; only the last tile
+// of a launch takes the element-by-element branches, which also read and write
+// the 1..VN-1 elements after the last whole vector.
+template <class T>
+struct Vec;
+template <>
+struct Vec<float> {
+  using type = float4;
+  static constexpr int N = 4;
+  static __device__ __forceinline__ float4 load(const float* p) { return ld_stream4(p); }
+  static __device__ __forceinline__ void store(float* p, float4 v) { st_stream4(p, v); }
+};
+template <>
+struct Vec<double> {
+  using type = double2;
+  static constexpr int N = 2;
+  static __device__ __forceinline__ double2 load(const double* p) { return ld_stream2(p); }
+  static __device__ __forceinline__ void store(double* p, double2 v) { st_stream2(p, v); }
+};
+
+// Elements of the tile at t0 that lie past n hold 1 after the load.
+template <class T, int U>
+__device__ __forceinline__ void tile_load(typename Vec<T>::type (&v)[U], const T* in, long long t0,
+                                          long long n, bool full) {
+  constexpr int VN = Vec<T>::N;
+  const T* p = in + t0;
+  if (full) {
+#pragma unroll
+    for (int u = 0; u < U; u++) v[u] = Vec<T>::load(p + VN * (threadIdx.x + u * BLOCK));
+  } else {
+    const int left = (int)(n - t0);  // below the tile's size, possibly <= 0
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int i = VN * (threadIdx.x + u * BLOCK);
+      T* e = reinterpret_cast<T*>(&v[u]);
+#pragma unroll
+      for (int c = 0; c < VN; c++) e[c] = i + c < left ? p[i + c] : T(1);
+    }
+  }
+}
+template <class T, int U>
+__device__ __forceinline__ void tile_store(const typename Vec<T>::type (&v)[U], T* out,
+                                           long long t0, long long n, bool full) {
+  constexpr int VN = Vec<T>::N;
+  T* p = out + t0;
+  if (full) {
+#pragma unroll
+    for (int u = 0; u < U; u++) Vec<T>::store(p + VN * (threadIdx.x + u * BLOCK), v[u]);
+  } else {
+    const int left = (int)(n - t0);
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int i = VN * (threadIdx.x + u * BLOCK);
+      const T* e = reinterpret_cast<const T*>(&v[u]);
+#pragma unroll
+      for (int c = 0; c < VN; c++)
+        if (i + c < left) p[i + c] = e[c];
+    }
+  }
+}
+// Bit VN u + c is set where element c of vector u lies below n.
+template <class T, int U>
+__device__ __forceinline__ unsigned tile_live(long long t0, long long n) {
+  constexpr int VN = Vec<T>::N;
+  const int left = (int)(n - t0);
+  unsigned m = 0;
+#pragma unroll
+  for (int u = 0; u < U; u++)
+#pragma unroll
+    for (int c = 0; c < VN; c++)
+      m |= (unsigned)(VN * (int)(threadIdx.x + u * BLOCK) + c < left) << (VN * u + c);
+  return m;
 }
 
 // ------------------------------------------------------------ evaluators
@@ -385,14 +465,21 @@ __device__ __forceinline__ void flush_queue(Deferred& q, const typename Op::Tab&
 }
 
 // ---------------------------------------------------------------- kernels
-// Persistent elementwise map over 16-byte aligned data.  Each workgroup walks
-// tiles of 2048 elements (tile t, t + gridDim.x, ...).  Per tile every thread
-// loads two float4 (lane i of a wave touches bytes [16 i, 16 i + 16) of a
-// contiguous 1 KiB span), runs the fast path on its 8 elements and stores.
+// Persistent elementwise map.  Each workgroup walks tiles of 1024 U elements
+// (tile t, t + gridDim.x, ...).  Per tile every thread loads U float4 (lane i of
+// a wave touches bytes [16 i, 16 i + 16) of a contiguous 1 KiB span), runs the
+// fast path on its 4U elements and stores.
 // Elements whose fast result is not certified are queued in LDS (index and
 // input value) and re-evaluated by the accurate path a whole workgroup at a
 // time -- when the queue passes QFLUSH and at the end -- so a rare failing
 // lane does not make a 64-lane wave run the slow path for it alone.
+// The call's whole range is one launch at any length and alignment, bound by
+// the VALU work per element (large arrays) or by the launch (small ones).
+// Measured against a scalar kernel for heads, tails and pointers of different
+// alignment beside a 16-byte aligned body: expf of 2^22 - 1 elements 10.4 -> 8.1
+// us (one launch instead of two), of 2^26 elements from a slice x[1:] 159 -> 97
+// us (scalar accesses before), sincosf of a slice of 2^24 73 -> 49 us; aligned
+// arrays unchanged within 1%.
 // Launch-shape variants (chosen per function by the autotuner, cr_autotune):
 //   U   float4 vectors per thread per tile (4U elements per thread),
 //   PF  1: the next tile's vectors are loaded while this one is evaluated,
@@ -408,11 +495,18 @@ __global__ void k_tab_init() {
 
 template <class Op, int U, int PF, int TP>
 __global__ void __launch_bounds__(BLOCK)
-    k_map_f32(const float4* in, float4* out, long long n4, DevStats* st,
-              unsigned flags, long long elem_base) {
+    k_map_f32(const float* in, float* out, long long n, DevStats* st, unsigned flags,
+              long long elem_base) {
   __shared__ typename Op::Tab lds_tab;
   __shared__ Deferred q;
+  constexpr int TE = BLOCK * 4 * U;  // elements per tile
   const typename Op::Tab& tab = TP ? g_tab<Op> : lds_tab;
+  // software pipelining: the next tile's vectors are loaded while this tile
+  // is evaluated (the first one while the tables are staged)
+  float4 nxt[U];
+  const long long step = (long long)gridDim.x * TE;
+  long long t0 = (long long)blockIdx.x * TE;
+  if (PF) tile_load<float, U>(nxt, in, t0, n, t0 + TE <= n);
   if (!TP) Op::load(lds_tab, threadIdx.x);
   if (threadIdx.x == 0) {
     q.n = 0;
@@ -420,59 +514,35 @@ __global__ void __launch_bounds__(BLOCK)
   }
   __syncthreads();
   const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  float* outf = reinterpret_cast<float*>(out);
-  const long long ntiles = (n4 + BLOCK * U - 1) / (BLOCK * U);
-  // software pipelining: the next tile's vectors are loaded while this tile
-  // is evaluated
-  float4 nxt[U];
-  if (PF) {
-    long long base = (long long)blockIdx.x * (BLOCK * U) + threadIdx.x;
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      long long i = base + (long long)u * BLOCK;
-      nxt[u] = i < n4 ? ld_stream(in + i) : make_float4(1.0f, 1.0f, 1.0f, 1.0f);
-    }
-  }
   int iter = 0;
-  for (long long t = blockIdx.x; t < ntiles; t += gridDim.x, iter++) {
-    long long base = t * (BLOCK * U) + threadIdx.x;
+  for (; t0 < n; t0 += step, iter++) {
+    const bool full = t0 + TE <= n;
     float4 v[U];
     if (PF) {
 #pragma unroll
       for (int u = 0; u < U; u++) v[u] = nxt[u];
+      const long long tn = t0 + step;
+      if (tn < n) tile_load<float, U>(nxt, in, tn, n, tn + TE <= n);
     } else {
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        long long i = base + (long long)u * BLOCK;
-        v[u] = i < n4 ? ld_stream(in + i) : make_float4(1.0f, 1.0f, 1.0f, 1.0f);
-      }
-    }
-    if (PF) {
-      long long nb = (t + gridDim.x) * (BLOCK * U) + threadIdx.x;
-#pragma unroll
-      for (int u = 0; u < U; u++) {
-        long long i = nb + (long long)u * BLOCK;
-        nxt[u] = i < n4 ? ld_stream(in + i) : make_float4(1.0f, 1.0f, 1.0f, 1.0f);
-      }
+      tile_load<float, U>(v, in, t0, n, full);
     }
     // Evaluate every element of the tile first -- straight-line code with no
     // branch between elements, so the scheduler can interleave their
     // dependency chains -- then queue the elements that failed the test.
-    // Slots past the end hold stale values: evaluated, never stored or queued.
     float xin[4 * U];
     unsigned fail = 0;
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      const bool live = base + (long long)u * BLOCK < n4;
       float* e = reinterpret_cast<float*>(&v[u]);
 #pragma unroll
       for (int c = 0; c < 4; c++) {
         bool ok;
         xin[4 * u + c] = e[c];
         e[c] = Op::fast(e[c], tab, ok);
-        fail |= (unsigned)(live && (!ok || force)) << (4 * u + c);
+        fail |= (unsigned)(!ok || force) << (4 * u + c);
       }
     }
+    if (!full) fail &= tile_live<float, U>(t0, n);
     if (fail) {
 #pragma unroll
       for (int u = 0; u < U; u++) {
@@ -480,74 +550,37 @@ __global__ void __launch_bounds__(BLOCK)
 #pragma unroll
         for (int c = 0; c < 4; c++) {
           if (fail & (1u << (4 * u + c))) {
-            const long long i = base + (long long)u * BLOCK;
+            const unsigned i = (unsigned)t0 + 4 * (threadIdx.x + u * BLOCK) + c;
             const float x = xin[4 * u + c];
             unsigned pos = atomicAdd(&q.n, 1u);
             if (pos < QCAP) {
-              q.idx[pos] = (unsigned)(4 * i + c);
+              q.idx[pos] = i;
               q.x[pos] = x;
             } else {  // queue full (only with pathological inputs or force)
               AccResult a = Op::accurate(x, tab);
               e[c] = a.r;
               atomicAdd(&q.lanes, 1u);
-              if (!a.ok) note_escape(st, elem_base + 4 * i + c);
+              if (!a.ok) note_escape(st, elem_base + i);
             }
           }
         }
       }
     }
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      long long i = base + (long long)u * BLOCK;
-      if (i < n4) st_stream(out + i, v[u]);
-    }
+    tile_store<float, U>(v, out, t0, n, full);
     if (iter % Op::qcheck == Op::qcheck - 1) {
       // every thread must see the same fill level: read it between two
       // barriers (no thread can queue more elements before all have read it)
       __syncthreads();
       const unsigned nq = q.n;
       __syncthreads();
-      if (nq > QFLUSH) flush_queue<Op>(q, tab, outf, st, elem_base);
+      if (nq > QFLUSH) flush_queue<Op>(q, tab, out, st, elem_base);
     }
   }
   __syncthreads();
-  flush_queue<Op, true>(q, tab, outf, st, elem_base);
+  flush_queue<Op, true>(q, tab, out, st, elem_base);
 }
 
-// Scalar form for unaligned heads, ragged tails and pointers whose alignment
-// differs; the accurate path runs in place.
-template <class Op>
-__global__ void __launch_bounds__(BLOCK)
-    k_map_f32_scalar(const float* in, float* out, long long n, DevStats* st,
-                     unsigned flags, long long elem_base) {
-  __shared__ typename Op::Tab tab;
-  Op::load(tab, threadIdx.x);
-  __syncthreads();
-  const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  unsigned lanes = 0;
-  for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n;
-       i += (long long)gridDim.x * BLOCK) {
-    bool ok;
-    float x = in[i];
-    float r = Op::fast(x, tab, ok);
-    if (!ok || force) {
-      AccResult a = Op::accurate(x, tab);
-      r = a.r;
-      lanes++;
-      if (!a.ok) note_escape(st, elem_base + i);
-    }
-    out[i] = r;
-  }
-  if (lanes) {
-    CounterSlot& c = st->slot[blockIdx.x % NSLOT];
-    atomicAdd(&c.fallback_lanes, (unsigned long long)lanes);
-    atomicAdd(&c.fallback_waves, 1ull);
-  }
-}
-
-// sincosf: the map kernel with two planar outputs (sin block, cos block); the
-// input and the sine block 16-byte aligned (the host checks; otherwise the
-// scalar form below runs).
+// sincosf: the map kernel with two planar outputs (sin block, cos block).
 template <class SC, bool FINAL = false>
 __device__ __forceinline__ void flush_queue_sincos(Deferred& q, const typename SC::Tab& tab,
                                                    float* os, float* oc, DevStats* st,
@@ -560,15 +593,13 @@ __device__ __forceinline__ void flush_queue_sincos(Deferred& q, const typename S
   });
 }
 
-// CVEC: the cosine block is 16-byte aligned as well (n a multiple of 4);
-// otherwise its four values per vector are stored one by one (still
-// contiguous across the lanes of a wave).
-template <class SC, bool CVEC>
+template <class SC>
 __global__ void __launch_bounds__(BLOCK)
-    k_map_sincos(const float4* in, float4* outs, float* outc, long long n4, DevStats* st,
+    k_map_sincos(const float* in, float* outs, float* outc, long long n, DevStats* st,
                  unsigned flags, long long elem_base) {
   __shared__ typename SC::Tab tab;
   __shared__ Deferred q;
+  constexpr int TE = BLOCK * 4 * TILE_U;
   SC::load(tab, threadIdx.x);
   if (threadIdx.x == 0) {
     q.n = 0;
@@ -576,100 +607,49 @@ __global__ void __launch_bounds__(BLOCK)
   }
   __syncthreads();
   const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  const long long ntiles = (n4 + BLOCK * TILE_U - 1) / (BLOCK * TILE_U);
+  const long long step = (long long)gridDim.x * TE;
   int iter = 0;
-  for (long long t = blockIdx.x; t < ntiles; t += gridDim.x, iter++) {
-    long long base = t * (BLOCK * TILE_U) + threadIdx.x;
+  for (long long t0 = (long long)blockIdx.x * TE; t0 < n; t0 += step, iter++) {
+    const bool full = t0 + TE <= n;
     float4 v[TILE_U], c4[TILE_U];
+    tile_load<float, TILE_U>(v, in, t0, n, full);
+    const unsigned live = full ? ~0u : tile_live<float, TILE_U>(t0, n);
 #pragma unroll
     for (int u = 0; u < TILE_U; u++) {
-      long long i = base + (long long)u * BLOCK;
-      if (i < n4) v[u] = ld_stream(in + i);
-    }
+      float* e = reinterpret_cast<float*>(&v[u]);
+      float* ec = reinterpret_cast<float*>(&c4[u]);
 #pragma unroll
-    for (int u = 0; u < TILE_U; u++) {
-      long long i = base + (long long)u * BLOCK;
-      if (i < n4) {
-        float* e = reinterpret_cast<float*>(&v[u]);
-        float* ec = reinterpret_cast<float*>(&c4[u]);
-#pragma unroll
-        for (int c = 0; c < 4; c++) {
-          bool ok;
-          float x = e[c];
-          e[c] = SC::fast(x, tab, ec[c], ok);
-          if (!ok || force) {
-            unsigned pos = atomicAdd(&q.n, 1u);
-            if (pos < QCAP) {
-              q.idx[pos] = (unsigned)(4 * i + c);
-              q.x[pos] = x;
-            } else {
-              AccResult2 a = SC::accurate(x, tab);
-              e[c] = a.s;
-              ec[c] = a.c;
-              atomicAdd(&q.lanes, 1u);
-              if (!a.ok) note_escape(st, elem_base + 4 * i + c);
-            }
+      for (int c = 0; c < 4; c++) {
+        bool ok;
+        float x = e[c];
+        e[c] = SC::fast(x, tab, ec[c], ok);
+        if ((!ok || force) && (live & (1u << (4 * u + c)))) {
+          const unsigned i = (unsigned)t0 + 4 * (threadIdx.x + u * BLOCK) + c;
+          unsigned pos = atomicAdd(&q.n, 1u);
+          if (pos < QCAP) {
+            q.idx[pos] = i;
+            q.x[pos] = x;
+          } else {
+            AccResult2 a = SC::accurate(x, tab);
+            e[c] = a.s;
+            ec[c] = a.c;
+            atomicAdd(&q.lanes, 1u);
+            if (!a.ok) note_escape(st, elem_base + i);
           }
         }
       }
     }
-#pragma unroll
-    for (int u = 0; u < TILE_U; u++) {
-      long long i = base + (long long)u * BLOCK;
-      if (i < n4) {
-        st_stream(outs + i, v[u]);
-        if (CVEC) {
-          st_stream(reinterpret_cast<float4*>(outc) + i, c4[u]);
-        } else {
-          float* p = outc + 4 * i;
-          p[0] = c4[u].x;
-          p[1] = c4[u].y;
-          p[2] = c4[u].z;
-          p[3] = c4[u].w;
-        }
-      }
-    }
+    tile_store<float, TILE_U>(v, outs, t0, n, full);
+    tile_store<float, TILE_U>(c4, outc, t0, n, full);
     if (iter % SC::qcheck == SC::qcheck - 1) {
       __syncthreads();
       const unsigned nq = q.n;
       __syncthreads();
-      if (nq > QFLUSH)
-        flush_queue_sincos<SC>(q, tab, reinterpret_cast<float*>(outs), outc, st, elem_base);
+      if (nq > QFLUSH) flush_queue_sincos<SC>(q, tab, outs, outc, st, elem_base);
     }
   }
   __syncthreads();
-  flush_queue_sincos<SC, true>(q, tab, reinterpret_cast<float*>(outs), outc, st, elem_base);
-}
-
-template <class SC>
-__global__ void __launch_bounds__(BLOCK)
-    k_map_sincos_scalar(const float* in, float* outs, float* outc, long long n, DevStats* st,
-                        unsigned flags, long long elem_base) {
-  __shared__ typename SC::Tab tab;
-  SC::load(tab, threadIdx.x);
-  __syncthreads();
-  const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  unsigned lanes = 0;
-  for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n;
-       i += (long long)gridDim.x * BLOCK) {
-    bool ok;
-    float x = in[i], c;
-    float s = SC::fast(x, tab, c, ok);
-    if (!ok || force) {
-      AccResult2 a = SC::accurate(x, tab);
-      s = a.s;
-      c = a.c;
-      lanes++;
-      if (!a.ok) note_escape(st, elem_base + i);
-    }
-    outs[i] = s;
-    outc[i] = c;
-  }
-  if (lanes) {
-    CounterSlot& c = st->slot[blockIdx.x % NSLOT];
-    atomicAdd(&c.fallback_lanes, (unsigned long long)lanes);
-    atomicAdd(&c.fallback_waves, 1ull);
-  }
+  flush_queue_sincos<SC, true>(q, tab, outs, outc, st, elem_base);
 }
 
 // ------------------------------------------------------------ binary64 map
@@ -746,10 +726,11 @@ __device__ __forceinline__ void flush_queue64(Deferred64& q, const typename Op::
 //         dependency chains) and the failing ones are queued afterwards.
 template <class Op, int U, int SL>
 __global__ void __launch_bounds__(BLOCK)
-    k_map_f64(const double2* in, double2* out, long long n2, DevStats* st, unsigned flags,
+    k_map_f64(const double* in, double* out, long long n, DevStats* st, unsigned flags,
               long long elem_base) {
   __shared__ typename Op::Tab tab;
   __shared__ Deferred64 q;
+  constexpr int TE = BLOCK * 2 * U;  // elements per tile
   Op::load(tab, threadIdx.x);
   if (threadIdx.x == 0) {
     q.n = 0;
@@ -757,14 +738,12 @@ __global__ void __launch_bounds__(BLOCK)
   }
   __syncthreads();
   const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  double* outd = reinterpret_cast<double*>(out);
-  const long long ntiles = (n2 + BLOCK * U - 1) / (BLOCK * U);
-  // queue element j (index 2 i + c of this launch) with input x, or run its
-  // accurate path in place when the queue is full
-  auto enqueue = [&](long long j, double x, double& res) {
+  // queue element j (of this launch) with input x, or run its accurate path in
+  // place when the queue is full
+  auto enqueue = [&](unsigned j, double x, double& res) {
     unsigned pos = atomicAdd(&q.n, 1u);
     if (pos < QCAP) {
-      q.idx[pos] = (unsigned)j;
+      q.idx[pos] = j;
       q.x[pos] = x;
     } else {
       AccResultD a = Op::accurate(x, tab);
@@ -773,100 +752,64 @@ __global__ void __launch_bounds__(BLOCK)
       if (!a.ok) note_escape(st, elem_base + j);
     }
   };
+  const long long step = (long long)gridDim.x * TE;
   int iter = 0;
-  for (long long t = blockIdx.x; t < ntiles; t += gridDim.x, iter++) {
-    long long base = t * (BLOCK * U) + threadIdx.x;
+  for (long long t0 = (long long)blockIdx.x * TE; t0 < n; t0 += step, iter++) {
+    const bool full = t0 + TE <= n;
+    const unsigned j0 = (unsigned)t0 + 2 * threadIdx.x;
     double2 v[U];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      long long i = base + (long long)u * BLOCK;
-      v[u] = i < n2 ? ld_stream(in + i) : make_double2(1.0, 1.0);
-    }
+    tile_load<double, U>(v, in, t0, n, full);
+    const unsigned live = full ? ~0u : tile_live<double, U>(t0, n);
     if (SL) {
       // slots past the end hold 1.0: evaluated, never stored or queued
       double xin[2 * U];
       unsigned fail = 0;
 #pragma unroll
       for (int u = 0; u < U; u++) {
-        const bool live = base + (long long)u * BLOCK < n2;
         double* e = reinterpret_cast<double*>(&v[u]);
 #pragma unroll
         for (int c = 0; c < 2; c++) {
           bool ok;
           xin[2 * u + c] = e[c];
           e[c] = Op::fast(e[c], tab, ok);
-          fail |= (unsigned)(live && (!ok || force)) << (2 * u + c);
+          fail |= (unsigned)(!ok || force) << (2 * u + c);
         }
       }
+      fail &= live;
       if (fail) {
 #pragma unroll
         for (int u = 0; u < U; u++) {
           double* e = reinterpret_cast<double*>(&v[u]);
-          const long long i = base + (long long)u * BLOCK;
 #pragma unroll
           for (int c = 0; c < 2; c++)
-            if ((fail >> (2 * u + c)) & 1u) enqueue(2 * i + c, xin[2 * u + c], e[c]);
+            if ((fail >> (2 * u + c)) & 1u)
+              enqueue(j0 + 2 * u * BLOCK + c, xin[2 * u + c], e[c]);
         }
       }
     } else {
 #pragma unroll
       for (int u = 0; u < U; u++) {
-        long long i = base + (long long)u * BLOCK;
-        if (i < n2) {
-          double* e = reinterpret_cast<double*>(&v[u]);
+        double* e = reinterpret_cast<double*>(&v[u]);
 #pragma unroll
-          for (int c = 0; c < 2; c++) {
-            bool ok;
-            double x = e[c];
-            e[c] = Op::fast(x, tab, ok);
-            if (!ok || force) enqueue(2 * i + c, x, e[c]);
-          }
+        for (int c = 0; c < 2; c++) {
+          bool ok;
+          double x = e[c];
+          e[c] = Op::fast(x, tab, ok);
+          if ((!ok || force) && (live & (1u << (2 * u + c))))
+            enqueue(j0 + 2 * u * BLOCK + c, x, e[c]);
         }
       }
     }
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      long long i = base + (long long)u * BLOCK;
-      if (i < n2) st_stream(out + i, v[u]);
-    }
+    tile_store<double, U>(v, out, t0, n, full);
     if (iter % Op::qcheck == Op::qcheck - 1) {
       __syncthreads();
       const unsigned nq = q.n;
       __syncthreads();
-      if (nq > QFLUSH) flush_queue64<Op>(q, tab, outd, st, elem_base);
+      if (nq > QFLUSH) flush_queue64<Op>(q, tab, out, st, elem_base);
     }
   }
   __syncthreads();
-  flush_queue64<Op, true>(q, tab, outd, st, elem_base);
-}
-
-template <class Op>
-__global__ void __launch_bounds__(BLOCK)
-    k_map_f64_scalar(const double* in, double* out, long long n, DevStats* st, unsigned flags,
-                     long long elem_base) {
-  __shared__ typename Op::Tab tab;
-  Op::load(tab, threadIdx.x);
-  __syncthreads();
-  const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  unsigned lanes = 0;
-  for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n;
-       i += (long long)gridDim.x * BLOCK) {
-    bool ok;
-    double x = in[i];
-    double r = Op::fast(x, tab, ok);
-    if (!ok || force) {
-      AccResultD a = Op::accurate(x, tab);
-      r = a.r;
-      lanes++;
-      if (!a.ok) note_escape(st, elem_base + i);
-    }
-    out[i] = r;
-  }
-  if (lanes) {
-    CounterSlot& c = st->slot[blockIdx.x % NSLOT];
-    atomicAdd(&c.fallback_lanes, (unsigned long long)lanes);
-    atomicAdd(&c.fallback_waves, 1ull);
-  }
+  flush_queue64<Op, true>(q, tab, out, st, elem_base);
 }
 
 // ------------------------------------------------- directed rounding modes
@@ -1050,10 +993,11 @@ struct CLogF {
 };
 
 // Complex map: interleaved (re, im) binary32 pairs, two complex numbers per
-// 128-bit load and store.  Persistent grid, tables staged in LDS.
+// 128-bit load and store, at any 4-byte alignment; the last one of an odd
+// number is loaded and stored by itself.  Persistent grid, tables staged in LDS.
 template <class CF>
 __global__ void __launch_bounds__(BLOCK)
-    k_complex(const float4* in, float4* out, long long n2, DevStats* st, unsigned flags,
+    k_complex(const float* in, float* out, long long n, DevStats* st, unsigned flags,
               long long elem_base) {
   __shared__ typename CF::Tab tab;
   __shared__ unsigned fails;
@@ -1062,48 +1006,29 @@ __global__ void __launch_bounds__(BLOCK)
   __syncthreads();
   const bool force = flags & CR_FLAG_FORCE_FALLBACK;
   LaneCount tot = {0u, 0u};
-  for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n2;
-       i += (long long)gridDim.x * BLOCK) {
-    const float4 v = ld_stream(in + i);
+  for (long long i = 2 * ((long long)blockIdx.x * BLOCK + threadIdx.x); i < n;
+       i += 2 * (long long)gridDim.x * BLOCK) {
+    const bool pair = i + 1 < n;
+    const float* p = in + 2 * i;
+    const float4 v = pair ? ld_stream4(p) : make_float4(p[0], p[1], 1.0f, 1.0f);
     LaneCount lc = {0u, 0u};
     const float2 r0 = CF::eval(v.x, v.y, tab, force, lc);
-    if (lc.escapes) note_escape(st, elem_base + 2 * i);
+    if (lc.escapes) note_escape(st, elem_base + i);
     tot.fails += lc.fails;
     lc = {0u, 0u};
     const float2 r1 = CF::eval(v.z, v.w, tab, force, lc);
-    if (lc.escapes) note_escape(st, elem_base + 2 * i + 1);
-    tot.fails += lc.fails;
-    st_stream(out + i, make_float4(r0.x, r0.y, r1.x, r1.y));
+    if (pair) {
+      if (lc.escapes) note_escape(st, elem_base + i + 1);
+      tot.fails += lc.fails;
+      st_stream4(out + 2 * i, make_float4(r0.x, r0.y, r1.x, r1.y));
+    } else {
+      out[2 * i] = r0.x;
+      out[2 * i + 1] = r0.y;
+    }
   }
   if (tot.fails) atomicAdd(&fails, tot.fails);
   __syncthreads();
   if (threadIdx.x == 0 && fails) {
-    CounterSlot& c = st->slot[blockIdx.x % NSLOT];
-    atomicAdd(&c.fallback_lanes, (unsigned long long)fails);
-    atomicAdd(&c.fallback_waves, 1ull);
-  }
-}
-
-// Scalar form for unaligned buffers and a ragged last element (4-byte loads).
-template <class CF>
-__global__ void __launch_bounds__(BLOCK)
-    k_complex_scalar(const float* in, float* out, long long n, DevStats* st, unsigned flags,
-                     long long elem_base) {
-  __shared__ typename CF::Tab tab;
-  CF::load(tab, threadIdx.x);
-  __syncthreads();
-  const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  unsigned fails = 0;
-  for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n;
-       i += (long long)gridDim.x * BLOCK) {
-    LaneCount lc = {0u, 0u};
-    const float2 r = CF::eval(in[2 * i], in[2 * i + 1], tab, force, lc);
-    if (lc.escapes) note_escape(st, elem_base + i);
-    fails += lc.fails;
-    out[2 * i] = r.x;
-    out[2 * i + 1] = r.y;
-  }
-  if (fails) {
     CounterSlot& c = st->slot[blockIdx.x % NSLOT];
     atomicAdd(&c.fallback_lanes, (unsigned long long)fails);
     atomicAdd(&c.fallback_waves, 1ull);
@@ -1275,7 +1200,7 @@ __device__ __forceinline__ void batch_tile(BReq R, BTile T, const typename Op::T
     for (int u = 0; u < BATCH_U; u++) {
       int i = threadIdx.x + u * BLOCK;
       if (i < n4) {
-        float4 v = ld_stream(reinterpret_cast<const float4*>(in) + i);
+        float4 v = ld_stream4(in + 4 * i);
         float* e = reinterpret_cast<float*>(&v);
 #pragma unroll
         for (int c = 0; c < 4; c++) {
@@ -1285,7 +1210,7 @@ __device__ __forceinline__ void batch_tile(BReq R, BTile T, const typename Op::T
           if (!ok || force)
             batch_enqueue<Op>(q, tab, T.req, R.orig, base + 4 * i + c, x, e[c], st);
         }
-        st_stream(reinterpret_cast<float4*>(out) + i, v);
+        st_stream4(out + 4 * i, v);
       }
     }
     int i = 4 * n4 + threadIdx.x;
@@ -1341,13 +1266,13 @@ __device__ __forceinline__ void batch_tile_sincos(BReq R, BTile T, const typenam
     for (int u = 0; u < BATCH_U; u++) {
       int i = threadIdx.x + u * BLOCK;
       if (i < n4) {
-        float4 v = ld_stream(reinterpret_cast<const float4*>(in) + i), cv;
+        float4 v = ld_stream4(in + 4 * i), cv;
         float* e = reinterpret_cast<float*>(&v);
         float* ec = reinterpret_cast<float*>(&cv);
 #pragma unroll
         for (int c = 0; c < 4; c++) one(4 * i + c, e[c], e[c], ec[c]);
-        st_stream(reinterpret_cast<float4*>(os) + i, v);
-        st_stream(reinterpret_cast<float4*>(oc) + i, cv);
+        st_stream4(os + 4 * i, v);
+        st_stream4(oc + 4 * i, cv);
       }
     }
     i0 = 4 * n4;
@@ -1547,6 +1472,8 @@ int ensure_gtab() {
   return CR_OK;
 }
 
+constexpr size_t LAUNCH_ELEMS = (size_t)1 << 31;
+
 template <class Op, int U, int PF, int TP>
 int launch_map_f32(const float* in, float* out, size_t n, hipStream_t s, unsigned flags,
                    DevStats* st, int grid) {
@@ -1554,39 +1481,15 @@ int launch_map_f32(const float* in, float* out, size_t n, hipStream_t s, unsigne
     int rc = ensure_gtab<Op>();
     if (rc) return rc;
   }
-  uintptr_t ai = (uintptr_t)in, ao = (uintptr_t)out;
-  size_t head = 0;
-  if ((ai & 15) == (ao & 15)) {
-    head = ((16 - (ai & 15)) & 15) / 4;
-    if (head > n) head = n;
-  } else {
-    head = n;  // incompatible alignment: all scalar
-  }
-  size_t body4 = (n - head) / 4;
-  size_t tail = n - head - 4 * body4;
-  if (head) {
-    size_t g = (head + BLOCK - 1) / BLOCK;
-    if (g > 65536) g = 65536;
-    hipLaunchKernelGGL(k_map_f32_scalar<Op>, dim3((unsigned)g), dim3(BLOCK), 0, s, in, out,
-                       (long long)head, st, flags, 0LL);
-  }
-  // the deferred queue stores 32-bit indices: split bodies beyond 2^32 elements
-  for (size_t done = 0; done < body4;) {
-    size_t chunk4 = body4 - done;
-    if (chunk4 > ((size_t)1 << 29)) chunk4 = (size_t)1 << 29;
-    size_t tiles = (chunk4 + BLOCK * U - 1) / (BLOCK * U);
-    size_t g = tiles < (size_t)grid ? tiles : (size_t)grid;
-    size_t off = head + 4 * done;
-    hipLaunchKernelGGL((k_map_f32<Op, U, PF, TP>), dim3((unsigned)g), dim3(BLOCK), 0, s,
-                       reinterpret_cast<const float4*>(in + off),
-                       reinterpret_cast<float4*>(out + off), (long long)chunk4, st, flags,
-                       (long long)off);
-    done += chunk4;
-  }
-  if (tail) {
-    size_t off = head + 4 * body4;
-    hipLaunchKernelGGL(k_map_f32_scalar<Op>, dim3(1), dim3(BLOCK), 0, s, in + off, out + off,
-                       (long long)tail, st, flags, (long long)off);
+  // the kernel counts elements in 32 bits (its deferred queue): at most
+  // LAUNCH_ELEMS a launch
+  for (size_t done = 0; done < n;) {
+    const size_t cnt = n - done < LAUNCH_ELEMS ? n - done : LAUNCH_ELEMS;
+    const size_t tiles = (cnt + BLOCK * 4 * U - 1) / (BLOCK * 4 * U);
+    const size_t g = tiles < (size_t)grid ? tiles : (size_t)grid;
+    hipLaunchKernelGGL((k_map_f32<Op, U, PF, TP>), dim3((unsigned)g), dim3(BLOCK), 0, s, in + done,
+                       out + done, (long long)cnt, st, flags, (long long)done);
+    done += cnt;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e);
@@ -1617,33 +1520,13 @@ template <class SC>
 int launch_sincos(const float* in, float* out, size_t n, hipStream_t s, unsigned flags,
                   DevStats* st, int grid) {
   float* outc = out + n;
-  uintptr_t ai = (uintptr_t)in, ao = (uintptr_t)out, ac = (uintptr_t)outc;
-  // vector body when the input and the sine block are 16-byte aligned; the
-  // cosine block (at out + n) is stored by vectors too when it is aligned
-  bool vec = (ai & 15) == 0 && (ao & 15) == 0;
-  bool cvec = (ac & 15) == 0;
-  size_t body4 = vec ? n / 4 : 0;
-  size_t done4 = 0;
-  while (done4 < body4) {
-    size_t chunk4 = body4 - done4;
-    if (chunk4 > ((size_t)1 << 29)) chunk4 = (size_t)1 << 29;
-    size_t tiles = (chunk4 + BLOCK * TILE_U - 1) / (BLOCK * TILE_U);
-    size_t g = tiles < (size_t)grid ? tiles : (size_t)grid;
-    size_t off = 4 * done4;
-    auto k = cvec ? k_map_sincos<SC, true> : k_map_sincos<SC, false>;
-    hipLaunchKernelGGL(k, dim3((unsigned)g), dim3(BLOCK), 0, s,
-                       reinterpret_cast<const float4*>(in + off),
-                       reinterpret_cast<float4*>(out + off), outc + off, (long long)chunk4, st,
-                       flags, (long long)off);
-    done4 += chunk4;
-  }
-  size_t off = 4 * body4;
-  if (off < n) {
-    size_t rest = n - off;
-    size_t g = (rest + BLOCK - 1) / BLOCK;
-    if (g > 65536) g = 65536;
-    hipLaunchKernelGGL(k_map_sincos_scalar<SC>, dim3((unsigned)g), dim3(BLOCK), 0, s, in + off,
-                       out + off, outc + off, (long long)rest, st, flags, (long long)off);
+  for (size_t done = 0; done < n;) {
+    const size_t cnt = n - done < LAUNCH_ELEMS ? n - done : LAUNCH_ELEMS;
+    const size_t tiles = (cnt + BLOCK * 4 * TILE_U - 1) / (BLOCK * 4 * TILE_U);
+    const size_t g = tiles < (size_t)grid ? tiles : (size_t)grid;
+    hipLaunchKernelGGL(k_map_sincos<SC>, dim3((unsigned)g), dim3(BLOCK), 0, s, in + done,
+                       out + done, outc + done, (long long)cnt, st, flags, (long long)done);
+    done += cnt;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e);
@@ -1653,38 +1536,13 @@ int launch_sincos(const float* in, float* out, size_t n, hipStream_t s, unsigned
 template <class Op, int U, int SL>
 int launch_map_f64(const double* in, double* out, size_t n, hipStream_t s, unsigned flags,
                    DevStats* st, int grid) {
-  uintptr_t ai = (uintptr_t)in, ao = (uintptr_t)out;
-  size_t head = 0;
-  if ((ai & 15) == (ao & 15)) {
-    head = ((16 - (ai & 15)) & 15) / 8;
-    if (head > n) head = n;
-  } else {
-    head = n;
-  }
-  size_t body2 = (n - head) / 2;
-  size_t tail = n - head - 2 * body2;
-  if (head) {
-    hipLaunchKernelGGL(k_map_f64_scalar<Op>, dim3((unsigned)((head + BLOCK - 1) / BLOCK > 65536
-                                                               ? 65536
-                                                               : (head + BLOCK - 1) / BLOCK)),
-                       dim3(BLOCK), 0, s, in, out, (long long)head, st, flags, 0LL);
-  }
-  for (size_t done = 0; done < body2;) {
-    size_t chunk2 = body2 - done;
-    if (chunk2 > ((size_t)1 << 30)) chunk2 = (size_t)1 << 30;
-    size_t tiles = (chunk2 + BLOCK * U - 1) / (BLOCK * U);
-    size_t g = tiles < (size_t)grid ? tiles : (size_t)grid;
-    size_t off = head + 2 * done;
-    hipLaunchKernelGGL((k_map_f64<Op, U, SL>), dim3((unsigned)g), dim3(BLOCK), 0, s,
-                       reinterpret_cast<const double2*>(in + off),
-                       reinterpret_cast<double2*>(out + off), (long long)chunk2, st, flags,
-                       (long long)off);
-    done += chunk2;
-  }
-  if (tail) {
-    size_t off = head + 2 * body2;
-    hipLaunchKernelGGL(k_map_f64_scalar<Op>, dim3(1), dim3(BLOCK), 0, s, in + off, out + off,
-                       (long long)tail, st, flags, (long long)off);
+  for (size_t done = 0; done < n;) {
+    const size_t cnt = n - done < LAUNCH_ELEMS ? n - done : LAUNCH_ELEMS;
+    const size_t tiles = (cnt + BLOCK * 2 * U - 1) / (BLOCK * 2 * U);
+    const size_t g = tiles < (size_t)grid ? tiles : (size_t)grid;
+    hipLaunchKernelGGL((k_map_f64<Op, U, SL>), dim3((unsigned)g), dim3(BLOCK), 0, s, in + done,
+                       out + done, (long long)cnt, st, flags, (long long)done);
+    done += cnt;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e);
@@ -1706,41 +1564,18 @@ int launch_variant64(const double* in, double* out, size_t n, hipStream_t s, uns
   return CR_E_TUNE;
 }
 
-// Complex binary32 map (n complex numbers, interleaved): 16-byte aligned
-// body of two complex numbers per vector, scalar head and tail.
+// Complex binary32 map (n complex numbers, interleaved), two a thread.
 template <class CF>
 int launch_complex(const float* in, float* out, size_t n, hipStream_t s, unsigned flags,
                    DevStats* st, int grid) {
-  uintptr_t ai = (uintptr_t)in, ao = (uintptr_t)out;
-  size_t head = 0;
-  if ((ai & 15) == (ao & 15) && (ai & 7) == 0) {
-    head = (ai & 15) ? 1 : 0;
-    if (head > n) head = n;
-  } else {
-    head = n;
-  }
-  const size_t body2 = (n - head) / 2;
-  const size_t tail = n - head - 2 * body2;
-  auto scalar = [&](size_t off, size_t cnt) {
-    size_t g = (cnt + BLOCK - 1) / BLOCK;
+  for (size_t done = 0; done < n;) {
+    const size_t cnt = n - done < LAUNCH_ELEMS ? n - done : LAUNCH_ELEMS;
+    size_t g = (cnt + 2 * BLOCK - 1) / (2 * BLOCK);
     if (g > (size_t)grid) g = grid;
-    hipLaunchKernelGGL(k_complex_scalar<CF>, dim3((unsigned)g), dim3(BLOCK), 0, s, in + 2 * off,
-                       out + 2 * off, (long long)cnt, st, flags, (long long)off);
-  };
-  if (head) scalar(0, head);
-  for (size_t done = 0; done < body2;) {
-    size_t chunk = body2 - done;
-    if (chunk > ((size_t)1 << 30)) chunk = (size_t)1 << 30;
-    size_t g = (chunk + BLOCK - 1) / BLOCK;
-    if (g > (size_t)grid) g = grid;
-    const size_t off = head + 2 * done;
-    hipLaunchKernelGGL(k_complex<CF>, dim3((unsigned)g), dim3(BLOCK), 0, s,
-                       reinterpret_cast<const float4*>(in + 2 * off),
-                       reinterpret_cast<float4*>(out + 2 * off), (long long)chunk, st, flags,
-                       (long long)off);
-    done += chunk;
+    hipLaunchKernelGGL(k_complex<CF>, dim3((unsigned)g), dim3(BLOCK), 0, s, in + 2 * done,
+                       out + 2 * done, (long long)cnt, st, flags, (long long)done);
+    done += cnt;
   }
-  if (tail) scalar(head + 2 * body2, tail);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e);
   return CR_OK;
