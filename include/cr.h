@@ -104,10 +104,11 @@ enum cr_flag {
    * functions (ids 0..18) with CR_IMPL_AUTO or CR_IMPL_F64_INTERNAL through
    * cr_eval_ex; other functions and implementations, and batch plans, return
    * CR_E_IMPL.  Overflow gives +-infinity or +-FLT_MAX as the mode
-   * says (Sec. 7.4); results that round to zero keep their sign.  Each
-   * element takes a double-double evaluation (about 2^-100 relative) with
-   * both ends of its error interval rounded in the mode, so these modes run
-   * at the accurate path's speed. */
+   * says (Sec. 7.4); results that round to zero keep their sign.  The
+   * binary64 fast path decides the elements whose value is certainly no
+   * binary32 number; the others take a double-double evaluation (about
+   * 2^-100 relative) with both ends of its error interval rounded in the
+   * mode. */
   CR_FLAG_ROUND_TOWARD_ZERO = 1u << 4,
   CR_FLAG_ROUND_UP = 2u << 4,
   CR_FLAG_ROUND_DOWN = 3u << 4

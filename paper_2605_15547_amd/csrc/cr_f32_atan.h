@@ -105,8 +105,9 @@ __device__ __forceinline__ bool atan_special_fast(float xf, float& res) {
   return spc;
 }
 
+// The fast path's binary64 value (error bound above).
 template <int KIND>
-__device__ __forceinline__ float atan_fast(float xf, const AtanTab& tb, bool& ok) {
+__device__ __forceinline__ double atan_value_fast(float xf, const AtanTab& tb) {
   // atan(2^100) and atan(inf) both round to RN(pi/2): clamp to keep 0 * inf out
   double x = (double)xf, a = fmin(fabs(x), 0x1p100);
   double hi, lo, yh;
@@ -132,7 +133,12 @@ __device__ __forceinline__ float atan_fast(float xf, const AtanTab& tb, bool& ok
       yh = p.hi + (p.lo + ((neg ? PI_LO : 0.0) + (neg ? -lo : lo)));
     }
   }
-  float res = round_f32_bits<ATAN_TEST_E>(yh, ok);
+  return yh;
+}
+
+template <int KIND>
+__device__ __forceinline__ float atan_fast(float xf, const AtanTab& tb, bool& ok) {
+  float res = round_f32_bits<ATAN_TEST_E>(atan_value_fast<KIND>(xf, tb), ok);
   float sp;
   if (atan_special_fast<KIND>(xf, sp)) {
     res = sp;

@@ -4,18 +4,25 @@
 // The paper's CPU library supports every IEEE 754 rounding mode: its kernels
 // end with round-to-zero + sticky so that the final conversion can round in
 // the user's mode (Sec. II-A); its GPU runs were round to nearest only
-// (Sec. III-C).  Here a directed mode runs each element through a double-
-// double evaluation of about 2^-100 relative accuracy (the accurate paths of
-// the round-to-nearest kernels, with the longer series where those were cut
-// to the round-to-nearest hard cases) and rounds both ends of its error
-// interval as round-to-odd binary64 numbers in the requested mode
-// (cr_round.h).  In a directed mode the rounding boundaries are the binary32
-// numbers themselves, so three kinds of input are decided before that:
+// (Sec. III-C).  In a directed mode the rounding boundaries are the binary32
+// numbers themselves instead of the midpoints between them, so each function
+// has two paths here as it has for round to nearest:
+//  * fast: the binary64 value of the round-to-nearest fast path, certified when
+//    no binary32 number lies within its error bound (read off the 29 low bits
+//    of the value), truncated to binary32 and moved one encoding away from zero
+//    where the mode rounds up in magnitude;
+//  * accurate (*_dir): a double-double evaluation of about 2^-100 relative
+//    accuracy (the accurate paths of the round-to-nearest kernels, with the
+//    longer series where those were cut to the round-to-nearest hard cases),
+//    both ends of its error interval rounded as round-to-odd binary64 numbers
+//    in the requested mode (cr_round.h).  It takes the lanes that fail the fast
+//    test: values next to a binary32 number.
+// Three kinds of input are decided before the evaluation on either path:
 //  * exact results (exp2f at integers, exp10f at 1..10, log2f at powers of
 //    two, log10f at 10..10^10, and the special values): an error interval
 //    around an exact binary32 result always straddles it;
-//  * tiny arguments, |x| < 2^-26, where f(x) = x (1 + c x^2 + ...) or
-//    1 + c x + ... lies within a quarter ulp of x or 1 on a known side;
+//  * tiny arguments, where f(x) = x (1 + c x^2 + ...) or 1 + c x + ... lies
+//    strictly between x (or 1) and a neighbour on a known side;
 //  * saturation that the evaluation clamps (expm1 near -1, infinite inputs).
 // Every other result is certified by the rounding of both interval ends.
 #pragma once
@@ -34,7 +41,87 @@ constexpr double DIR_DREL = 0x1p-90;  // relative bound used with the ~2^-100 ev
 __device__ __forceinline__ float quiet_nan(float x) { return bits_f32(f32_bits(x) | 0x00400000u); }
 __device__ __forceinline__ int sign_of(float x) { return x < 0.0f ? -1 : 1; }
 
+// ------------------------------------------------- fast paths: the rounding
+// 1 where mode RM rounds a magnitude of the sign of the encoding b up, else 0
+template <int RM>
+__device__ __forceinline__ uint32_t dir_away(uint32_t b) {
+  return RM == RM_RZ ? 0u : RM == RM_RU ? 1u - (b >> 31) : b >> 31;
+}
+// The rounding of a real strictly between x and the next binary32 number of
+// larger (GROW) or smaller magnitude, x != 0; x itself for +-0.
+template <int RM, bool GROW>
+__device__ __forceinline__ float dir_beside(float x) {
+  const uint32_t b = f32_bits(x);
+  const uint32_t r = GROW ? b + dir_away<RM>(b) : b - 1u + dir_away<RM>(b);
+  return x == 0.0f ? x : bits_f32(r);
+}
+// y truncated to binary32 (|y| >= 2^-126): the 29 low bits cleared, then an exact
+// conversion, or an infinity beyond the format
+__device__ __forceinline__ float f32_trunc(double y) {
+  return (float)__hiloint2double(__double2hiint(y), __double2loint(y) & 0xe0000000);
+}
+// The rounding of y in mode RM (|y| >= 2^-126) when it is not a binary32 number: its
+// truncation (the largest finite number where y overflows: OVF), the next encoding where
+// the mode rounds the magnitude up (from the largest finite number: an infinity)
+template <int RM, bool OVF>
+__device__ __forceinline__ float dir_round(double y) {
+  float f = f32_trunc(y);
+  if (OVF) f = __builtin_amdgcn_fmed3f(f, -0x1.fffffep127f, 0x1.fffffep127f);
+  const uint32_t b = f32_bits(f);
+  return bits_f32(b + dir_away<RM>(b));
+}
+// The test of a directed mode: within the binade of y (|y| >= 2^-126) the binary32
+// numbers are the binary64 numbers whose 29 low bits are 0, an integer number of
+// ulps of y; when the low bits differ from 0 (mod 2^29) by more than E, none lies
+// within E + 1 ulps, so the test is sound for an error bound below E + 1 ulps.
+// A binade edge is itself a binary32 number.
+template <unsigned E>
+__device__ __forceinline__ bool dir_certain(double y) {
+  const uint32_t lo = (uint32_t)__double2loint(y);
+  return ((lo + E) & 0x1fffffffu) > 2u * E;
+}
+
 // ------------------------------------------------------------ exp family
+// Fast path.  Error bounds of exp_value_fast (cr_f32_exp.h): 2 ulps, expm1 8.  The
+// results cover the whole range of the format, below the normal numbers and beyond
+// the largest one too, so the test compares y with the nearest binary32 number f
+// (exact in binary64; an infinity is as far as can be): certain when they differ by
+// more than the bound.  |f| > |y| then means the truncation is the encoding before
+// f's -- 0 or a subnormal number, or the largest finite one.
+// exp2f at integers gives an exact power of two (q = 0, T = 1).
+template <int K, int RM>
+__device__ __forceinline__ float exp_fast_dir(float xf, const ExpTab& tb, bool& ok) {
+  const double y = exp_value_fast<K>(xf, tb);
+  const float f = (float)y;
+  const double fd = (double)f;
+  ok = fabs(fd - y) > fabs(y) * (K == EXPK_EM1 ? 0x1p-49 : 0x1p-51);
+  const uint32_t fb = f32_bits(f) - (fabs(fd) > fabs(y) ? 1u : 0u);
+  float r = bits_f32(fb + dir_away<RM>(fb));
+  if (K == EXPK_2) {
+    const bool exact = rintf(xf) == xf && xf >= -149.0f && xf <= 127.0f;
+    r = exact ? f : r;
+    ok |= exact;
+  }
+  // NaN, infinities, zeros, tiny arguments, and expm1 below -18
+  const bool tiny = fabsf(xf) < DIR_TINY;
+  float v = xf;  // +inf; NaN is quieted below
+  if (K == EXPK_EM1) {
+    // expm1 x = x + x^2/2 + ...: above x, by magnitude up or down with its sign
+    const float t = xf < 0.0f ? dir_beside<RM, false>(xf) : dir_beside<RM, true>(xf);
+    v = tiny ? t : v;
+    v = xf <= -18.0f ? dir_beside<RM, false>(-1.0f) : v;
+    v = xf == -INFINITY ? -1.0f : v;
+  } else {
+    // b^x = 1 + x ln b + ...
+    const float t = xf < 0.0f ? dir_beside<RM, false>(1.0f) : dir_beside<RM, true>(1.0f);
+    v = tiny ? (xf == 0.0f ? 1.0f : t) : v;
+    v = xf == -INFINITY ? 0.0f : v;
+  }
+  const bool sp = __builtin_amdgcn_class(xf, 0x207) | tiny | (K == EXPK_EM1 && xf <= -18.0f);
+  ok |= sp;
+  return sp ? nan_or(xf, v) : r;
+}
+
 template <int K, int RM>
 __device__ __noinline__ AccResult exp_dir(float xf, const ExpTab& tb) {
   if (xf != xf) return {quiet_nan(xf), 1};
@@ -92,6 +179,29 @@ __device__ __forceinline__ dd log1p_dd_long(dd t) {
   return {2.0 * l.hi, 2.0 * l.lo};
 }
 
+// Fast path.  Error bound of log_value_fast (cr_f32_log.h): below 2 ulps.  log2f
+// of a normal power of two is exact (t = 0 and a zero table entry), as is +0 at 1;
+// log1p x = x - x^2/2 + ... lies below x, by less than 2^-26 |x| for |x| < 2^-25.
+template <int K, int RM>
+__device__ __forceinline__ float log_fast_dir(float xf, const LogTab& tb, bool& ok) {
+  const double y = log_value_fast<K>(xf, tb);
+  ok = dir_certain<LOG_TEST_E>(y);
+  float r = dir_round<RM, false>(y);
+  const bool exact = K == LOGK_2 ? (f32_bits(xf) & 0x007fffffu) == 0 : K != LOGK_1P && xf == 1.0f;
+  r = exact ? (float)y : r;
+  ok |= exact;
+  float v;
+  bool sp = log_special<K>(xf, v);
+  if (K == LOGK_1P) {
+    const bool tiny = fabsf(xf) < 0x1p-25f;
+    const float t = xf < 0.0f ? dir_beside<RM, true>(xf) : dir_beside<RM, false>(xf);
+    v = tiny ? t : v;
+    sp |= tiny;
+  }
+  ok |= sp;
+  return sp ? v : r;
+}
+
 template <int K, int RM>
 __device__ __noinline__ AccResult log_dir(float xf, const LogTab& tb) {
   float sp;
@@ -130,18 +240,81 @@ __device__ __noinline__ AccResult log_dir(float xf, const LogTab& tb) {
 // z = RN(x^-1/2) is decided exactly (cr_f32_rsqrt.h); the sign of z^2 x - 1
 // (z^2 exact in binary64, one rounding in the fma) tells whether z lies above
 // or below x^-1/2, and it is zero exactly when x^-1/2 is z.
+// There is nothing to certify: this is the fast path and the accurate one.
+template <int RM>
+__device__ __forceinline__ float rsqrt_fast_dir(float xf) {
+  float sp;
+  const bool s = rsqrt_special(xf, sp);
+  const float x = s ? 1.0f : xf;
+  const float z = rsqrt_eval(x);
+  const double zd = (double)z;
+  const double d = fma(zd * zd, (double)x, -1.0);
+  // z > 0 lies above x^-1/2 when d > 0 and below it when d < 0
+  uint32_t b = f32_bits(z);
+  if (RM == RM_RU)
+    b += d < 0.0 ? 1u : 0u;
+  else
+    b -= d > 0.0 ? 1u : 0u;
+  return s ? sp : bits_f32(b);
+}
 template <int RM>
 __device__ __noinline__ AccResult rsqrt_dir(float xf) {
-  float sp;
-  if (rsqrt_special(xf, sp)) return {sp, 1};
-  const float z = rsqrt_eval(xf);
-  const double zd = (double)z;
-  const double d = fma(zd * zd, (double)xf, -1.0);
-  if (d == 0.0) return {z, 1};
-  return {round_near_float<RM>(z, d > 0.0 ? -1 : 1), 1};
+  return {rsqrt_fast_dir<RM>(xf), 1};
 }
 
 // ------------------------------------------------------------------- trig
+// Fast path.  sin and cos: below 512 ulps for results of at least 2^-12
+// (round_trig_fast); tan: the absolute bound of tan_value_fast, both ends
+// truncated.  |x| < 2^-12: sin x lies below x in magnitude and tan x above it, by
+// less than 2^-25.5 |x|, and cos x below 1 by less than 2^-25, on this side of
+// the next binary32 number.
+template <int KIND, int RM>
+__device__ __forceinline__ bool trig_special_dir(float xf, float& res) {
+  const bool inf = fabsf(xf) == INFINITY;
+  const float t = KIND == TRIGK_COS ? (xf == 0.0f ? 1.0f : dir_beside<RM, false>(1.0f))
+                                    : dir_beside<RM, KIND == TRIGK_TAN>(xf);
+  res = nan_or(xf, inf ? bits_f32(0x7fc00000u) : t);
+  return __builtin_amdgcn_class(xf, 0x207) | (fabsf(xf) < 0x1p-12f);
+}
+template <int RM>
+__device__ __forceinline__ float trig_round_dir(double y, bool& ok) {
+  ok = dir_certain<512>(y) && fabs(y) >= 0x1p-12;
+  return dir_round<RM, false>(y);
+}
+template <int KIND, int RM>
+__device__ __forceinline__ float trig_fast_dir(float xf, const TrigTab& tb, bool& ok) {
+  TrigFast F = trig_fast_core(xf, tb);
+  const uint32_t xs = sign_mask(xf);
+  float r;
+  if (KIND == TRIGK_COS) {
+    r = trig_round_dir<RM>(flip(F.c, F.sc), ok);
+  } else if (KIND == TRIGK_SIN) {
+    r = trig_round_dir<RM>(flip(F.s, F.ss ^ xs), ok);
+  } else {
+    double e;
+    const double t = flip(tan_value_fast(F, e), F.ss ^ F.sc ^ xs);
+    ok = f32_bits(f32_trunc(t - e)) == f32_bits(f32_trunc(t + e));
+    r = dir_round<RM, false>(t);
+  }
+  float v;
+  const bool sp = trig_special_dir<KIND, RM>(xf, v);
+  ok |= sp;
+  return sp ? v : r;
+}
+template <int RM>
+__device__ __forceinline__ float sincos_fast_dir(float xf, const TrigTab& tb, float& c, bool& ok) {
+  TrigFast F = trig_fast_core(xf, tb);
+  bool ok1, ok2;
+  const float s = trig_round_dir<RM>(flip(F.s, F.ss ^ sign_mask(xf)), ok1);
+  c = trig_round_dir<RM>(flip(F.c, F.sc), ok2);
+  float vs, vc;
+  const bool sp = trig_special_dir<TRIGK_SIN, RM>(xf, vs);
+  trig_special_dir<TRIGK_COS, RM>(xf, vc);
+  ok = (ok1 && ok2) || sp;
+  c = sp ? vc : c;
+  return sp ? vs : s;
+}
+
 template <int KIND, int RM>
 __device__ __noinline__ AccResult trig_dir(float xf, const TrigTab& tb) {
   float sp;
@@ -189,6 +362,24 @@ __device__ __noinline__ AccResult2 sincos_dir(float xf, const TrigTab& tb) {
 }
 
 // ------------------------------------------------------------------- atan
+// Fast path, within 16 ulps (cr_f32_atan.h).  |x| < 2^-13: atan x lies below x in
+// magnitude, asin x above it, by less than 2^-27 |x|.
+template <int KIND, int RM>
+__device__ __forceinline__ float atan_fast_dir(float xf, const AtanTab& tb, bool& ok) {
+  const double y = atan_value_fast<KIND>(xf, tb);
+  ok = dir_certain<ATAN_TEST_E>(y);
+  const float r = dir_round<RM, false>(y);
+  float v;
+  bool sp = atan_special(xf, KIND, v);
+  if (KIND != ATANK_ACOS) {
+    const bool tiny = fabsf(xf) < 0x1p-13f;
+    v = tiny ? dir_beside<RM, KIND == ATANK_ASIN>(xf) : v;
+    sp |= tiny;
+  }
+  ok |= sp;
+  return sp ? v : r;
+}
+
 template <int KIND, int RM>
 __device__ __noinline__ AccResult atan_dir(float xf, const AtanTab& tb) {
   float sp;
@@ -216,6 +407,31 @@ __device__ __noinline__ AccResult atan_dir(float xf, const AtanTab& tb) {
 }
 
 // ------------------------------------------------------------- hyperbolic
+// Fast path, within 32 ulps (cr_f32_hyp.h).  |x| < 2^-13: sinh x lies above x in
+// magnitude, tanh x below it, by less than 2^-27 |x|, cosh x above 1 by less than
+// 2^-26; |x| >= 10: tanh x lies below 1 in magnitude by less than 2^-27.
+template <int KIND, int RM>
+__device__ __forceinline__ float hyp_fast_dir(float xf, const ExpTab& tb, bool& ok) {
+  const double a = hyp_value_fast<KIND>(xf, tb);
+  const double y = KIND != HYPK_COSH && xf < 0.0f ? -a : a;
+  ok = dir_certain<HYP_TEST_E>(y);
+  const float r = dir_round<RM, KIND != HYPK_TANH>(y);
+  const bool tiny = fabsf(xf) < 0x1p-13f;
+  bool sp = __builtin_amdgcn_class(xf, 0x207) | tiny;
+  float v;
+  if (KIND == HYPK_COSH) {
+    v = tiny ? (xf == 0.0f ? 1.0f : dir_beside<RM, true>(1.0f)) : fabsf(xf);
+  } else if (KIND == HYPK_SINH) {
+    v = tiny ? dir_beside<RM, true>(xf) : xf;
+  } else {
+    const float one = copysignf(1.0f, xf);
+    v = fabsf(xf) == INFINITY ? one : dir_beside<RM, false>(tiny ? xf : one);
+    sp |= fabsf(xf) >= 10.0f;
+  }
+  ok |= sp;
+  return sp ? nan_or(xf, v) : r;
+}
+
 template <int KIND, int RM>
 __device__ __noinline__ AccResult hyp_dir(float xf, const ExpTab& tb) {
   if (xf != xf) return {quiet_nan(xf), 1};

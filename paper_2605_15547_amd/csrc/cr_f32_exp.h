@@ -161,25 +161,28 @@ __device__ __forceinline__ bool exp_special(float xf, float& res) {
   return nan | tie | zero;
 }
 
-// Fast path: binary64 evaluation and the rounding test.  ok = false means the
-// returned value is not certified and the accurate path must decide.
+// The fast path's binary64 value (error bound above).
 template <int K>
-__device__ __forceinline__ float exp_fast(float xf, const ExpTab& tb, bool& ok) {
+__device__ __forceinline__ double exp_value_fast(float xf, const ExpTab& tb) {
   ExpSetup<K> S = exp_setup<K>(xf, tb);
   double r = S.r;
   double p = EXPM1_P[EXPM1_P_DEG];
 #pragma unroll
   for (int i = EXPM1_P_DEG - 1; i >= 0; i--) p = fma(p, r, EXPM1_P[i]);
   double q = fma(r * r, p, r);  // e^r - 1
-  double yh;
   if (K == EXPK_EM1) {
     double s = pow2i(S.m);
     double D = fma(s, S.T.x, -1.0);
-    yh = fma(s, fma(S.T.x, q, S.T.y), D);
-  } else {
-    yh = scale_exp(S.T.x + fma(S.T.x, q, S.T.y), S.m);  // |m| <= 217: stays normal
+    return fma(s, fma(S.T.x, q, S.T.y), D);
   }
-  float res = round_f32_fast<ExpErr<K>::LOG2E>(yh, ok);
+  return scale_exp(S.T.x + fma(S.T.x, q, S.T.y), S.m);  // |m| <= 217: stays normal
+}
+
+// Fast path: binary64 evaluation and the rounding test.  ok = false means the
+// returned value is not certified and the accurate path must decide.
+template <int K>
+__device__ __forceinline__ float exp_fast(float xf, const ExpTab& tb, bool& ok) {
+  float res = round_f32_fast<ExpErr<K>::LOG2E>(exp_value_fast<K>(xf, tb), ok);
   float sp;
   if (exp_special<K>(xf, sp)) {
     res = sp;

@@ -199,8 +199,9 @@ __device__ __forceinline__ bool log1p_special_fast(float xf, float& res) {
   return __builtin_amdgcn_class(xf, 0x207) | (fabsf(xf) < 0x1p-25f) | (xf <= -1.0f);
 }
 
+// The fast path's binary64 value (error bound above).
 template <int K>
-__device__ __forceinline__ float log_fast(float xf, const LogTab& tb, bool& ok) {
+__device__ __forceinline__ double log_value_fast(float xf, const LogTab& tb) {
   LogSetup S = log_setup<K>(xf, tb);
   double t = S.t;
   double Q = log_Q<K>(t);
@@ -211,10 +212,14 @@ __device__ __forceinline__ float log_fast(float xf, const LogTab& tb, bool& ok) 
   const double Ah = fma(ed, log_C_hi<K>(), S.L.x);
   const double lo = K == LOGK_2 ? S.L.y : fma(ed, log_C_lo<K>(), S.L.y);
   double inner = fma(t, Q, lo);
-  double yh = Ah + fma(log_K<K>(), t, inner);
+  return Ah + fma(log_K<K>(), t, inner);
+}
+
+template <int K>
+__device__ __forceinline__ float log_fast(float xf, const LogTab& tb, bool& ok) {
   // logf, log2f and log10f round to normal binary32 numbers (or to +0 at 1),
   // log1pf too except for subnormal x, which are left to the accurate path
-  float res = round_f32_bits<LOG_TEST_E>(yh, ok);
+  float res = round_f32_bits<LOG_TEST_E>(log_value_fast<K>(xf, tb), ok);
   float sp;
   if (K == LOGK_1P ? log1p_special_fast(xf, sp) : log_special_fast(xf, sp)) {
     res = sp;

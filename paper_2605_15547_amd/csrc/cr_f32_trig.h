@@ -405,6 +405,18 @@ __device__ __noinline__ AccResult2 sincos_accurate(float xf, const TrigTab& tb) 
   return {rs, rc, (ok1 && ok2) ? 1 : 0};
 }
 
+// tan |x| up to its sign, and an absolute error bound: t = s / c from the
+// hardware reciprocal and two corrections by exact residuals (each squares the
+// relative error of the estimate), within 2^-52 |t|; then the absolute errors
+// of s and c magnified by 1/|c|:
+// |dt| <= |t| 2^-52 + (es + |t| ec) / |c| (bound with margins)
+__device__ __forceinline__ double tan_value_fast(const TrigFast& F, double& e) {
+  const double t = div_fast(F.s, F.c);
+  const double ic = __builtin_amdgcn_rcp(F.c);
+  e = fma(fabs(t), 0x1p-50, (F.es + fabs(t) * F.ec) * fabs(ic) * 2.0);
+  return t;
+}
+
 template <int KIND>
 __device__ __forceinline__ float trig_fast(float xf, const TrigTab& tb, bool& ok) {
   TrigFast F = trig_fast_core(xf, tb);
@@ -415,13 +427,8 @@ __device__ __forceinline__ float trig_fast(float xf, const TrigTab& tb, bool& ok
   } else if (KIND == TRIGK_SIN) {
     res = round_trig_fast(flip(F.s, F.ss ^ xs), ok);
   } else {
-    // t = s / c from the hardware reciprocal and two corrections by exact
-    // residuals (each squares the relative error of the estimate), within
-    // 2^-52 |t|; then the absolute errors of s and c magnified by 1/|c|:
-    // |dt| <= |t| 2^-52 + (es + |t| ec) / |c| (bound with margins)
-    const double t = div_fast(F.s, F.c);
-    const double ic = __builtin_amdgcn_rcp(F.c);
-    double e = fma(fabs(t), 0x1p-50, (F.es + fabs(t) * F.ec) * fabs(ic) * 2.0);
+    double e;
+    const double t = tan_value_fast(F, e);
     res = round_f32_fast_abs(flip(t, F.ss ^ F.sc ^ xs), e, ok);
   }
   float sp;

@@ -78,18 +78,94 @@ constexpr int QCAP = 512;                   // deferred elements held in LDS
 constexpr int QCHECK = 8;                   // tiles between two looks at the queue
 constexpr int QFLUSH = QCAP / 2;            // flush when the queue is fuller than this
 
-// Streaming accesses: each input is read once and each output written once,
-// so the 128-bit loads and stores carry the nontemporal hint (measured on
-// MI355X: a plain 2^26-float copy moves 5.1-5.5 TB/s without it and
-// 5.8-6.6 TB/s with it, depending on the grid).
+// Streaming accesses: each input is read once and each output written once, so
+// the 128-bit loads and stores carry the nontemporal hint (measured on MI355X: a
+// plain 2^26-float copy moves 5.1-5.5 TB/s without it and 5.8-6.6 TB/s with it,
+// depending on the grid).
+//
+// Tiles of the map kernels.  T is float or double, VN elements make a 128-bit
+// vector, and a tile is U vectors per thread (vector u of thread t is vector
+// t + u BLOCK of the tile); nv = n / VN whole vectors.  A tile is accessed through
+// a buffer descriptor whose base is the tile's first vector and whose size ends at
+// nv, built by scalar instructions from the tile's number: the hardware drops
+// stores past the end and returns 0 for loads there, so the ragged last tile takes
+// the same instructions as any other and no lane computes a 64-bit address or a
+// bounds check (expf 4% faster than with per-lane addresses at 2^24 elements,
+// binary64 log 4%, sincosf 3%).
+// gfx950 takes 128-bit accesses at any 4-byte address, so a slice of an array, a
+// cosine block behind an odd number of sines and an aligned buffer all run the
+// same kernel.  The n % VN elements after the last vector are evaluated one to a
+// thread by the workgroup that takes the last tile.
 #ifndef CR_NT
 #define CR_NT 1
 #endif
-// The vector types carry the alignment of one element only: gfx950 takes 128-bit
-// global accesses at any 4-byte address, so a slice of an array, a cosine block
-// behind an odd number of sines and an aligned buffer all run the same kernel.
+typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
+template <class T>
+struct Vec;
+template <>
+struct Vec<float> {
+  using type = float4;
+  static constexpr int N = 4;
+};
+template <>
+struct Vec<double> {
+  using type = double2;
+  static constexpr int N = 2;
+};
+
+// The tile of tv vectors that starts at vector t0 of the nv vectors at p (counts
+// of vectors fit in 32 bits: LAUNCH_ELEMS elements a launch).
+template <class T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const T* p, int t0, int nv, int tv) {
+  // the same in every lane: scalar registers (and past the end: an empty tile)
+  t0 = min(__builtin_amdgcn_readfirstlane(t0), nv);
+  const int left = min(nv - t0, tv);
+  // 0x00020000: raw buffer, 32-bit data format, bounds checked by the byte
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p) + (size_t)Vec<T>::N * (unsigned)t0,
+                                           0, 16 * left, 0x00020000);
+}
+template <class T, int U>
+__device__ __forceinline__ void tile_load(typename Vec<T>::type (&v)[U], const T* in, int t0,
+                                          int nv) {
+  const __amdgpu_buffer_rsrc_t r = tile_rsrc(in, t0, nv, BLOCK * U);
+#pragma unroll
+  for (int u = 0; u < U; u++) {
+    const v4u_t x = __builtin_amdgcn_raw_buffer_load_b128(r, 16 * threadIdx.x, 16 * BLOCK * u,
+                                                          CR_NT ? 2 : 0);
+    __builtin_memcpy(&v[u], &x, 16);
+  }
+}
+template <class T, int U>
+__device__ __forceinline__ void tile_store(const typename Vec<T>::type (&v)[U], T* out, int t0,
+                                           int nv) {
+  const __amdgpu_buffer_rsrc_t r = tile_rsrc(out, t0, nv, BLOCK * U);
+#pragma unroll
+  for (int u = 0; u < U; u++) {
+    v4u_t x;
+    __builtin_memcpy(&x, &v[u], 16);
+    __builtin_amdgcn_raw_buffer_store_b128(x, r, 16 * threadIdx.x, 16 * BLOCK * u, CR_NT ? 2 : 0);
+  }
+}
+// Bit VN u + c is set where vector u of the tile lies below nv.
+template <class T, int U>
+__device__ __forceinline__ unsigned tile_live(int t0, int nv) {
+  constexpr int VN = Vec<T>::N;
+  unsigned m = 0;
+#pragma unroll
+  for (int u = 0; u < U; u++)
+    m |= (int)threadIdx.x + u * BLOCK < nv - t0 ? ((1u << VN) - 1u) << (VN * u) : 0u;
+  return m;
+}
+// The tail's elements go to the workgroup that takes the tile containing vector nv
+// (a ragged tile, or the one after the last full tile): the workgroup's last tile
+// or, t0 being where it left the loop, the next.
+__device__ __forceinline__ bool takes_tail(int t0, int step, int nv, int tv) {
+  const int d = nv - t0, e = d + step;
+  return (d >= 0 && d < tv) || (e >= 0 && e < tv);
+}
+
+// One 128-bit access at any 4-byte address
 typedef float v4f_t __attribute__((ext_vector_type(4), aligned(4)));
-typedef double v2d_t __attribute__((ext_vector_type(2), aligned(8)));
 __device__ __forceinline__ float4 ld_stream4(const float* p) {
   const v4f_t* q = reinterpret_cast<const v4f_t*>(p);
   v4f_t v = CR_NT ? __builtin_nontemporal_load(q) : *q;
@@ -103,101 +179,11 @@ __device__ __forceinline__ void st_stream4(float* p, float4 a) {
   else
     *q = v;
 }
-__device__ __forceinline__ double2 ld_stream2(const double* p) {
-  const v2d_t* q = reinterpret_cast<const v2d_t*>(p);
-  v2d_t v = CR_NT ? __builtin_nontemporal_load(q) : *q;
-  return make_double2(v.x, v.y);
-}
-__device__ __forceinline__ void st_stream2(double* p, double2 a) {
-  v2d_t v = {a.x, a.y};
-  v2d_t* q = reinterpret_cast<v2d_t*>(p);
-  if (CR_NT)
-    __builtin_nontemporal_store(v, q);
-  else
-    *q = v;
-}
-
-// Tiles of the map kernels.  T is float or double, VN elements make a 128-bit
-// vector, and a tile is U vectors per thread (vector u of thread t at element
-// VN (t + u BLOCK) of the tile).  `full` (the whole tile lies below n) is the
-// same for every thread, so whole tiles pay no bounds check; only the last tile
-// of a launch takes the element-by-element branches, which also read and write
-// the 1..VN-1 elements after the last whole vector.
-template <class T>
-struct Vec;
-template <>
-struct Vec<float> {
-  using type = float4;
-  static constexpr int N = 4;
-  static __device__ __forceinline__ float4 load(const float* p) { return ld_stream4(p); }
-  static __device__ __forceinline__ void store(float* p, float4 v) { st_stream4(p, v); }
-};
-template <>
-struct Vec<double> {
-  using type = double2;
-  static constexpr int N = 2;
-  static __device__ __forceinline__ double2 load(const double* p) { return ld_stream2(p); }
-  static __device__ __forceinline__ void store(double* p, double2 v) { st_stream2(p, v); }
-};
-
-// Elements of the tile at t0 that lie past n hold 1 after the load.
-template <class T, int U>
-__device__ __forceinline__ void tile_load(typename Vec<T>::type (&v)[U], const T* in, long long t0,
-                                          long long n, bool full) {
-  constexpr int VN = Vec<T>::N;
-  const T* p = in + t0;
-  if (full) {
-#pragma unroll
-    for (int u = 0; u < U; u++) v[u] = Vec<T>::load(p + VN * (threadIdx.x + u * BLOCK));
-  } else {
-    const int left = (int)(n - t0);  // below the tile's size, possibly <= 0
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      const int i = VN * (threadIdx.x + u * BLOCK);
-      T* e = reinterpret_cast<T*>(&v[u]);
-#pragma unroll
-      for (int c = 0; c < VN; c++) e[c] = i + c < left ? p[i + c] : T(1);
-    }
-  }
-}
-template <class T, int U>
-__device__ __forceinline__ void tile_store(const typename Vec<T>::type (&v)[U], T* out,
-                                           long long t0, long long n, bool full) {
-  constexpr int VN = Vec<T>::N;
-  T* p = out + t0;
-  if (full) {
-#pragma unroll
-    for (int u = 0; u < U; u++) Vec<T>::store(p + VN * (threadIdx.x + u * BLOCK), v[u]);
-  } else {
-    const int left = (int)(n - t0);
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      const int i = VN * (threadIdx.x + u * BLOCK);
-      const T* e = reinterpret_cast<const T*>(&v[u]);
-#pragma unroll
-      for (int c = 0; c < VN; c++)
-        if (i + c < left) p[i + c] = e[c];
-    }
-  }
-}
-// Bit VN u + c is set where element c of vector u lies below n.
-template <class T, int U>
-__device__ __forceinline__ unsigned tile_live(long long t0, long long n) {
-  constexpr int VN = Vec<T>::N;
-  const int left = (int)(n - t0);
-  unsigned m = 0;
-#pragma unroll
-  for (int u = 0; u < U; u++)
-#pragma unroll
-    for (int c = 0; c < VN; c++)
-      m |= (unsigned)(VN * (int)(threadIdx.x + u * BLOCK) + c < left) << (VN * u + c);
-  return m;
-}
 
 // ------------------------------------------------------------ evaluators
 // Op::fast(x, tab, ok): binary64 fast path and rounding test (inlined).
 // Op::accurate(x, tab): double-double path from x alone (out of line).
-// Op::dir<RM>(x, tab): the result in a directed rounding mode (out of line).
+// Op::fast_dir<RM>, Op::dir<RM>: the same two in a directed rounding mode.
 template <int K>
 struct OpExp {
   using Tab = ExpTab;
@@ -208,6 +194,10 @@ struct OpExp {
   }
   static __device__ __forceinline__ AccResult accurate(float x, const Tab& t) {
     return exp_accurate<K>(x, t);
+  }
+  template <int RM>
+  static __device__ __forceinline__ float fast_dir(float x, const Tab& t, bool& ok) {
+    return exp_fast_dir<K, RM>(x, t, ok);
   }
   template <int RM>
   static __device__ __forceinline__ AccResult dir(float x, const Tab& t) {
@@ -225,6 +215,10 @@ struct SinCosF64 {
   }
   static __device__ __forceinline__ AccResult2 accurate(float x, const Tab& t) {
     return sincos_accurate(x, t);
+  }
+  template <int RM>
+  static __device__ __forceinline__ float fast_dir(float x, const Tab& t, float& c, bool& ok) {
+    return sincos_fast_dir<RM>(x, t, c, ok);
   }
   template <int RM>
   static __device__ __forceinline__ AccResult2 dir(float x, const Tab& t) {
@@ -335,6 +329,10 @@ struct OpLog {
     return log_accurate<K>(x, t);
   }
   template <int RM>
+  static __device__ __forceinline__ float fast_dir(float x, const Tab& t, bool& ok) {
+    return log_fast_dir<K, RM>(x, t, ok);
+  }
+  template <int RM>
   static __device__ __forceinline__ AccResult dir(float x, const Tab& t) {
     return log_dir<K, RM>(x, t);
   }
@@ -351,6 +349,11 @@ struct OpRsqrt {
   static __device__ __noinline__ AccResult accurate(float x, const Tab&) {
     bool ok;
     return {rsqrt_fast(x, ok), 1};
+  }
+  template <int RM>
+  static __device__ __forceinline__ float fast_dir(float x, const Tab&, bool& ok) {
+    ok = true;
+    return rsqrt_fast_dir<RM>(x);
   }
   template <int RM>
   static __device__ __forceinline__ AccResult dir(float x, const Tab&) {
@@ -370,6 +373,10 @@ struct OpTrig {
     return trig_accurate<KIND>(x, t);
   }
   template <int RM>
+  static __device__ __forceinline__ float fast_dir(float x, const Tab& t, bool& ok) {
+    return trig_fast_dir<KIND, RM>(x, t, ok);
+  }
+  template <int RM>
   static __device__ __forceinline__ AccResult dir(float x, const Tab& t) {
     return trig_dir<KIND, RM>(x, t);
   }
@@ -387,6 +394,10 @@ struct OpAtan {
     return atan_accurate<KIND>(x, t);
   }
   template <int RM>
+  static __device__ __forceinline__ float fast_dir(float x, const Tab& t, bool& ok) {
+    return atan_fast_dir<KIND, RM>(x, t, ok);
+  }
+  template <int RM>
   static __device__ __forceinline__ AccResult dir(float x, const Tab& t) {
     return atan_dir<KIND, RM>(x, t);
   }
@@ -402,6 +413,10 @@ struct OpHyp {
   }
   static __device__ __forceinline__ AccResult accurate(float x, const Tab& t) {
     return hyp_accurate<KIND>(x, t);
+  }
+  template <int RM>
+  static __device__ __forceinline__ float fast_dir(float x, const Tab& t, bool& ok) {
+    return hyp_fast_dir<KIND, RM>(x, t, ok);
   }
   template <int RM>
   static __device__ __forceinline__ AccResult dir(float x, const Tab& t) {
@@ -478,8 +493,7 @@ __device__ __forceinline__ void flush_queue(Deferred& q, const typename Op::Tab&
 // Measured against a scalar kernel for heads, tails and pointers of different
 // alignment beside a 16-byte aligned body: expf of 2^22 - 1 elements 10.4 -> 8.1
 // us (one launch instead of two), of 2^26 elements from a slice x[1:] 159 -> 97
-// us (scalar accesses before), sincosf of a slice of 2^24 73 -> 49 us; aligned
-// arrays unchanged within 1%.
+// us (scalar accesses before), sincosf of a slice of 2^24 73 -> 49 us.
 // Launch-shape variants (chosen per function by the autotuner, cr_autotune):
 //   U   float4 vectors per thread per tile (4U elements per thread),
 //   PF  1: the next tile's vectors are loaded while this one is evaluated,
@@ -499,14 +513,8 @@ __global__ void __launch_bounds__(BLOCK)
               long long elem_base) {
   __shared__ typename Op::Tab lds_tab;
   __shared__ Deferred q;
-  constexpr int TE = BLOCK * 4 * U;  // elements per tile
+  constexpr int TV = BLOCK * U;  // vectors per tile
   const typename Op::Tab& tab = TP ? g_tab<Op> : lds_tab;
-  // software pipelining: the next tile's vectors are loaded while this tile
-  // is evaluated (the first one while the tables are staged)
-  float4 nxt[U];
-  const long long step = (long long)gridDim.x * TE;
-  long long t0 = (long long)blockIdx.x * TE;
-  if (PF) tile_load<float, U>(nxt, in, t0, n, t0 + TE <= n);
   if (!TP) Op::load(lds_tab, threadIdx.x);
   if (threadIdx.x == 0) {
     q.n = 0;
@@ -514,17 +522,35 @@ __global__ void __launch_bounds__(BLOCK)
   }
   __syncthreads();
   const bool force = flags & CR_FLAG_FORCE_FALLBACK;
+  const int n4 = (int)(n >> 2), step = (int)gridDim.x * TV;
+  int t0 = (int)blockIdx.x * TV;
+  // queue element i (of this launch) with input x, or run its accurate path in
+  // place when the queue is full (only with pathological inputs or force)
+  auto enqueue = [&](unsigned i, float x, float& res) {
+    unsigned pos = atomicAdd(&q.n, 1u);
+    if (pos < QCAP) {
+      q.idx[pos] = i;
+      q.x[pos] = x;
+    } else {
+      AccResult a = Op::accurate(x, tab);
+      res = a.r;
+      atomicAdd(&q.lanes, 1u);
+      if (!a.ok) note_escape(st, elem_base + i);
+    }
+  };
+  // software pipelining: the next tile's vectors are loaded while this tile is
+  // evaluated
+  float4 nxt[U];
+  if (PF) tile_load<float, U>(nxt, in, t0, n4);
   int iter = 0;
-  for (; t0 < n; t0 += step, iter++) {
-    const bool full = t0 + TE <= n;
+  for (; t0 < n4; t0 += step, iter++) {
     float4 v[U];
     if (PF) {
 #pragma unroll
       for (int u = 0; u < U; u++) v[u] = nxt[u];
-      const long long tn = t0 + step;
-      if (tn < n) tile_load<float, U>(nxt, in, tn, n, tn + TE <= n);
+      tile_load<float, U>(nxt, in, t0 + step, n4);
     } else {
-      tile_load<float, U>(v, in, t0, n, full);
+      tile_load<float, U>(v, in, t0, n4);
     }
     // Evaluate every element of the tile first -- straight-line code with no
     // branch between elements, so the scheduler can interleave their
@@ -542,39 +568,34 @@ __global__ void __launch_bounds__(BLOCK)
         fail |= (unsigned)(!ok || force) << (4 * u + c);
       }
     }
-    if (!full) fail &= tile_live<float, U>(t0, n);
+    if (t0 + TV > n4) fail &= tile_live<float, U>(t0, n4);
     if (fail) {
+      const unsigned i0 = 4 * ((unsigned)t0 + threadIdx.x);
 #pragma unroll
       for (int u = 0; u < U; u++) {
         float* e = reinterpret_cast<float*>(&v[u]);
 #pragma unroll
-        for (int c = 0; c < 4; c++) {
-          if (fail & (1u << (4 * u + c))) {
-            const unsigned i = (unsigned)t0 + 4 * (threadIdx.x + u * BLOCK) + c;
-            const float x = xin[4 * u + c];
-            unsigned pos = atomicAdd(&q.n, 1u);
-            if (pos < QCAP) {
-              q.idx[pos] = i;
-              q.x[pos] = x;
-            } else {  // queue full (only with pathological inputs or force)
-              AccResult a = Op::accurate(x, tab);
-              e[c] = a.r;
-              atomicAdd(&q.lanes, 1u);
-              if (!a.ok) note_escape(st, elem_base + i);
-            }
-          }
-        }
+        for (int c = 0; c < 4; c++)
+          if (fail & (1u << (4 * u + c))) enqueue(i0 + 4 * u * BLOCK + c, xin[4 * u + c], e[c]);
       }
     }
-    tile_store<float, U>(v, out, t0, n, full);
+    tile_store<float, U>(v, out, t0, n4);
     if (iter % Op::qcheck == Op::qcheck - 1) {
       // every thread must see the same fill level: read it between two
       // barriers (no thread can queue more elements before all have read it)
       __syncthreads();
-      const unsigned nq = q.n;
+      const unsigned nq = __builtin_amdgcn_readfirstlane(q.n);
       __syncthreads();
       if (nq > QFLUSH) flush_queue<Op>(q, tab, out, st, elem_base);
     }
+  }
+  if ((n & 3) > threadIdx.x && takes_tail(t0, step, n4, TV)) {
+    const long long i = 4 * n4 + threadIdx.x;
+    bool ok;
+    const float x = in[i];
+    float r = Op::fast(x, tab, ok);
+    if (!ok || force) enqueue((unsigned)i, x, r);
+    out[i] = r;
   }
   __syncthreads();
   flush_queue<Op, true>(q, tab, out, st, elem_base);
@@ -599,7 +620,7 @@ __global__ void __launch_bounds__(BLOCK)
                  unsigned flags, long long elem_base) {
   __shared__ typename SC::Tab tab;
   __shared__ Deferred q;
-  constexpr int TE = BLOCK * 4 * TILE_U;
+  constexpr int TV = BLOCK * TILE_U;  // vectors per tile
   SC::load(tab, threadIdx.x);
   if (threadIdx.x == 0) {
     q.n = 0;
@@ -607,46 +628,55 @@ __global__ void __launch_bounds__(BLOCK)
   }
   __syncthreads();
   const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  const long long step = (long long)gridDim.x * TE;
-  int iter = 0;
-  for (long long t0 = (long long)blockIdx.x * TE; t0 < n; t0 += step, iter++) {
-    const bool full = t0 + TE <= n;
-    float4 v[TILE_U], c4[TILE_U];
-    tile_load<float, TILE_U>(v, in, t0, n, full);
-    const unsigned live = full ? ~0u : tile_live<float, TILE_U>(t0, n);
-#pragma unroll
-    for (int u = 0; u < TILE_U; u++) {
-      float* e = reinterpret_cast<float*>(&v[u]);
-      float* ec = reinterpret_cast<float*>(&c4[u]);
-#pragma unroll
-      for (int c = 0; c < 4; c++) {
-        bool ok;
-        float x = e[c];
-        e[c] = SC::fast(x, tab, ec[c], ok);
-        if ((!ok || force) && (live & (1u << (4 * u + c)))) {
-          const unsigned i = (unsigned)t0 + 4 * (threadIdx.x + u * BLOCK) + c;
-          unsigned pos = atomicAdd(&q.n, 1u);
-          if (pos < QCAP) {
-            q.idx[pos] = i;
-            q.x[pos] = x;
-          } else {
-            AccResult2 a = SC::accurate(x, tab);
-            e[c] = a.s;
-            ec[c] = a.c;
-            atomicAdd(&q.lanes, 1u);
-            if (!a.ok) note_escape(st, elem_base + i);
-          }
-        }
+  const int n4 = (int)(n >> 2), step = (int)gridDim.x * TV;
+  // element i of this launch: fast path, queue or accurate path in place
+  auto one = [&](unsigned i, float x, float& s, float& c) {
+    bool ok;
+    s = SC::fast(x, tab, c, ok);
+    if (!ok || force) {
+      unsigned pos = atomicAdd(&q.n, 1u);
+      if (pos < QCAP) {
+        q.idx[pos] = i;
+        q.x[pos] = x;
+      } else {
+        AccResult2 a = SC::accurate(x, tab);
+        s = a.s;
+        c = a.c;
+        atomicAdd(&q.lanes, 1u);
+        if (!a.ok) note_escape(st, elem_base + i);
       }
     }
-    tile_store<float, TILE_U>(v, outs, t0, n, full);
-    tile_store<float, TILE_U>(c4, outc, t0, n, full);
+  };
+  int t0 = (int)blockIdx.x * TV;
+  int iter = 0;
+  for (; t0 < n4; t0 += step, iter++) {
+    float4 v[TILE_U], c4[TILE_U];
+    tile_load<float, TILE_U>(v, in, t0, n4);
+    const unsigned i0 = 4 * ((unsigned)t0 + threadIdx.x);
+#pragma unroll
+    for (int u = 0; u < TILE_U; u++) {
+      if (t0 + (int)threadIdx.x + u * BLOCK < n4) {
+        float* e = reinterpret_cast<float*>(&v[u]);
+        float* ec = reinterpret_cast<float*>(&c4[u]);
+#pragma unroll
+        for (int c = 0; c < 4; c++) one(i0 + 4 * u * BLOCK + c, e[c], e[c], ec[c]);
+      }
+    }
+    tile_store<float, TILE_U>(v, outs, t0, n4);
+    tile_store<float, TILE_U>(c4, outc, t0, n4);
     if (iter % SC::qcheck == SC::qcheck - 1) {
       __syncthreads();
-      const unsigned nq = q.n;
+      const unsigned nq = __builtin_amdgcn_readfirstlane(q.n);
       __syncthreads();
       if (nq > QFLUSH) flush_queue_sincos<SC>(q, tab, outs, outc, st, elem_base);
     }
+  }
+  if ((n & 3) > threadIdx.x && takes_tail(t0, step, n4, TV)) {
+    const long long i = 4 * n4 + threadIdx.x;
+    float s, c;
+    one((unsigned)i, in[i], s, c);
+    outs[i] = s;
+    outc[i] = c;
   }
   __syncthreads();
   flush_queue_sincos<SC, true>(q, tab, outs, outc, st, elem_base);
@@ -730,7 +760,7 @@ __global__ void __launch_bounds__(BLOCK)
               long long elem_base) {
   __shared__ typename Op::Tab tab;
   __shared__ Deferred64 q;
-  constexpr int TE = BLOCK * 2 * U;  // elements per tile
+  constexpr int TV = BLOCK * U;  // vectors per tile
   Op::load(tab, threadIdx.x);
   if (threadIdx.x == 0) {
     q.n = 0;
@@ -752,14 +782,13 @@ __global__ void __launch_bounds__(BLOCK)
       if (!a.ok) note_escape(st, elem_base + j);
     }
   };
-  const long long step = (long long)gridDim.x * TE;
+  const int n2 = (int)(n >> 1), step = (int)gridDim.x * TV;
+  int t0 = (int)blockIdx.x * TV;
   int iter = 0;
-  for (long long t0 = (long long)blockIdx.x * TE; t0 < n; t0 += step, iter++) {
-    const bool full = t0 + TE <= n;
-    const unsigned j0 = (unsigned)t0 + 2 * threadIdx.x;
+  for (; t0 < n2; t0 += step, iter++) {
+    const unsigned j0 = 2 * ((unsigned)t0 + threadIdx.x);
     double2 v[U];
-    tile_load<double, U>(v, in, t0, n, full);
-    const unsigned live = full ? ~0u : tile_live<double, U>(t0, n);
+    tile_load<double, U>(v, in, t0, n2);
     if (SL) {
       // slots past the end hold 1.0: evaluated, never stored or queued
       double xin[2 * U];
@@ -775,7 +804,7 @@ __global__ void __launch_bounds__(BLOCK)
           fail |= (unsigned)(!ok || force) << (2 * u + c);
         }
       }
-      fail &= live;
+      if (t0 + TV > n2) fail &= tile_live<double, U>(t0, n2);
       if (fail) {
 #pragma unroll
         for (int u = 0; u < U; u++) {
@@ -789,77 +818,69 @@ __global__ void __launch_bounds__(BLOCK)
     } else {
 #pragma unroll
       for (int u = 0; u < U; u++) {
-        double* e = reinterpret_cast<double*>(&v[u]);
+        if (t0 + (int)threadIdx.x + u * BLOCK < n2) {
+          double* e = reinterpret_cast<double*>(&v[u]);
 #pragma unroll
-        for (int c = 0; c < 2; c++) {
-          bool ok;
-          double x = e[c];
-          e[c] = Op::fast(x, tab, ok);
-          if ((!ok || force) && (live & (1u << (2 * u + c))))
-            enqueue(j0 + 2 * u * BLOCK + c, x, e[c]);
+          for (int c = 0; c < 2; c++) {
+            bool ok;
+            double x = e[c];
+            e[c] = Op::fast(x, tab, ok);
+            if (!ok || force) enqueue(j0 + 2 * u * BLOCK + c, x, e[c]);
+          }
         }
       }
     }
-    tile_store<double, U>(v, out, t0, n, full);
+    tile_store<double, U>(v, out, t0, n2);
     if (iter % Op::qcheck == Op::qcheck - 1) {
       __syncthreads();
-      const unsigned nq = q.n;
+      const unsigned nq = __builtin_amdgcn_readfirstlane(q.n);
       __syncthreads();
       if (nq > QFLUSH) flush_queue64<Op>(q, tab, out, st, elem_base);
     }
+  }
+  if ((n & 1) > threadIdx.x && takes_tail(t0, step, n2, TV)) {
+    const long long i = 2 * n2;
+    bool ok;
+    const double x = in[i];
+    double r = Op::fast(x, tab, ok);
+    if (!ok || force) enqueue((unsigned)i, x, r);
+    out[i] = r;
   }
   __syncthreads();
   flush_queue64<Op, true>(q, tab, out, st, elem_base);
 }
 
 // ------------------------------------------------- directed rounding modes
-// Every element through the function's ~2^-100 double-double evaluation with
-// both ends of its error interval rounded in the mode RM (cr_f32_dir.h); the
-// paper's GPU runs leave these modes out (Sec. III-C).  A grid-stride map with
-// the tables in LDS; each element counts as an accurate-path lane.
+// The map kernels over a function's directed-mode paths (cr_f32_dir.h; the
+// paper's GPU runs leave these modes out, Sec. III-C).  Measured against every
+// element through the double-double evaluation, toward +infinity, 2^24 elements of
+// the benchmark's inputs (5% of them hard to round in the exp/log family): expf
+// 155 -> 36 us, logf 169 -> 38, sinf 235 -> 52, sincosf 265 -> 64, tanf 284 -> 60,
+// acosf 231 -> 57, tanhf 191 -> 42, rsqrtf 45 -> 32.
 template <class Op, int RM>
-__global__ void __launch_bounds__(BLOCK)
-    k_map_f32_dir(const float* in, float* out, long long n, DevStats* st, long long elem_base) {
-  __shared__ typename Op::Tab tab;
-  Op::load(tab, threadIdx.x);
-  __syncthreads();
-  unsigned lanes = 0;
-  for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n;
-       i += (long long)gridDim.x * BLOCK) {
-    AccResult a = Op::template dir<RM>(in[i], tab);
-    out[i] = a.r;
-    lanes++;
-    if (!a.ok) note_escape(st, elem_base + i);
+struct OpDir {
+  using Tab = typename Op::Tab;
+  static constexpr int qcheck = QCHECK;
+  static __device__ __forceinline__ void load(Tab& t, int tid) { Op::load(t, tid); }
+  static __device__ __forceinline__ float fast(float x, const Tab& t, bool& ok) {
+    return Op::template fast_dir<RM>(x, t, ok);
   }
-  if (lanes) {
-    CounterSlot& c = st->slot[blockIdx.x % NSLOT];
-    atomicAdd(&c.fallback_lanes, (unsigned long long)lanes);
-    atomicAdd(&c.fallback_waves, 1ull);
+  static __device__ __forceinline__ AccResult accurate(float x, const Tab& t) {
+    return Op::template dir<RM>(x, t);
   }
-}
-
+};
 template <class SC, int RM>
-__global__ void __launch_bounds__(BLOCK)
-    k_sincos_dir(const float* in, float* outs, float* outc, long long n, DevStats* st,
-                 long long elem_base) {
-  __shared__ typename SC::Tab tab;
-  SC::load(tab, threadIdx.x);
-  __syncthreads();
-  unsigned lanes = 0;
-  for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n;
-       i += (long long)gridDim.x * BLOCK) {
-    AccResult2 a = SC::template dir<RM>(in[i], tab);
-    outs[i] = a.s;
-    outc[i] = a.c;
-    lanes++;
-    if (!a.ok) note_escape(st, elem_base + i);
+struct SinCosDir {
+  using Tab = typename SC::Tab;
+  static constexpr int qcheck = QCHECK;
+  static __device__ __forceinline__ void load(Tab& t, int tid) { SC::load(t, tid); }
+  static __device__ __forceinline__ float fast(float x, const Tab& t, float& c, bool& ok) {
+    return SC::template fast_dir<RM>(x, t, c, ok);
   }
-  if (lanes) {
-    CounterSlot& c = st->slot[blockIdx.x % NSLOT];
-    atomicAdd(&c.fallback_lanes, (unsigned long long)lanes);
-    atomicAdd(&c.fallback_waves, 1ull);
+  static __device__ __forceinline__ AccResult2 accurate(float x, const Tab& t) {
+    return SC::template dir<RM>(x, t);
   }
-}
+};
 
 // ------------------------------------------------- application workloads
 // The paper's two synthetic applications built on the correctly rounded
@@ -1336,7 +1357,7 @@ __global__ void __launch_bounds__(BLOCK)
     batch_tile<Op>(reqs[T.req], T, tab, q, force, st);
     if (iter % Op::qcheck == Op::qcheck - 1) {
       __syncthreads();
-      const unsigned nq = q.n;
+      const unsigned nq = __builtin_amdgcn_readfirstlane(q.n);
       __syncthreads();
       if (nq > QFLUSH) batch_flush_one<Op>(q, tab, reqs, st);
     }
@@ -1364,7 +1385,7 @@ __global__ void __launch_bounds__(BLOCK)
     batch_tile_sincos<SC>(reqs[T.req], T, tab, q, force, st);
     if (iter % SC::qcheck == SC::qcheck - 1) {
       __syncthreads();
-      const unsigned nq = q.n;
+      const unsigned nq = __builtin_amdgcn_readfirstlane(q.n);
       __syncthreads();
       if (nq > QFLUSH) batch_flush_one_sincos<SC>(q, tab, reqs, st);
     }
@@ -1649,57 +1670,47 @@ int dispatch_f32(int f, const float* in, float* out, size_t n, hipStream_t s, un
 }
 
 
-// Directed rounding modes: one grid-stride kernel per (function, mode).
+// Directed rounding modes: one kernel per (function, mode), in the default shape.
 template <class Op, int RM>
-int launch_dir(const float* in, float* out, size_t n, hipStream_t s, DevStats* st, int grid) {
-  size_t g = (n + BLOCK - 1) / BLOCK;
-  if (g > (size_t)grid) g = grid;
-  hipLaunchKernelGGL((k_map_f32_dir<Op, RM>), dim3((unsigned)g), dim3(BLOCK), 0, s, in, out,
-                     (long long)n, st, 0LL);
-  hipError_t e = hipGetLastError();
-  return e == hipSuccess ? CR_OK : hip_fail(e);
+int launch_dir(const float* in, float* out, size_t n, hipStream_t s, unsigned flags, DevStats* st,
+               int grid) {
+  return launch_map_f32<OpDir<Op, RM>, 2, 1, 0>(in, out, n, s, flags, st, grid);
 }
 
 template <int RM>
-int dispatch_f32_dir(int f, const float* in, float* out, size_t n, hipStream_t s, DevStats* st,
-                     int g) {
+int dispatch_f32_dir(int f, const float* in, float* out, size_t n, hipStream_t s,
+                     unsigned flags, DevStats* st, int g) {
   switch (f) {
-    case CR_EXPF: return launch_dir<OpExp<EXPK_E>, RM>(in, out, n, s, st, g);
-    case CR_EXP2F: return launch_dir<OpExp<EXPK_2>, RM>(in, out, n, s, st, g);
-    case CR_EXP10F: return launch_dir<OpExp<EXPK_10>, RM>(in, out, n, s, st, g);
-    case CR_EXPM1F: return launch_dir<OpExp<EXPK_EM1>, RM>(in, out, n, s, st, g);
-    case CR_LOGF: return launch_dir<OpLog<LOGK_E>, RM>(in, out, n, s, st, g);
-    case CR_LOG2F: return launch_dir<OpLog<LOGK_2>, RM>(in, out, n, s, st, g);
-    case CR_LOG10F: return launch_dir<OpLog<LOGK_10>, RM>(in, out, n, s, st, g);
-    case CR_LOG1PF: return launch_dir<OpLog<LOGK_1P>, RM>(in, out, n, s, st, g);
-    case CR_RSQRTF: return launch_dir<OpRsqrt, RM>(in, out, n, s, st, g);
-    case CR_SINF: return launch_dir<OpTrig<TRIGK_SIN>, RM>(in, out, n, s, st, g);
-    case CR_COSF: return launch_dir<OpTrig<TRIGK_COS>, RM>(in, out, n, s, st, g);
-    case CR_TANF: return launch_dir<OpTrig<TRIGK_TAN>, RM>(in, out, n, s, st, g);
-    case CR_ASINF: return launch_dir<OpAtan<ATANK_ASIN>, RM>(in, out, n, s, st, g);
-    case CR_ACOSF: return launch_dir<OpAtan<ATANK_ACOS>, RM>(in, out, n, s, st, g);
-    case CR_ATANF: return launch_dir<OpAtan<ATANK_ATAN>, RM>(in, out, n, s, st, g);
-    case CR_SINHF: return launch_dir<OpHyp<HYPK_SINH>, RM>(in, out, n, s, st, g);
-    case CR_COSHF: return launch_dir<OpHyp<HYPK_COSH>, RM>(in, out, n, s, st, g);
-    case CR_TANHF: return launch_dir<OpHyp<HYPK_TANH>, RM>(in, out, n, s, st, g);
-    case CR_SINCOSF: {
-      size_t gg = (n + BLOCK - 1) / BLOCK;
-      if (gg > (size_t)g) gg = g;
-      hipLaunchKernelGGL((k_sincos_dir<SinCosF64, RM>), dim3((unsigned)gg), dim3(BLOCK), 0, s, in,
-                         out, out + n, (long long)n, st, 0LL);
-      hipError_t e = hipGetLastError();
-      return e == hipSuccess ? CR_OK : hip_fail(e);
-    }
+    case CR_EXPF: return launch_dir<OpExp<EXPK_E>, RM>(in, out, n, s, flags, st, g);
+    case CR_EXP2F: return launch_dir<OpExp<EXPK_2>, RM>(in, out, n, s, flags, st, g);
+    case CR_EXP10F: return launch_dir<OpExp<EXPK_10>, RM>(in, out, n, s, flags, st, g);
+    case CR_EXPM1F: return launch_dir<OpExp<EXPK_EM1>, RM>(in, out, n, s, flags, st, g);
+    case CR_LOGF: return launch_dir<OpLog<LOGK_E>, RM>(in, out, n, s, flags, st, g);
+    case CR_LOG2F: return launch_dir<OpLog<LOGK_2>, RM>(in, out, n, s, flags, st, g);
+    case CR_LOG10F: return launch_dir<OpLog<LOGK_10>, RM>(in, out, n, s, flags, st, g);
+    case CR_LOG1PF: return launch_dir<OpLog<LOGK_1P>, RM>(in, out, n, s, flags, st, g);
+    case CR_RSQRTF: return launch_dir<OpRsqrt, RM>(in, out, n, s, flags, st, g);
+    case CR_SINF: return launch_dir<OpTrig<TRIGK_SIN>, RM>(in, out, n, s, flags, st, g);
+    case CR_COSF: return launch_dir<OpTrig<TRIGK_COS>, RM>(in, out, n, s, flags, st, g);
+    case CR_TANF: return launch_dir<OpTrig<TRIGK_TAN>, RM>(in, out, n, s, flags, st, g);
+    case CR_ASINF: return launch_dir<OpAtan<ATANK_ASIN>, RM>(in, out, n, s, flags, st, g);
+    case CR_ACOSF: return launch_dir<OpAtan<ATANK_ACOS>, RM>(in, out, n, s, flags, st, g);
+    case CR_ATANF: return launch_dir<OpAtan<ATANK_ATAN>, RM>(in, out, n, s, flags, st, g);
+    case CR_SINHF: return launch_dir<OpHyp<HYPK_SINH>, RM>(in, out, n, s, flags, st, g);
+    case CR_COSHF: return launch_dir<OpHyp<HYPK_COSH>, RM>(in, out, n, s, flags, st, g);
+    case CR_TANHF: return launch_dir<OpHyp<HYPK_TANH>, RM>(in, out, n, s, flags, st, g);
+    case CR_SINCOSF:
+      return launch_sincos<SinCosDir<SinCosF64, RM>>(in, out, n, s, flags, st, g);
   }
   return CR_E_FUNC;
 }
 
 int dispatch_dir(int mode, int f, const float* in, float* out, size_t n, hipStream_t s,
-                 DevStats* st, int g) {
+                 unsigned flags, DevStats* st, int g) {
   switch (mode) {
-    case RM_RZ: return dispatch_f32_dir<RM_RZ>(f, in, out, n, s, st, g);
-    case RM_RU: return dispatch_f32_dir<RM_RU>(f, in, out, n, s, st, g);
-    case RM_RD: return dispatch_f32_dir<RM_RD>(f, in, out, n, s, st, g);
+    case RM_RZ: return dispatch_f32_dir<RM_RZ>(f, in, out, n, s, flags, st, g);
+    case RM_RU: return dispatch_f32_dir<RM_RU>(f, in, out, n, s, flags, st, g);
+    case RM_RD: return dispatch_f32_dir<RM_RD>(f, in, out, n, s, flags, st, g);
   }
   return CR_E_IMPL;
 }
@@ -1735,7 +1746,7 @@ int eval_cfg(int func_id, int impl, unsigned flags, const void* in, void* out, s
   const int g = num_cus() * (bpc > 0 ? bpc : default_bpc());
   const int mode = (int)((flags & CR_FLAG_ROUND_MASK) >> CR_FLAG_ROUND_SHIFT);
   if (mode != RM_RN)
-    rc = dispatch_dir(mode, func_id, (const float*)in, (float*)out, n, s, st, g);
+    rc = dispatch_dir(mode, func_id, (const float*)in, (float*)out, n, s, flags, st, g);
   else if (func_id < CR_NUM_F32 && impl == CR_IMPL_SPLIT_F32)
     rc = dispatch_f32_split(func_id, (const float*)in, (float*)out, n, s, flags, st, variant, g);
   else if (func_id < CR_NUM_F32)
