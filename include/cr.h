@@ -164,9 +164,8 @@ int cr_dft(const float *x, int64_t n, const float *w, int64_t m, double *X, unsi
            void *stream);
 
 /* ------------------------------------------------------------------ batches
- * Many requests of mixed function and uneven length evaluated by ONE graph
- * launch (captured once, replayed on every launch; the batched form of
- * the elementwise map; the paper's SIMD functions are called on vectors of
+ * Many requests of mixed function and uneven length evaluated by ONE launch (the
+ * batched form of the elementwise map; the paper's SIMD functions are called on vectors of
  * arbitrary length, Sec. III-A).  Requests follow the conventions above
  * (device pointers, element alignment, sincosf planar within its own output,
  * in place allowed except for sincosf); binary32 functions only (ids 0..18);
@@ -183,8 +182,8 @@ typedef struct {
 
 typedef struct cr_batch_plan cr_batch_plan; /* opaque, owned by the library */
 
-/* Validate the requests, upload the tile table and capture the launch in a
- * HIP graph.  The plan keeps the request pointers: the buffers must stay
+/* Validate the requests and upload the request and tile tables (for a plan of
+ * more than 2^26 elements, also capture its launches in a HIP graph).  The plan keeps the request pointers: the buffers must stay
  * valid while the plan is launched.  flags: enum cr_flag (applied to every
  * request).  On success *plan receives a new plan (free it with
  * cr_batch_plan_destroy); on error *plan is NULL and nothing is allocated.
@@ -194,35 +193,37 @@ typedef struct cr_batch_plan cr_batch_plan; /* opaque, owned by the library */
  * CR_E_HIP. */
 int cr_batch_plan_create(const cr_request *reqs, int32_t num, unsigned flags,
                          cr_batch_plan **plan);
-/* Launch the plan's graph on the stream (asynchronous, stream-ordered).  The
- * graph holds one persistent kernel per (implementation, function) present,
- * each over its own contiguous range of 4096-element tiles (requests are
- * sorted by implementation and function when the plan is made), spread over
- * four parallel branches that join before the launch completes. */
+/* Launch the plan on the stream (asynchronous, stream-ordered): one kernel per
+ * implementation present, over all its requests (sorted by function when the
+ * plan is made); for a plan of more than 2^26 elements a graph of one
+ * persistent kernel per (implementation, function), spread over four parallel
+ * branches that join before the launch completes. */
 int cr_batch_plan_launch(cr_batch_plan *plan, void *stream);
 /* Release the plan (synchronises with its last launch first). */
 int cr_batch_plan_destroy(cr_batch_plan *plan);
-/* Evaluate the requests with one launch on the stream, without a graph.  The
- * request and tile tables are allocated and freed stream-ordered; the call
- * synchronises the stream once, after copying the tables from host memory
- * and before the launch. */
+/* Evaluate the requests without a plan.  Batches of up to a few hundred requests
+ * go to the kernel as its arguments (up to four launches): nothing is allocated
+ * or copied and the call does not wait.  For larger ones, and on a stream that is
+ * being captured, the request and tile tables are allocated and freed
+ * stream-ordered, and the call synchronises the stream once, after copying the
+ * tables from host memory and before the launch. */
 int cr_eval_batch(const cr_request *reqs, int32_t num, void *stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * evaluation as cr_eval_batch, with the same request conventions, results
- * and errors, but the request and tile tables go into a fixed scratch array
- * in the library's static device memory instead of stream-ordered
- * allocations.  The call makes no hipMalloc/hipFree or other allocating
+ * and errors, but the tables of a batch too large to go as kernel arguments
+ * are put into a fixed scratch array in the library's static device memory
+ * instead of stream-ordered allocations.  The call makes no hipMalloc/hipFree or other allocating
  * device call.  The scratch holds at most CR_NOALLOC_MAX_REQUESTS requests and
  * CR_NOALLOC_MAX_TILES tiles, where a request of n elements takes
  * ceil(n / 4096) tiles (about 2 10^9 elements in all); larger batches return
  * CR_E_SCRATCH before anything is copied or launched.  Each device holds one
- * scratch (about 8.4 MiB, kept until the process ends) shared by every call
+ * scratch (about 2.3 MiB, kept until the process ends) shared by every call
  * on that device: calls on one stream are ordered, but calls that overlap in
  * time on different streams of one device race on the tables and must not
- * be made.  Copies the tables from host memory and synchronises the stream
- * once before launching, as cr_eval_batch does. */
+ * be made.  Where cr_eval_batch copies its tables, this call copies them from
+ * host memory and synchronises the stream once before launching. */
 #define CR_NOALLOC_MAX_REQUESTS 8192
 #define CR_NOALLOC_MAX_TILES (1 << 19)
 int cr_eval_batch_noalloc(const cr_request *reqs, int32_t num, void *stream);
@@ -287,7 +288,8 @@ int cr_tune_set(int func_id, int impl, const cr_tune_cfg *cfg);
 int cr_tune_reset(void);
 /* Grid of the batch kernels (cr_batch_plan_create, cr_eval_batch,
  * cr_eval_batch_noalloc): workgroups per compute unit of each per-function
- * kernel of a batch, one setting per implementation (CR_IMPL_AUTO means
+ * kernel of a large plan's graph, and an eighth of those of the one kernel that
+ * evaluates other batches, one setting per implementation (CR_IMPL_AUTO means
  * F64_INTERNAL), 1..64, default 4.  A plan keeps the value in force when it is
  * created.  Results never depend on it.  CR_E_IMPL / CR_E_NULL / CR_E_TUNE on
  * bad input. */

@@ -188,7 +188,7 @@ def _requests(reqs):
 
 
 class BatchPlan:
-    """A cr_batch_plan: requests captured into one graph launch."""
+    """A cr_batch_plan: requests evaluated by one launch."""
 
     def __init__(self, reqs, flags=0):
         self._arr = _requests(reqs)

@@ -16,6 +16,7 @@
 #include <atomic>
 #include <vector>
 #include <mutex>
+#include <new>
 
 #include "../../include/cr.h"
 #include "cr_f32_exp.h"
@@ -64,16 +65,7 @@ struct DevStats {
 #endif
 constexpr int BLOCK = 256;
 constexpr int TILE_U = CR_TILE_U;           // float4 vectors per thread per tile (sincosf)
-// Batch tiles: BATCH_U float4 vectors per thread, TILE elements per tile.
-// Measured on the 4096-request batch (three alternating runs per build),
-// 4096-element tiles against 2048: +0.9% binary64-internal, +1.6%
-// binary32-only, within the run-to-run spread (larger tiles mean fewer
-// tile-table reads and queue checks per element, smaller ones a shorter tail).
-#ifndef CR_BATCH_U
-#define CR_BATCH_U 4
-#endif
-constexpr int BATCH_U = CR_BATCH_U;
-constexpr int TILE = BLOCK * 4 * BATCH_U;   // 4096 elements per tile
+constexpr int TILE = 4096;                  // elements of a batch tile, at most
 constexpr int QCAP = 512;                   // deferred elements held in LDS
 constexpr int QCHECK = 8;                   // tiles between two looks at the queue
 constexpr int QFLUSH = QCAP / 2;            // flush when the queue is fuller than this
@@ -1142,26 +1134,38 @@ __global__ void __launch_bounds__(BLOCK)
 }
 
 // ------------------------------------------------------------ ragged batch
-// One persistent kernel evaluates a whole plan: a request table (function,
-// pointers, length) and a tile table (request, start, count; tiles of TILE
-// elements).  Each workgroup walks a contiguous range of tiles; requests are
-// ordered by function when the plan is built, so consecutive tiles mostly
-// share a function and its LDS table, which is reloaded only when the
-// function changes.  The function switch is per tile, hence wave-uniform.
+// One persistent kernel evaluates a whole batch: the requests sorted by
+// (implementation, function) and cut into tiles of 1024, 2048 or 4096 elements,
+// tile t of the batch being tile t - tile0 of its request.  Workgroup b takes the
+// tiles [b per, (b + 1) per): the function changes rarely along them, and where it
+// does the workgroup runs the accurate path on its queue and stages the next tables.
+// Bound by the latency of a workgroup's look-ups and first loads (small batches) and
+// by VALU issue (large ones).  Before, every batch ran one kernel per function
+// present, 19 of them for most, from a graph (125-140 us a launch whatever the work)
+// or one after the other (cr_eval_batch, 100 us and more).  Measured: a plan of 48
+// requests (40259 elements) 131 -> 7.9 us, of 512 requests (12.4e6) 125 -> 38 us,
+// cr_eval_batch of 48 requests 115 -> 6.4 us, of 512 requests 184 -> 59 us.
 struct BReq {
-  const void* in;
-  void* out;
-  long long n;
-  int func;
-  int aligned;  // in and out (and the cos block for sincosf) are 16-byte aligned
-  int key;      // func + BSPLIT for the binary32-only implementation
-  int orig;     // index of the request in the caller's array
+  const float* in;
+  float* out;
+  unsigned n;
+  unsigned tile0;  // the request's first tile
+  int key;         // func, + BSPLIT for the binary32-only implementation
+  int orig;        // index of the request in the caller's array
 };
 constexpr int BSPLIT = 32;
-struct BTile {
-  int req;
-  int count;
-  long long start;
+
+// Up to BARG requests go to the kernel as its arguments, with nothing to allocate
+// or copy (first tiles apart, for the search); larger batches and plans keep a
+// request table and the request of every tile in device memory.
+constexpr int BARG = 96;
+// The tables do not change while a kernel reads them: the constant address space
+// makes the accesses that are the same in every lane scalar loads.
+typedef const __attribute__((address_space(4))) BReq* BReqTab;
+typedef const __attribute__((address_space(4))) unsigned* BTileTab;
+struct BArgs {
+  unsigned tile0[128];  // 0xffffffff beyond the last request
+  BReq req[BARG];
 };
 
 // Static device memory of the library.  Each device the library runs on holds
@@ -1171,11 +1175,13 @@ struct BTile {
 // per-device addresses with hipGetSymbolAddress.
 //   g_dev_stats  the statistics counters and escape list of every entry point
 //   scratch      the request and tile tables of cr_eval_batch_noalloc:
-//                CR_NOALLOC_MAX_REQUESTS BReq, then CR_NOALLOC_MAX_TILES BTile
+//                CR_NOALLOC_MAX_REQUESTS BReq, then the request of each of up to
+//                CR_NOALLOC_MAX_TILES tiles
 __device__ __align__(256) DevStats g_dev_stats;
 constexpr size_t NOALLOC_REQ_BYTES =
     ((size_t)CR_NOALLOC_MAX_REQUESTS * sizeof(BReq) + 255) / 256 * 256;
-constexpr size_t SCRATCH_BYTES = NOALLOC_REQ_BYTES + (size_t)CR_NOALLOC_MAX_TILES * sizeof(BTile);
+constexpr size_t SCRATCH_BYTES =
+    NOALLOC_REQ_BYTES + (size_t)CR_NOALLOC_MAX_TILES * sizeof(unsigned);
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
 struct BDeferred {
@@ -1191,207 +1197,287 @@ __device__ __forceinline__ long long batch_escape_id(unsigned req, unsigned idx)
   return (long long)(((unsigned long long)req << 32) | idx);
 }
 
+// A function's evaluator for the batch: one output (Op) or two (SC, sincosf).
 template <class Op>
-__device__ __forceinline__ void batch_enqueue(BDeferred& q, const typename Op::Tab& tab,
-                                              unsigned req, unsigned orig, unsigned idx, float x,
-                                              float& res, DevStats* st) {
+struct BOne {
+  using Tab = typename Op::Tab;
+  static constexpr bool TWO = false;
+  static constexpr int qcheck = Op::qcheck;
+  static __device__ __forceinline__ void load(Tab& t, int tid) { Op::load(t, tid); }
+  static __device__ __forceinline__ float fast(float x, const Tab& t, float&, bool& ok) {
+    return Op::fast(x, t, ok);
+  }
+  static __device__ __forceinline__ AccResult2 accurate(float x, const Tab& t) {
+    const AccResult a = Op::accurate(x, t);
+    return {a.r, 0.0f, a.ok};
+  }
+};
+template <class SC>
+struct BTwo : SC {
+  static constexpr bool TWO = true;
+};
+
+constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
+struct BShared {
+  BDeferred q;
+  __align__(16) unsigned char tab[cmax(
+      cmax(cmax(sizeof(ExpTab), sizeof(LogTab)), cmax(sizeof(TrigTab), sizeof(AtanTab))),
+      cmax(cmax(cmax(sizeof(SExpTab), sizeof(SLogTab)), cmax(sizeof(STrigTab), sizeof(SAtanTab))),
+           sizeof(SHypTab)))];
+};
+
+// Element idx of request R failed its test: queued, or its accurate path in place
+// when the queue is full (pathological inputs, or force).
+template <class E>
+__device__ __forceinline__ void batch_enqueue(BDeferred& q, const typename E::Tab& tab, int ri,
+                                              int orig, unsigned idx, float x, float& s, float& c,
+                                              DevStats* st) {
   unsigned pos = atomicAdd(&q.n, 1u);
   if (pos < QCAP) {
-    q.req[pos] = req;
+    q.req[pos] = ri;
     q.idx[pos] = idx;
     q.x[pos] = x;
   } else {
-    AccResult a = Op::accurate(x, tab);
-    res = a.r;
+    const AccResult2 a = E::accurate(x, tab);
+    s = a.s;
+    c = a.c;
     atomicAdd(&q.lanes, 1u);
     if (!a.ok) note_escape(st, batch_escape_id(orig, idx));
   }
 }
 
-template <class Op>
-__device__ __forceinline__ void batch_tile(BReq R, BTile T, const typename Op::Tab& tab,
-                                        BDeferred& q, bool force, DevStats* st) {
-  const float* in = reinterpret_cast<const float*>(R.in) + T.start;
-  float* out = reinterpret_cast<float*>(R.out) + T.start;
-  const int cnt = T.count;
-  const unsigned base = (unsigned)T.start;
-  if (R.aligned) {
-    const int n4 = cnt >> 2;
+// cnt elements from element `start` of request ri, 1024 at a time: four a thread
+// in straight-line code, the next four loaded meanwhile.  The cnt % 4 elements
+// after the last whole vector are the lane's that would take the next vector.
+template <class E>
+__device__ __forceinline__ void batch_tile(BReq R, int ri, unsigned start, unsigned cnt,
+                                           const typename E::Tab& tab, BDeferred& q, bool force,
+                                           DevStats* st) {
+  const float* in = R.in + start;
+  float* out = R.out + start;
+  float* outc = E::TWO ? out + R.n : out;
+  const int n4 = (int)(cnt >> 2), rem = (int)(cnt & 3u), orig = R.orig;
+  const int steps = (int)((cnt + 4 * BLOCK - 1) / (4 * BLOCK));
+  float4 nxt[1];
+  tile_load<float, 1>(nxt, in, 0, n4);
+#pragma unroll 1
+  for (int k = 0; k < steps; k++) {
+    const int t0 = k * BLOCK, i = t0 + (int)threadIdx.x;
+    float4 v[1] = {nxt[0]}, vc[1];
+    tile_load<float, 1>(nxt, in, t0 + BLOCK, n4);
+    float* e = reinterpret_cast<float*>(&v[0]);
+    float* ec = reinterpret_cast<float*>(&vc[0]);
+    unsigned live = 0xfu;
+    if (t0 + BLOCK > n4) {  // the tile's last step
+      live = i < n4 ? 0xfu : i == n4 ? (1u << rem) - 1u : 0u;
+      if (i == n4) {
 #pragma unroll
-    for (int u = 0; u < BATCH_U; u++) {
-      int i = threadIdx.x + u * BLOCK;
-      if (i < n4) {
-        float4 v = ld_stream4(in + 4 * i);
-        float* e = reinterpret_cast<float*>(&v);
-#pragma unroll
-        for (int c = 0; c < 4; c++) {
-          bool ok;
-          float x = e[c];
-          e[c] = Op::fast(x, tab, ok);
-          if (!ok || force)
-            batch_enqueue<Op>(q, tab, T.req, R.orig, base + 4 * i + c, x, e[c], st);
-        }
-        st_stream4(out + 4 * i, v);
+        for (int c = 0; c < 3; c++)
+          if (c < rem) e[c] = in[4 * i + c];
       }
     }
-    int i = 4 * n4 + threadIdx.x;
-    if (i < cnt) {
+    float x[4];
+    unsigned fail = 0;
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
       bool ok;
-      float x = in[i];
-      float r = Op::fast(x, tab, ok);
-      if (!ok || force) batch_enqueue<Op>(q, tab, T.req, R.orig, base + i, x, r, st);
-      out[i] = r;
+      x[c] = e[c];
+      e[c] = E::fast(x[c], tab, ec[c], ok);
+      fail |= (unsigned)(!ok || force) << c;
     }
-  } else {
-    for (int i = threadIdx.x; i < cnt; i += BLOCK) {
-      bool ok;
-      float x = in[i];
-      float r = Op::fast(x, tab, ok);
-      if (!ok || force) batch_enqueue<Op>(q, tab, T.req, R.orig, base + i, x, r, st);
-      out[i] = r;
+    fail &= live;
+    if (fail) {
+#pragma unroll
+      for (int c = 0; c < 4; c++)
+        if (fail & (1u << c))
+          batch_enqueue<E>(q, tab, ri, orig, start + 4 * i + c, x[c], e[c], ec[c], st);
     }
-  }
-}
-
-template <class SC>
-__device__ __forceinline__ void batch_tile_sincos(BReq R, BTile T, const typename SC::Tab& tab,
-                                               BDeferred& q, bool force, DevStats* st) {
-  const float* in = reinterpret_cast<const float*>(R.in) + T.start;
-  float* os = reinterpret_cast<float*>(R.out) + T.start;
-  float* oc = reinterpret_cast<float*>(R.out) + R.n + T.start;
-  const int cnt = T.count;
-  const unsigned base = (unsigned)T.start;
-  // one element: fast path, queue or accurate path in place
-  auto one = [&](int i, float x, float& sv, float& c) {
-    bool ok;
-    sv = SC::fast(x, tab, c, ok);
-    if (!ok || force) {
-      unsigned pos = atomicAdd(&q.n, 1u);
-      if (pos < QCAP) {
-        q.req[pos] = T.req;
-        q.idx[pos] = base + i;
-        q.x[pos] = x;
-      } else {
-        AccResult2 a = SC::accurate(x, tab);
-        sv = a.s;
-        c = a.c;
-        atomicAdd(&q.lanes, 1u);
-        if (!a.ok) note_escape(st, batch_escape_id(R.orig, base + i));
+    tile_store<float, 1>(v, out, t0, n4);
+    if (E::TWO) tile_store<float, 1>(vc, outc, t0, n4);
+    if (i == n4) {
+#pragma unroll
+      for (int c = 0; c < 3; c++) {
+        if (c < rem) out[4 * i + c] = e[c];
+        if (E::TWO && c < rem) outc[4 * i + c] = ec[c];
       }
     }
-  };
-  int i0 = 0;
-  if (R.aligned) {  // input, sine block and cosine block 16-byte aligned
-    const int n4 = cnt >> 2;
-#pragma unroll
-    for (int u = 0; u < BATCH_U; u++) {
-      int i = threadIdx.x + u * BLOCK;
-      if (i < n4) {
-        float4 v = ld_stream4(in + 4 * i), cv;
-        float* e = reinterpret_cast<float*>(&v);
-        float* ec = reinterpret_cast<float*>(&cv);
-#pragma unroll
-        for (int c = 0; c < 4; c++) one(4 * i + c, e[c], e[c], ec[c]);
-        st_stream4(os + 4 * i, v);
-        st_stream4(oc + 4 * i, cv);
+  }
+}
+
+// The accurate path on the queued elements, 256 at a time.
+template <class E>
+__device__ __forceinline__ void batch_flush(BDeferred& q, const typename E::Tab& tab,
+                                            BReqTab reqs, DevStats* st) {
+  const unsigned n = q.n < QCAP ? q.n : QCAP;  // see run_queue
+  for (unsigned k = threadIdx.x; k < n; k += BLOCK) {
+    const AccResult2 a = E::accurate(q.x[k], tab);
+    const unsigned ri = q.req[k], idx = q.idx[k];
+    float* out = reqs[ri].out;
+    out[idx] = a.s;
+    if (E::TWO) out[(size_t)reqs[ri].n + idx] = a.c;
+    if (!a.ok) note_escape(st, batch_escape_id(reqs[ri].orig, idx));
+  }
+  if (threadIdx.x == 0) {
+    q.lanes += n;
+    q.waves += (n + 63) / 64;
+  }
+}
+
+// The workgroup's tiles t, t + step, ... < t1 that share the function of request ri;
+// t and ri move past them.  find(t): the request of tile t.
+template <class E, class Find>
+__device__ __forceinline__ void batch_segment(BReqTab reqs, int& t, int step, int t1, int& ri,
+                                              int tile, const Find& find, BShared& sh, bool force,
+                                              DevStats* st) {
+  typename E::Tab& tab = *reinterpret_cast<typename E::Tab*>(sh.tab);
+  BDeferred& q = sh.q;
+  E::load(tab, threadIdx.x);
+  if (threadIdx.x == 0) q.n = 0;
+  __syncthreads();
+  // the next tile's request is looked up while this tile is evaluated
+  BReq R = {reqs[ri].in, reqs[ri].out, reqs[ri].n, reqs[ri].tile0, reqs[ri].key, reqs[ri].orig};
+  const int key = R.key;
+  int iter = 0, next;
+  do {
+    const unsigned start = (unsigned)(t - (int)R.tile0) * (unsigned)tile;
+    next = t + step < t1 ? find(t + step) : ri;
+    const BReq N = {reqs[next].in,    reqs[next].out, reqs[next].n,
+                    reqs[next].tile0, reqs[next].key, reqs[next].orig};
+    batch_tile<E>(R, ri, start, min(R.n - start, (unsigned)tile), tab, q, force, st);
+    R = N;
+    if (++iter % E::qcheck == 0) {
+      __syncthreads();
+      const unsigned nq = __builtin_amdgcn_readfirstlane(q.n);
+      __syncthreads();
+      if (nq > QFLUSH) {
+        batch_flush<E>(q, tab, reqs, st);
+        __syncthreads();
+        if (threadIdx.x == 0) q.n = 0;
+        __syncthreads();
       }
     }
-    i0 = 4 * n4;
+    t += step;
+    ri = next;
+  } while (t < t1 && R.key == key);
+  __syncthreads();
+  batch_flush<E>(q, tab, reqs, st);
+  if (t < t1) __syncthreads();  // the tables and the queue are free for the next function
+}
+
+// The workgroup's counters to the device statistics.
+__device__ __forceinline__ void batch_count(const BDeferred& q, DevStats* st) {
+  if (threadIdx.x == 0 && q.lanes) {
+    CounterSlot& c = st->slot[blockIdx.x % NSLOT];
+    atomicAdd(&c.fallback_lanes, (unsigned long long)q.lanes);
+    atomicAdd(&c.fallback_waves, (unsigned long long)q.waves);
   }
-  for (int i = i0 + threadIdx.x; i < cnt; i += BLOCK) {
-    float sv, c;
-    one(i, in[i], sv, c);
-    os[i] = sv;
-    oc[i] = c;
+}
+
+template <bool SPLIT, class Find>
+__device__ __forceinline__ void batch_run(BReqTab reqs, int t, int t1, int tile,
+                                          const Find& find, DevStats* st, unsigned flags) {
+  __shared__ BShared sh;
+  if (threadIdx.x == 0) sh.q.lanes = sh.q.waves = 0;
+  const bool force = flags & CR_FLAG_FORCE_FALLBACK;
+  int ri = find(t);
+#define CR_SEG(id, ...)                                                                 \
+  case id:                                                                              \
+    batch_segment<__VA_ARGS__>(reqs, t, 1, t1, ri, tile, find, sh, force, st);          \
+    break
+  while (t < t1) {
+    if (!SPLIT) {
+      switch (__builtin_amdgcn_readfirstlane(reqs[ri].key)) {
+        CR_SEG(CR_EXPF, BOne<OpExp<EXPK_E>>);
+        CR_SEG(CR_EXP2F, BOne<OpExp<EXPK_2>>);
+        CR_SEG(CR_EXP10F, BOne<OpExp<EXPK_10>>);
+        CR_SEG(CR_EXPM1F, BOne<OpExp<EXPK_EM1>>);
+        CR_SEG(CR_LOGF, BOne<OpLog<LOGK_E>>);
+        CR_SEG(CR_LOG2F, BOne<OpLog<LOGK_2>>);
+        CR_SEG(CR_LOG10F, BOne<OpLog<LOGK_10>>);
+        CR_SEG(CR_LOG1PF, BOne<OpLog<LOGK_1P>>);
+        CR_SEG(CR_RSQRTF, BOne<OpRsqrt>);
+        CR_SEG(CR_SINF, BOne<OpTrig<TRIGK_SIN>>);
+        CR_SEG(CR_COSF, BOne<OpTrig<TRIGK_COS>>);
+        CR_SEG(CR_SINCOSF, BTwo<SinCosF64>);
+        CR_SEG(CR_TANF, BOne<OpTrig<TRIGK_TAN>>);
+        CR_SEG(CR_ASINF, BOne<OpAtan<ATANK_ASIN>>);
+        CR_SEG(CR_ACOSF, BOne<OpAtan<ATANK_ACOS>>);
+        CR_SEG(CR_ATANF, BOne<OpAtan<ATANK_ATAN>>);
+        CR_SEG(CR_SINHF, BOne<OpHyp<HYPK_SINH>>);
+        CR_SEG(CR_COSHF, BOne<OpHyp<HYPK_COSH>>);
+        CR_SEG(CR_TANHF, BOne<OpHyp<HYPK_TANH>>);
+        default: return;  // not reached: the host builds the keys
+      }
+    } else {
+      switch (__builtin_amdgcn_readfirstlane(reqs[ri].key) - BSPLIT) {
+        CR_SEG(CR_EXPF, BOne<OpSExp<EXPK_E>>);
+        CR_SEG(CR_EXP2F, BOne<OpSExp<EXPK_2>>);
+        CR_SEG(CR_EXP10F, BOne<OpSExp<EXPK_10>>);
+        CR_SEG(CR_EXPM1F, BOne<OpSExp<EXPK_EM1>>);
+        CR_SEG(CR_LOGF, BOne<OpSLog<LOGK_E>>);
+        CR_SEG(CR_LOG2F, BOne<OpSLog<LOGK_2>>);
+        CR_SEG(CR_LOG10F, BOne<OpSLog<LOGK_10>>);
+        CR_SEG(CR_LOG1PF, BOne<OpSLog<LOGK_1P>>);
+        CR_SEG(CR_RSQRTF, BOne<OpSRsqrt>);
+        CR_SEG(CR_SINF, BOne<OpSTrig<TRIGK_SIN>>);
+        CR_SEG(CR_COSF, BOne<OpSTrig<TRIGK_COS>>);
+        CR_SEG(CR_SINCOSF, BTwo<SinCosSplit>);
+        CR_SEG(CR_TANF, BOne<OpSTrig<TRIGK_TAN>>);
+        CR_SEG(CR_ASINF, BOne<OpSAtan<ATANK_ASIN>>);
+        CR_SEG(CR_ACOSF, BOne<OpSAtan<ATANK_ACOS>>);
+        CR_SEG(CR_ATANF, BOne<OpSAtan<ATANK_ATAN>>);
+        CR_SEG(CR_SINHF, BOne<OpSHyp<HYPK_SINH>>);
+        CR_SEG(CR_COSHF, BOne<OpSHyp<HYPK_COSH>>);
+        CR_SEG(CR_TANHF, BOne<OpSHyp<HYPK_TANH>>);
+        default: return;
+      }
+    }
   }
+#undef CR_SEG
+  batch_count(sh.q, st);
 }
 
-// Run the accurate path on the queued elements (see run_queue).
-template <class Op, bool FINAL = false>
-__device__ __forceinline__ void batch_flush_one(BDeferred& q, const typename Op::Tab& tab,
-                                                const BReq* reqs, DevStats* st) {
-  run_queue<FINAL>(q, st, [&](unsigned k) {
-    AccResult a = Op::accurate(q.x[k], tab);
-    float* out = reinterpret_cast<float*>(reqs[q.req[k]].out);
-    out[q.idx[k]] = a.r;
-    if (!a.ok) note_escape(st, batch_escape_id(reqs[q.req[k]].orig, q.idx[k]));
-  });
-}
-
-template <class SC, bool FINAL = false>
-__device__ __forceinline__ void batch_flush_one_sincos(BDeferred& q, const typename SC::Tab& tab,
-                                                       const BReq* reqs, DevStats* st) {
-  run_queue<FINAL>(q, st, [&](unsigned k) {
-    AccResult2 a = SC::accurate(q.x[k], tab);
-    const BReq& R = reqs[q.req[k]];
-    float* out = reinterpret_cast<float*>(R.out);
-    out[q.idx[k]] = a.s;
-    out[R.n + q.idx[k]] = a.c;
-    if (!a.ok) note_escape(st, batch_escape_id(reqs[q.req[k]].orig, q.idx[k]));
-  });
-}
-
-// The batch runs one persistent kernel per function present (implementation
-// and function: the tiles are sorted by both), all captured in the plan's one
-// graph and run back to back.  Each kernel is specialised on its function, so
-// it keeps only that function's tables in LDS and only that function's
-// registers (one kernel over all functions would run every function at the
-// occupancy of the largest).  Workgroup b takes tiles t0 + b, t0 + b + grid,
-// ... of its function's contiguous range [t0, t1).
-template <class Op>
+// One function's tiles [t0, t1) of a large plan, strided over the grid.
+template <class E>
 __global__ void __launch_bounds__(BLOCK)
-    k_tiles(const BReq* reqs, const BTile* tiles, long long t0, long long t1, DevStats* st,
+    k_tiles(BReqTab reqs, BTileTab tile_req, int t0, int t1, int tile, DevStats* st,
             unsigned flags) {
-  __shared__ typename Op::Tab tab;
-  __shared__ BDeferred q;
-  Op::load(tab, threadIdx.x);
-  if (threadIdx.x == 0) {
-    q.n = 0;
-    q.lanes = q.waves = 0;
-  }
-  __syncthreads();
-  const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  int iter = 0;
-  for (long long t = t0 + blockIdx.x; t < t1; t += gridDim.x, iter++) {
-    const BTile T = tiles[t];
-    batch_tile<Op>(reqs[T.req], T, tab, q, force, st);
-    if (iter % Op::qcheck == Op::qcheck - 1) {
-      __syncthreads();
-      const unsigned nq = __builtin_amdgcn_readfirstlane(q.n);
-      __syncthreads();
-      if (nq > QFLUSH) batch_flush_one<Op>(q, tab, reqs, st);
-    }
-  }
-  __syncthreads();
-  batch_flush_one<Op, true>(q, tab, reqs, st);
+  __shared__ BShared sh;
+  if (threadIdx.x == 0) sh.q.lanes = sh.q.waves = 0;
+  const auto find = [&](int k) { return (int)__builtin_amdgcn_readfirstlane(tile_req[k]); };
+  int t = t0 + (int)blockIdx.x, ri = find(t);
+  batch_segment<E>(reqs, t, (int)gridDim.x, t1, ri, tile, find, sh,
+                   flags & CR_FLAG_FORCE_FALLBACK, st);
+  batch_count(sh.q, st);
 }
 
-template <class SC>
+// Tiles [t0, t1) of the batch, `per` to a workgroup, tables in device memory.
+template <bool SPLIT>
 __global__ void __launch_bounds__(BLOCK)
-    k_tiles_sincos(const BReq* reqs, const BTile* tiles, long long t0, long long t1,
-                   DevStats* st, unsigned flags) {
-  __shared__ typename SC::Tab tab;
-  __shared__ BDeferred q;
-  SC::load(tab, threadIdx.x);
-  if (threadIdx.x == 0) {
-    q.n = 0;
-    q.lanes = q.waves = 0;
-  }
-  __syncthreads();
-  const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  int iter = 0;
-  for (long long t = t0 + blockIdx.x; t < t1; t += gridDim.x, iter++) {
-    const BTile T = tiles[t];
-    batch_tile_sincos<SC>(reqs[T.req], T, tab, q, force, st);
-    if (iter % SC::qcheck == SC::qcheck - 1) {
-      __syncthreads();
-      const unsigned nq = __builtin_amdgcn_readfirstlane(q.n);
-      __syncthreads();
-      if (nq > QFLUSH) batch_flush_one_sincos<SC>(q, tab, reqs, st);
-    }
-  }
-  __syncthreads();
-  batch_flush_one_sincos<SC, true>(q, tab, reqs, st);
+    k_batch(BReqTab reqs, BTileTab tile_req, int t0, int t1, int per, int tile,
+            DevStats* st, unsigned flags) {
+  const int t = t0 + (int)blockIdx.x * per;
+  batch_run<SPLIT>(reqs, t, min(t + per, t1), tile,
+                   [&](int k) { return (int)__builtin_amdgcn_readfirstlane(tile_req[k]); }, st,
+                   flags);
+}
+// The same with the requests as kernel arguments (the first argument lies at the
+// start of the kernel argument segment, read in place).  Tile k belongs to the
+// last request whose first tile is not beyond k: a count over the wave's lanes.
+template <bool SPLIT>
+__global__ void __launch_bounds__(BLOCK)
+    k_batch_args(const BArgs args, int t1, int per, int tile, DevStats* st, unsigned flags) {
+  typedef const __attribute__((address_space(4))) BArgs* ArgTab;
+  const ArgTab a = (ArgTab)__builtin_amdgcn_kernarg_segment_ptr();
+  const int lane = threadIdx.x & 63;
+  const unsigned lo = a->tile0[lane], hi = a->tile0[lane + 64];
+  const int t = (int)blockIdx.x * per;
+  batch_run<SPLIT>(a->req, t, min(t + per, t1), tile,
+                   [&](int k) {
+                     return __popcll(__ballot(lo <= (unsigned)k)) +
+                            __popcll(__ballot(hi <= (unsigned)k)) - 1;
+                   },
+                   st, flags);
 }
 
 __global__ void k_zero_stats(DevStats* st) {
@@ -1781,32 +1867,38 @@ const char* const FUNC_NAMES[NFUNC_IDX] = {
 int func_of_idx(int i) { return i < CR_NUM_F32 ? i : EXTRA_FUNCS[i - CR_NUM_F32]; }
 
 // ------------------------------------------------------------ batch plans
-}  // namespace
 
-struct cr_batch_plan {
-  int device;
-  BReq* d_reqs;
-  BTile* d_tiles;
-  long long ntiles;
-  int grid;
-  unsigned flags;
-  hipGraphExec_t exec;
-  hipEvent_t done;
-  bool launched;
-  long long elems;
+// A batch on the host: the requests with elements, sorted by (implementation,
+// function), and the request of every tile.
+struct BatchTables {
+  std::vector<BReq> reqs;
+  std::vector<unsigned> tile_req;
+  int split_req = 0, split_tile = 0;  // where the binary32-only ones begin
+  int tile = TILE;                    // elements per tile
+  long long elems = 0;
 };
 
-namespace {
+// The functions in the order a batch evaluates them within an implementation: the
+// most expensive element first, so that the last workgroups are short ones.
+constexpr int BATCH_ORDER[CR_NUM_F32] = {
+    CR_SINCOSF, CR_TANF,  CR_ACOSF, CR_ASINF,  CR_SINF,   CR_COSF,  CR_ATANF,
+    CR_SINHF,   CR_TANHF, CR_COSHF, CR_LOG1PF, CR_EXPM1F, CR_LOGF,  CR_LOG10F,
+    CR_LOG2F,   CR_EXP2F, CR_EXP10F, CR_EXPF,  CR_RSQRTF};
 
-// Validate requests and build the request and tile tables (host side).
-int build_tables(const cr_request* reqs, int32_t num, std::vector<BReq>& hr,
-                 std::vector<BTile>& ht, long long& elems) {
+// Workgroups per compute unit of the batch kernels, per implementation
+// (binary64-internal, binary32-only): a tuned setting (cr_tune_batch_set, the
+// "batch" lines of the tuning file).  The graph of a large plan runs up to four
+// per-function kernels at a time with this many each (2, 4, 8: 636, 588, 592 us on
+// 3.07e8 elements); the one kernel over all functions gets BATCH_GRID_SCALE times as
+// many, of which four fit at a time: the rest start as others end, which evens out
+// the functions' different costs (a scale of 1, 4, 8: 48, 41, 38 us on 12.4e6).
+constexpr int BATCH_BPC_DEFAULT = 4, BATCH_GRID_SCALE = 8;
+std::atomic<int> g_batch_bpc[2] = {BATCH_BPC_DEFAULT, BATCH_BPC_DEFAULT};
+
+// Validate requests and build the tables.
+int build_tables_unguarded(const cr_request* reqs, int32_t num, BatchTables& T) {
   if (num < 0) return CR_E_SIZE;
   if (num > 0 && !reqs) return CR_E_NULL;
-  hr.clear();
-  ht.clear();
-  elems = 0;
-  std::vector<int> order(num);
   for (int i = 0; i < num; i++) {
     const cr_request& r = reqs[i];
     if (r.func_id < 0 || r.func_id >= CR_NUM_F32) return CR_E_FUNC;
@@ -1821,136 +1913,242 @@ int build_tables(const cr_request* reqs, int32_t num, std::vector<BReq>& hr,
     bool same = a == b && nout == (size_t)r.n;
     if (!same && a < b + nout * 4 && b < a + (size_t)r.n * 4) return CR_E_OVERLAP;
     if (!cr_available(r.func_id, r.impl)) return CR_E_IMPL;
+    T.elems += r.n;
   }
-  // order requests by (implementation, function) so that tiles sharing tables
-  // are adjacent
-  auto key = [&](int i) {
-    return reqs[i].func_id + (reqs[i].impl == CR_IMPL_SPLIT_F32 ? BSPLIT : 0);
-  };
-  for (int i = 0; i < num; i++) order[i] = i;
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return key(x) < key(y); });
-  for (int oi = 0; oi < num; oi++) {
-    const cr_request& r = reqs[order[oi]];
-    if (r.n == 0) continue;
-    BReq q;
-    q.in = r.in;
-    q.out = r.out;
-    q.n = r.n;
-    q.func = r.func_id;
-    q.key = key(order[oi]);
-    q.orig = order[oi];
-    uintptr_t a = (uintptr_t)r.in, b = (uintptr_t)r.out;
-    uintptr_t c = b + 4 * (uintptr_t)r.n;
-    q.aligned = ((a | b) & 15) == 0 && (r.func_id != CR_SINCOSF || (c & 15) == 0);
-    int ri = (int)hr.size();
-    hr.push_back(q);
-    for (long long s = 0; s < r.n; s += TILE) {
-      BTile t;
-      t.req = ri;
-      t.start = s;
-      t.count = (int)((r.n - s) < TILE ? (r.n - s) : TILE);
-      ht.push_back(t);
+  int rank[CR_NUM_F32];
+  for (int k = 0; k < CR_NUM_F32; k++) rank[BATCH_ORDER[k]] = k;
+  std::vector<std::pair<int, int>> order;  // (rank, index in the caller's array)
+  for (int i = 0; i < num; i++)
+    if (reqs[i].n > 0)
+      order.push_back({rank[reqs[i].func_id] +
+                           (reqs[i].impl == CR_IMPL_SPLIT_F32 ? CR_NUM_F32 : 0), i});
+  std::sort(order.begin(), order.end());
+  // A batch that leaves the chip short of workgroups is cut finer, up to 8 tiles per
+  // compute unit.  Finer still costs more in look-ups than it gains: at up to 32 tiles
+  // per compute unit 12.4e6 elements took 42 us instead of 38, 3.2e6 19 instead of 16.
+  for (T.tile = TILE / 4; T.tile < TILE && T.elems / T.tile > 8LL * num_cus(); T.tile *= 2) {
+  }
+  long long ntiles = 0;
+  for (const auto& o : order) ntiles += (reqs[o.second].n + T.tile - 1) / T.tile;
+  if (ntiles > ((long long)1 << 30)) return CR_E_SIZE;
+  T.reqs.reserve(order.size());
+  T.tile_req.reserve((size_t)ntiles);
+  for (const auto& o : order) {
+    const cr_request& r = reqs[o.second];
+    const bool split = o.first >= CR_NUM_F32;
+    if (!split) {
+      T.split_req++;
+      T.split_tile += (int)((r.n + T.tile - 1) / T.tile);
     }
-    elems += r.n;
+    const unsigned ri = (unsigned)T.reqs.size();
+    T.reqs.push_back({(const float*)r.in, (float*)r.out, (unsigned)r.n,
+                      (unsigned)T.tile_req.size(), r.func_id + (split ? BSPLIT : 0), o.second});
+    T.tile_req.insert(T.tile_req.end(), (size_t)((r.n + T.tile - 1) / T.tile), ri);
   }
   return CR_OK;
 }
 
-// Contiguous tile ranges of one key (function + BSPLIT for the split
-// implementation) in the sorted tile table.
-struct BRange {
-  int key;
-  long long t0, t1;
+int build_tables(const cr_request* reqs, int32_t num, BatchTables& T) {
+  try {
+    return build_tables_unguarded(reqs, num, T);
+  } catch (const std::bad_alloc&) {
+    return CR_E_NOMEM;
+  }
+}
+
+// Tiles per workgroup for a launch of nt tiles.
+int batch_per(long long nt, bool split) {
+  const long long grid = (long long)num_cus() * BATCH_GRID_SCALE * g_batch_bpc[split ? 1 : 0].load();
+  return (int)((nt + grid - 1) / grid);
+}
+
+// The batch from tables in device memory: one kernel per implementation present.
+hipError_t launch_batch(const BReq* reqs, const unsigned* tile_req, const BatchTables& T,
+                        const int (&per)[2], DevStats* st, unsigned flags, hipStream_t s) {
+  const int nt = (int)T.tile_req.size();
+  if (T.split_tile > 0)
+    hipLaunchKernelGGL(k_batch<false>, dim3((T.split_tile + per[0] - 1) / per[0]), dim3(BLOCK), 0,
+                       s, (BReqTab)reqs, (BTileTab)tile_req, 0, T.split_tile, per[0], T.tile, st, flags);
+  if (nt > T.split_tile)
+    hipLaunchKernelGGL(k_batch<true>, dim3((nt - T.split_tile + per[1] - 1) / per[1]), dim3(BLOCK),
+                       0, s, (BReqTab)reqs, (BTileTab)tile_req, T.split_tile, nt, per[1], T.tile, st, flags);
+  return hipGetLastError();
+}
+
+// One kernel per function present, on the streams in turn.
+template <class E>
+void launch_tiles(const BReq* r, const unsigned* tr, int t0, int t1, int grid, int tile,
+                  DevStats* st, unsigned flags, hipStream_t s) {
+  hipLaunchKernelGGL(k_tiles<E>, dim3(grid), dim3(BLOCK), 0, s, (BReqTab)r, (BTileTab)tr, t0, t1, tile, st, flags);
+}
+int launch_functions(const BReq* r, const unsigned* tr, const BatchTables& T, DevStats* st,
+                     unsigned flags, hipStream_t* streams, int nstreams) {
+  const int n = (int)T.reqs.size(), nt = (int)T.tile_req.size();
+  int si = 0;
+  for (int r0 = 0, r1; r0 < n; r0 = r1) {
+    const int key = T.reqs[r0].key;
+    for (r1 = r0; r1 < n && T.reqs[r1].key == key;) r1++;
+    const int t0 = (int)T.reqs[r0].tile0, t1 = r1 < n ? (int)T.reqs[r1].tile0 : nt;
+    const int g = (int)std::min<long long>(
+        t1 - t0, (long long)num_cus() * g_batch_bpc[key >= BSPLIT ? 1 : 0].load());
+    hipStream_t s = streams[si++ % nstreams];
+    switch (key) {
+#define CR_CASE(id, ...)                                               \
+  case id:                                                             \
+    launch_tiles<__VA_ARGS__>(r, tr, t0, t1, g, T.tile, st, flags, s); \
+    break
+      CR_CASE(CR_EXPF, BOne<OpExp<EXPK_E>>);
+      CR_CASE(CR_EXP2F, BOne<OpExp<EXPK_2>>);
+      CR_CASE(CR_EXP10F, BOne<OpExp<EXPK_10>>);
+      CR_CASE(CR_EXPM1F, BOne<OpExp<EXPK_EM1>>);
+      CR_CASE(CR_LOGF, BOne<OpLog<LOGK_E>>);
+      CR_CASE(CR_LOG2F, BOne<OpLog<LOGK_2>>);
+      CR_CASE(CR_LOG10F, BOne<OpLog<LOGK_10>>);
+      CR_CASE(CR_LOG1PF, BOne<OpLog<LOGK_1P>>);
+      CR_CASE(CR_RSQRTF, BOne<OpRsqrt>);
+      CR_CASE(CR_SINF, BOne<OpTrig<TRIGK_SIN>>);
+      CR_CASE(CR_COSF, BOne<OpTrig<TRIGK_COS>>);
+      CR_CASE(CR_SINCOSF, BTwo<SinCosF64>);
+      CR_CASE(CR_TANF, BOne<OpTrig<TRIGK_TAN>>);
+      CR_CASE(CR_ASINF, BOne<OpAtan<ATANK_ASIN>>);
+      CR_CASE(CR_ACOSF, BOne<OpAtan<ATANK_ACOS>>);
+      CR_CASE(CR_ATANF, BOne<OpAtan<ATANK_ATAN>>);
+      CR_CASE(CR_SINHF, BOne<OpHyp<HYPK_SINH>>);
+      CR_CASE(CR_COSHF, BOne<OpHyp<HYPK_COSH>>);
+      CR_CASE(CR_TANHF, BOne<OpHyp<HYPK_TANH>>);
+      CR_CASE(BSPLIT + CR_EXPF, BOne<OpSExp<EXPK_E>>);
+      CR_CASE(BSPLIT + CR_EXP2F, BOne<OpSExp<EXPK_2>>);
+      CR_CASE(BSPLIT + CR_EXP10F, BOne<OpSExp<EXPK_10>>);
+      CR_CASE(BSPLIT + CR_EXPM1F, BOne<OpSExp<EXPK_EM1>>);
+      CR_CASE(BSPLIT + CR_LOGF, BOne<OpSLog<LOGK_E>>);
+      CR_CASE(BSPLIT + CR_LOG2F, BOne<OpSLog<LOGK_2>>);
+      CR_CASE(BSPLIT + CR_LOG10F, BOne<OpSLog<LOGK_10>>);
+      CR_CASE(BSPLIT + CR_LOG1PF, BOne<OpSLog<LOGK_1P>>);
+      CR_CASE(BSPLIT + CR_RSQRTF, BOne<OpSRsqrt>);
+      CR_CASE(BSPLIT + CR_SINF, BOne<OpSTrig<TRIGK_SIN>>);
+      CR_CASE(BSPLIT + CR_COSF, BOne<OpSTrig<TRIGK_COS>>);
+      CR_CASE(BSPLIT + CR_SINCOSF, BTwo<SinCosSplit>);
+      CR_CASE(BSPLIT + CR_TANF, BOne<OpSTrig<TRIGK_TAN>>);
+      CR_CASE(BSPLIT + CR_ASINF, BOne<OpSAtan<ATANK_ASIN>>);
+      CR_CASE(BSPLIT + CR_ACOSF, BOne<OpSAtan<ATANK_ACOS>>);
+      CR_CASE(BSPLIT + CR_ATANF, BOne<OpSAtan<ATANK_ATAN>>);
+      CR_CASE(BSPLIT + CR_SINHF, BOne<OpSHyp<HYPK_SINH>>);
+      CR_CASE(BSPLIT + CR_COSHF, BOne<OpSHyp<HYPK_COSH>>);
+      CR_CASE(BSPLIT + CR_TANHF, BOne<OpSHyp<HYPK_TANH>>);
+#undef CR_CASE
+      default: return CR_E_FUNC;
+    }
+  }
+  return CR_OK;
+}
+
+// Plans of more elements than this run one kernel per function (at most 8 waves per
+// SIMD instead of the 4 that the registers of the most demanding function leave the
+// one kernel), captured in a graph on four parallel branches, whose 125 us of launch
+// work then overlaps the kernels: 3.07e8 elements 588 us against about 630 by the one
+// kernel, 1.14e8 256 against 255, 5.6e7 158 against 125-143.
+constexpr long long GRAPH_ELEMS = 1LL << 26;
+
+// The graph of a plan's per-function kernels: private streams at default priority,
+// a fork from the origin stream and a join back to it, so that one kernel's tail
+// overlaps the next kernel's start.
+hipError_t capture_functions(const BReq* r, const unsigned* tr, const BatchTables& T, DevStats* st,
+                             unsigned flags, hipGraphExec_t* exec) {
+  constexpr int NBRANCH = 4;
+  hipStream_t cs = nullptr, side[NBRANCH] = {};
+  hipEvent_t fork = nullptr, join[NBRANCH] = {};
+  hipGraph_t g = nullptr;
+  hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
+  for (int b = 0; b < NBRANCH && e == hipSuccess; b++) {
+    e = hipStreamCreateWithFlags(&side[b], hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&join[b], hipEventDisableTiming);
+  }
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+  if (e == hipSuccess) {
+    hipError_t ec = hipEventRecord(fork, cs);
+    for (int b = 0; b < NBRANCH && ec == hipSuccess; b++) ec = hipStreamWaitEvent(side[b], fork, 0);
+    int rc = ec == hipSuccess ? launch_functions(r, tr, T, st, flags, side, NBRANCH) : CR_OK;
+    for (int b = 0; b < NBRANCH && ec == hipSuccess; b++) {
+      ec = hipEventRecord(join[b], side[b]);
+      if (ec == hipSuccess) ec = hipStreamWaitEvent(cs, join[b], 0);
+    }
+    hipError_t e2 = hipStreamEndCapture(cs, &g);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = ec;
+    if (e == hipSuccess) e = e2;
+    if (e == hipSuccess && rc != CR_OK) e = hipErrorInvalidValue;
+  }
+  if (e == hipSuccess) e = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
+  if (g) (void)hipGraphDestroy(g);
+  if (fork) (void)hipEventDestroy(fork);
+  for (int b = 0; b < NBRANCH; b++) {
+    if (join[b]) (void)hipEventDestroy(join[b]);
+    if (side[b]) (void)hipStreamDestroy(side[b]);
+  }
+  if (cs) (void)hipStreamDestroy(cs);
+  return e;
+}
+
+// The batch from kernel arguments, BARG requests of one implementation a launch.
+int args_launches(const BatchTables& T) {
+  return (T.split_req + BARG - 1) / BARG + ((int)T.reqs.size() - T.split_req + BARG - 1) / BARG;
+}
+hipError_t launch_batch_args(const BatchTables& T, DevStats* st, unsigned flags, hipStream_t s) {
+  BArgs a;
+  for (int r0 = 0, n = (int)T.reqs.size(); r0 < n;) {
+    const bool split = r0 >= T.split_req;
+    const int r1 = std::min(r0 + BARG, split ? n : T.split_req);
+    const unsigned base = T.reqs[r0].tile0;
+    const int nt = (int)((r1 < n ? T.reqs[r1].tile0 : (unsigned)T.tile_req.size()) - base);
+    for (int k = 0; k < 128; k++) {
+      a.tile0[k] = k < r1 - r0 ? T.reqs[r0 + k].tile0 - base : 0xffffffffu;
+      if (k < r1 - r0) {
+        a.req[k] = T.reqs[r0 + k];
+        a.req[k].tile0 -= base;
+      }
+    }
+    const int per = batch_per(nt, split);
+    if (split)
+      hipLaunchKernelGGL(k_batch_args<true>, dim3((nt + per - 1) / per), dim3(BLOCK), 0, s, a, nt,
+                         per, T.tile, st, flags);
+    else
+      hipLaunchKernelGGL(k_batch_args<false>, dim3((nt + per - 1) / per), dim3(BLOCK), 0, s, a, nt,
+                         per, T.tile, st, flags);
+    r0 = r1;
+  }
+  return hipGetLastError();
+}
+
+// Whether a batch goes by kernel arguments: a launch costs about 4.5 us here, the
+// allocation and copy of the tables and the wait for it about 35 us more than that
+// (200 requests, three launches: 18 us; 512 requests by tables: 44 us), so up to
+// ARGS_LAUNCHES launches.  A stream being captured keeps to the tables.
+constexpr int ARGS_LAUNCHES = 4;
+bool by_args(const BatchTables& T, hipStream_t s) {
+  if (args_launches(T) > ARGS_LAUNCHES) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs == hipStreamCaptureStatusNone;
+}
+
+}  // namespace
+
+struct cr_batch_plan {
+  int device;
+  BReq* d_reqs;
+  unsigned* d_tile_req;
+  BatchTables tables;
+  DevStats* stats;
+  int per[2];  // tiles per workgroup, binary64-internal and binary32-only
+  unsigned flags;
+  hipGraphExec_t exec;  // large plans: the per-function kernels
+  hipEvent_t done;
+  bool launched;
 };
-
-std::vector<BRange> key_ranges(const std::vector<BReq>& hr, const std::vector<BTile>& ht) {
-  std::vector<BRange> rs;
-  for (long long t = 0; t < (long long)ht.size(); t++) {
-    int key = hr[ht[t].req].key;
-    if (rs.empty() || rs.back().key != key) rs.push_back({key, t, t});
-    rs.back().t1 = t + 1;
-  }
-  return rs;
-}
-
-template <class Op>
-void launch_tiles_op(const BReq* r, const BTile* t, const BRange& g, int grid, DevStats* st,
-                     unsigned flags, hipStream_t s) {
-  hipLaunchKernelGGL(k_tiles<Op>, dim3(grid), dim3(BLOCK), 0, s, r, t, g.t0, g.t1, st, flags);
-}
-
-// Workgroups per compute unit of each batch kernel, per implementation
-// (binary64-internal, binary32-only): a tuned setting (cr_tune_batch_set, the
-// "batch" lines of the tuning file).  The plan's graph runs up to four kernels
-// at a time (parallel branches), so together they hold about four times as
-// many workgroups per CU; the default, 4, was the best of {1, 2, 4, 8, 16, 32}
-// on the 4096-request workload when it was chosen (1 -> 361, 2 -> 413,
-// 4 -> 428, 8 -> 422, 16 -> 411, 32 -> 385 Gelem/s).
-constexpr int BATCH_BPC_DEFAULT = 4;
-std::atomic<int> g_batch_bpc[2] = {BATCH_BPC_DEFAULT, BATCH_BPC_DEFAULT};
-
-// Launch the kernel of one key range (at most one workgroup per tile).
-int launch_tiles(const BReq* r, const BTile* t, const BRange& g, DevStats* st, unsigned flags,
-                 hipStream_t s) {
-  long long grid = (long long)num_cus() * g_batch_bpc[g.key >= BSPLIT ? 1 : 0].load();
-  if (grid > g.t1 - g.t0) grid = g.t1 - g.t0;
-  const int G = (int)grid;
-  switch (g.key) {
-    case CR_EXPF: launch_tiles_op<OpExp<EXPK_E>>(r, t, g, G, st, flags, s); break;
-    case CR_EXP2F: launch_tiles_op<OpExp<EXPK_2>>(r, t, g, G, st, flags, s); break;
-    case CR_EXP10F: launch_tiles_op<OpExp<EXPK_10>>(r, t, g, G, st, flags, s); break;
-    case CR_EXPM1F: launch_tiles_op<OpExp<EXPK_EM1>>(r, t, g, G, st, flags, s); break;
-    case CR_LOGF: launch_tiles_op<OpLog<LOGK_E>>(r, t, g, G, st, flags, s); break;
-    case CR_LOG2F: launch_tiles_op<OpLog<LOGK_2>>(r, t, g, G, st, flags, s); break;
-    case CR_LOG10F: launch_tiles_op<OpLog<LOGK_10>>(r, t, g, G, st, flags, s); break;
-    case CR_LOG1PF: launch_tiles_op<OpLog<LOGK_1P>>(r, t, g, G, st, flags, s); break;
-    case CR_RSQRTF: launch_tiles_op<OpRsqrt>(r, t, g, G, st, flags, s); break;
-    case CR_SINF: launch_tiles_op<OpTrig<TRIGK_SIN>>(r, t, g, G, st, flags, s); break;
-    case CR_COSF: launch_tiles_op<OpTrig<TRIGK_COS>>(r, t, g, G, st, flags, s); break;
-    case CR_TANF: launch_tiles_op<OpTrig<TRIGK_TAN>>(r, t, g, G, st, flags, s); break;
-    case CR_SINCOSF:
-      hipLaunchKernelGGL(k_tiles_sincos<SinCosF64>, dim3(G), dim3(BLOCK), 0, s, r, t, g.t0, g.t1,
-                         st, flags);
-      break;
-    case CR_ASINF: launch_tiles_op<OpAtan<ATANK_ASIN>>(r, t, g, G, st, flags, s); break;
-    case CR_ACOSF: launch_tiles_op<OpAtan<ATANK_ACOS>>(r, t, g, G, st, flags, s); break;
-    case CR_ATANF: launch_tiles_op<OpAtan<ATANK_ATAN>>(r, t, g, G, st, flags, s); break;
-    case CR_SINHF: launch_tiles_op<OpHyp<HYPK_SINH>>(r, t, g, G, st, flags, s); break;
-    case CR_COSHF: launch_tiles_op<OpHyp<HYPK_COSH>>(r, t, g, G, st, flags, s); break;
-    case CR_TANHF: launch_tiles_op<OpHyp<HYPK_TANH>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_EXPF: launch_tiles_op<OpSExp<EXPK_E>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_EXP2F: launch_tiles_op<OpSExp<EXPK_2>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_EXP10F: launch_tiles_op<OpSExp<EXPK_10>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_EXPM1F: launch_tiles_op<OpSExp<EXPK_EM1>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_LOGF: launch_tiles_op<OpSLog<LOGK_E>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_LOG2F: launch_tiles_op<OpSLog<LOGK_2>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_LOG10F: launch_tiles_op<OpSLog<LOGK_10>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_LOG1PF: launch_tiles_op<OpSLog<LOGK_1P>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_RSQRTF: launch_tiles_op<OpSRsqrt>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_SINF: launch_tiles_op<OpSTrig<TRIGK_SIN>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_COSF: launch_tiles_op<OpSTrig<TRIGK_COS>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_TANF: launch_tiles_op<OpSTrig<TRIGK_TAN>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_SINCOSF:
-      hipLaunchKernelGGL(k_tiles_sincos<SinCosSplit>, dim3(G), dim3(BLOCK), 0, s, r, t, g.t0,
-                         g.t1, st, flags);
-      break;
-    case BSPLIT + CR_ASINF: launch_tiles_op<OpSAtan<ATANK_ASIN>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_ACOSF: launch_tiles_op<OpSAtan<ATANK_ACOS>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_ATANF: launch_tiles_op<OpSAtan<ATANK_ATAN>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_SINHF: launch_tiles_op<OpSHyp<HYPK_SINH>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_COSHF: launch_tiles_op<OpSHyp<HYPK_COSH>>(r, t, g, G, st, flags, s); break;
-    case BSPLIT + CR_TANHF: launch_tiles_op<OpSHyp<HYPK_TANH>>(r, t, g, G, st, flags, s); break;
-    default: return CR_E_FUNC;
-  }
-  return CR_OK;
-}
-
-}  // namespace
-
-extern "C" int cr_batch_plan_destroy(cr_batch_plan* plan);
-
-namespace {
-}  // namespace
 
 extern "C" {
 
@@ -2253,15 +2451,24 @@ int cr_dft(const float* x, int64_t n, const float* w, int64_t m, double* X, unsi
 }
 
 
+int cr_batch_plan_destroy(cr_batch_plan* plan) {
+  if (!plan) return CR_OK;
+  if (plan->launched && plan->done) (void)hipEventSynchronize(plan->done);
+  if (plan->exec) (void)hipGraphExecDestroy(plan->exec);
+  if (plan->done) (void)hipEventDestroy(plan->done);
+  if (plan->d_reqs) (void)hipFree(plan->d_reqs);
+  if (plan->d_tile_req) (void)hipFree(plan->d_tile_req);
+  delete plan;
+  return CR_OK;
+}
+
 int cr_batch_plan_create(const cr_request* reqs, int32_t num, unsigned flags,
                          cr_batch_plan** plan) {
   if (!plan) return CR_E_NULL;
   *plan = nullptr;
   if (flags & CR_FLAG_ROUND_MASK) return CR_E_IMPL;  // batches round to nearest
-  std::vector<BReq> hr;
-  std::vector<BTile> ht;
-  long long elems = 0;
-  int rc = build_tables(reqs, num, hr, ht, elems);
+  BatchTables T;
+  int rc = build_tables(reqs, num, T);
   if (rc) return rc;
   DevStats* st = nullptr;
   rc = get_stats(&st);
@@ -2269,12 +2476,15 @@ int cr_batch_plan_create(const cr_request* reqs, int32_t num, unsigned flags,
   cr_batch_plan* p = new cr_batch_plan();
   (void)hipGetDevice(&p->device);
   p->flags = flags;
-  p->ntiles = (long long)ht.size();
-  p->elems = elems;
-  p->grid = (int)(p->ntiles < grid_blocks() ? p->ntiles : grid_blocks());
+  p->stats = st;
+  p->tables = std::move(T);
+  const std::vector<BReq>& hr = p->tables.reqs;
+  const std::vector<unsigned>& ht = p->tables.tile_req;
+  p->per[0] = std::max(1, batch_per(p->tables.split_tile, false));
+  p->per[1] = std::max(1, batch_per((long long)ht.size() - p->tables.split_tile, true));
   hipError_t e = hipSuccess;
   if (!hr.empty()) e = hipMalloc(&p->d_reqs, hr.size() * sizeof(BReq));
-  if (e == hipSuccess && !ht.empty()) e = hipMalloc(&p->d_tiles, ht.size() * sizeof(BTile));
+  if (e == hipSuccess && !ht.empty()) e = hipMalloc(&p->d_tile_req, ht.size() * sizeof(unsigned));
   if (e != hipSuccess) {
     t_last_hip = (int)e;
     cr_batch_plan_destroy(p);
@@ -2282,52 +2492,10 @@ int cr_batch_plan_create(const cr_request* reqs, int32_t num, unsigned flags,
   }
   if (!hr.empty()) e = hipMemcpy(p->d_reqs, hr.data(), hr.size() * sizeof(BReq), hipMemcpyHostToDevice);
   if (e == hipSuccess && !ht.empty())
-    e = hipMemcpy(p->d_tiles, ht.data(), ht.size() * sizeof(BTile), hipMemcpyHostToDevice);
+    e = hipMemcpy(p->d_tile_req, ht.data(), ht.size() * sizeof(unsigned), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&p->done, hipEventDisableTiming);
-  // Capture the launches in a graph (private streams at default priority).
-  // The per-function kernels are spread over NBRANCH parallel branches (a
-  // fork from the origin stream and a join back to it) so that one kernel's
-  // tail overlaps the next kernel's start.
-  if (e == hipSuccess && p->grid > 0) {
-    constexpr int NBRANCH = 4;
-    hipStream_t cs = nullptr, side[NBRANCH] = {};
-    hipEvent_t fork = nullptr, join[NBRANCH] = {};
-    hipGraph_t g = nullptr;
-    e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
-    for (int b = 0; b < NBRANCH && e == hipSuccess; b++) {
-      e = hipStreamCreateWithFlags(&side[b], hipStreamNonBlocking);
-      if (e == hipSuccess) e = hipEventCreateWithFlags(&join[b], hipEventDisableTiming);
-    }
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-      hipError_t ec = hipEventRecord(fork, cs);
-      for (int b = 0; b < NBRANCH && ec == hipSuccess; b++)
-        ec = hipStreamWaitEvent(side[b], fork, 0);
-      int rc2 = CR_OK, i = 0;
-      if (ec == hipSuccess)
-        for (const BRange& g2 : key_ranges(hr, ht))
-          if (rc2 == CR_OK)
-            rc2 = launch_tiles(p->d_reqs, p->d_tiles, g2, st, flags, side[i++ % NBRANCH]);
-      for (int b = 0; b < NBRANCH && ec == hipSuccess; b++) {
-        ec = hipEventRecord(join[b], side[b]);
-        if (ec == hipSuccess) ec = hipStreamWaitEvent(cs, join[b], 0);
-      }
-      hipError_t e2 = hipStreamEndCapture(cs, &g);
-      e = hipGetLastError();
-      if (e == hipSuccess) e = ec;
-      if (e == hipSuccess) e = e2;
-      if (e == hipSuccess && rc2 != CR_OK) e = hipErrorInvalidValue;
-    }
-    if (e == hipSuccess) e = hipGraphInstantiate(&p->exec, g, nullptr, nullptr, 0);
-    if (g) (void)hipGraphDestroy(g);
-    if (fork) (void)hipEventDestroy(fork);
-    for (int b = 0; b < NBRANCH; b++) {
-      if (join[b]) (void)hipEventDestroy(join[b]);
-      if (side[b]) (void)hipStreamDestroy(side[b]);
-    }
-    if (cs) (void)hipStreamDestroy(cs);
-  }
+  if (e == hipSuccess && p->tables.elems > GRAPH_ELEMS)
+    e = capture_functions(p->d_reqs, p->d_tile_req, p->tables, st, flags, &p->exec);
   if (e != hipSuccess) {
     t_last_hip = (int)e;
     cr_batch_plan_destroy(p);
@@ -2340,98 +2508,88 @@ int cr_batch_plan_create(const cr_request* reqs, int32_t num, unsigned flags,
 int cr_batch_plan_launch(cr_batch_plan* plan, void* stream) {
   if (!plan) return CR_E_NULL;
   hipStream_t s = (hipStream_t)stream;
-  if (plan->exec) {
-    hipError_t e = hipGraphLaunch(plan->exec, s);
+  if (!plan->tables.reqs.empty()) {
+    hipError_t e = hipSuccess;
+    if (plan->exec)
+      e = hipGraphLaunch(plan->exec, s);
+    else
+      e = launch_batch(plan->d_reqs, plan->d_tile_req, plan->tables, plan->per, plan->stats,
+                       plan->flags, s);
     if (e == hipSuccess) e = hipEventRecord(plan->done, s);
     if (e != hipSuccess) return hip_fail(e);
     plan->launched = true;
-    g_elems[plan->device] += plan->elems;
+    g_elems[plan->device] += plan->tables.elems;
   }
   return CR_OK;
 }
 
-int cr_batch_plan_destroy(cr_batch_plan* plan) {
-  if (!plan) return CR_OK;
-  if (plan->launched && plan->done) (void)hipEventSynchronize(plan->done);
-  if (plan->exec) (void)hipGraphExecDestroy(plan->exec);
-  if (plan->done) (void)hipEventDestroy(plan->done);
-  if (plan->d_reqs) (void)hipFree(plan->d_reqs);
-  if (plan->d_tiles) (void)hipFree(plan->d_tiles);
-  delete plan;
+// The batch by kernel arguments or, for larger ones, by tables copied to device
+// memory at dr and dt; the host vectors are freed on return, so the call waits until
+// the copies have read them.
+static int run_batch(const BatchTables& T, bool args, BReq* dr, unsigned* dt, DevStats* st,
+                     hipStream_t s) {
+  hipError_t e = hipSuccess;
+  if (args) {
+    e = launch_batch_args(T, st, 0u, s);
+  } else {
+    const int per[2] = {std::max(1, batch_per(T.split_tile, false)),
+                        std::max(1, batch_per((long long)T.tile_req.size() - T.split_tile, true))};
+    e = hipMemcpyAsync(dr, T.reqs.data(), T.reqs.size() * sizeof(BReq), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(dt, T.tile_req.data(), T.tile_req.size() * sizeof(unsigned),
+                         hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = launch_batch(dr, dt, T, per, st, 0u, s);
+  }
+  if (e != hipSuccess) return hip_fail(e);
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  g_elems[dev] += T.elems;
   return CR_OK;
 }
 
 int cr_eval_batch(const cr_request* reqs, int32_t num, void* stream) {
-  std::vector<BReq> hr;
-  std::vector<BTile> ht;
-  long long elems = 0;
-  int rc = build_tables(reqs, num, hr, ht, elems);
+  BatchTables T;
+  int rc = build_tables(reqs, num, T);
   if (rc) return rc;
-  if (ht.empty()) return CR_OK;
+  if (T.reqs.empty()) return CR_OK;
   DevStats* st = nullptr;
   rc = get_stats(&st);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
-  BReq* dr = nullptr;
-  BTile* dt = nullptr;
-  hipError_t e = hipMallocAsync((void**)&dr, hr.size() * sizeof(BReq), s);
-  if (e == hipSuccess) e = hipMallocAsync((void**)&dt, ht.size() * sizeof(BTile), s);
+  if (by_args(T, s)) return run_batch(T, true, nullptr, nullptr, st, s);
+  // one stream-ordered allocation for both tables
+  const size_t rb = (T.reqs.size() * sizeof(BReq) + 255) / 256 * 256;
+  unsigned char* d = nullptr;
+  hipError_t e = hipMallocAsync((void**)&d, rb + T.tile_req.size() * sizeof(unsigned), s);
   if (e != hipSuccess) {
-    if (dt) (void)hipFreeAsync(dt, s);
-    if (dr) (void)hipFreeAsync(dr, s);
     t_last_hip = (int)e;
     return CR_E_NOMEM;
   }
-  e = hipMemcpyAsync(dr, hr.data(), hr.size() * sizeof(BReq), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(dt, ht.data(), ht.size() * sizeof(BTile), hipMemcpyHostToDevice, s);
-  // the host vectors are freed on return: make sure the copies have read them
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e == hipSuccess) {
-    for (const BRange& g : key_ranges(hr, ht)) (void)launch_tiles(dr, dt, g, st, 0u, s);
-    e = hipGetLastError();
-  }
-  (void)hipFreeAsync(dt, s);
-  (void)hipFreeAsync(dr, s);
-  if (e != hipSuccess) return hip_fail(e);
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  g_elems[dev] += elems;
-  return CR_OK;
+  rc = run_batch(T, false, (BReq*)d, (unsigned*)(d + rb), st, s);
+  (void)hipFreeAsync(d, s);
+  return rc;
 }
 
 int cr_eval_batch_noalloc(const cr_request* reqs, int32_t num, void* stream) {
   if (num > CR_NOALLOC_MAX_REQUESTS) return CR_E_SCRATCH;
-  std::vector<BReq> hr;
-  std::vector<BTile> ht;
-  long long elems = 0;
-  int rc = build_tables(reqs, num, hr, ht, elems);
+  BatchTables T;
+  int rc = build_tables(reqs, num, T);
   if (rc) return rc;
-  if (ht.empty()) return CR_OK;
-  if (hr.size() > (size_t)CR_NOALLOC_MAX_REQUESTS || ht.size() > (size_t)CR_NOALLOC_MAX_TILES)
+  if (T.reqs.empty()) return CR_OK;
+  // the limit counts tiles of 4096 elements, whatever tiles the batch is cut into
+  size_t tiles = 0;
+  for (const BReq& r : T.reqs) tiles += ((size_t)r.n + TILE - 1) / TILE;
+  if (tiles > (size_t)CR_NOALLOC_MAX_TILES || T.tile_req.size() > (size_t)CR_NOALLOC_MAX_TILES)
     return CR_E_SCRATCH;
   DevState* ds = nullptr;
   rc = get_state(&ds);
   if (rc) return rc;
-  BReq* dr = reinterpret_cast<BReq*>(ds->scratch);
-  BTile* dt = reinterpret_cast<BTile*>(ds->scratch + NOALLOC_REQ_BYTES);
   hipStream_t s = (hipStream_t)stream;
-  // stream-ordered after earlier work on s (including an earlier call's
-  // kernels still reading the tables); the host vectors are freed on return,
-  // so wait until the copies have read them
-  hipError_t e = hipMemcpyAsync(dr, hr.data(), hr.size() * sizeof(BReq), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(dt, ht.data(), ht.size() * sizeof(BTile), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e == hipSuccess) {
-    for (const BRange& g : key_ranges(hr, ht)) (void)launch_tiles(dr, dt, g, ds->stats, 0u, s);
-    e = hipGetLastError();
-  }
-  if (e != hipSuccess) return hip_fail(e);
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  g_elems[dev] += elems;
-  return CR_OK;
+  // stream-ordered after earlier work on s (including an earlier call's kernels
+  // still reading the tables)
+  return run_batch(T, by_args(T, s), reinterpret_cast<BReq*>(ds->scratch),
+                   reinterpret_cast<unsigned*>(ds->scratch + NOALLOC_REQ_BYTES), ds->stats, s);
 }
 
 int cr_stats_reset(void* stream) {

@@ -59,7 +59,7 @@ REF_IDS = {"0": "HIP expf", "4": "HIP logf", "11": "HIP sincosf", "64": "HIP exp
 
 def short(name):
     """k_map_f32<OpLog<3>> (log1pf) style names for the library's kernels."""
-    name = name.replace("(anonymous namespace)::", "")
+    name = name.replace("(anonymous namespace)::", "").replace("BOne<", "").replace("BTwo<", "")
     m = re.match(r"void (k_\w+)<(\w+(?:<\d+>)?)[ ,>]", name)
     if m:
         op = m.group(2)
@@ -195,7 +195,7 @@ def elems_of(kernel, batch):
         return 1 << 26
     if k in ("k_map_f64", "k_complex", "k_ref64"):
         return 1 << 24
-    if k in ("k_tiles", "k_tiles_sincos"):
+    if k == "k_tiles":
         return batch.get(what.split()[0])
     return None
 
