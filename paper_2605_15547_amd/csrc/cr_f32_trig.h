@@ -318,7 +318,7 @@ __device__ __forceinline__ TrigAcc trig_acc_core(float xf, const TrigTab& tb) {
   bool small = axd < PI64;
   Reduced R = payne_hanek(ax, tb.w);
   double d1 = (double)(R.fhi >> 11) * 0x1p-53;
-  double d2 = (double)(((uint64_t)(R.fhi & 0x7ff) << 42) | (R.flo >> 22)) * 0x1p-117;
+  double d2 = (double)(((uint64_t)(R.fhi & 0x7ff) << 42) | (R.flo >> 22)) * 0x1p-106;
   double d3 = (double)(R.flo & 0x3fffff) * 0x1p-128;
   dd f = dd_add_d(fast_two_sum(d1, d2), d3);
   dd r = dd_mul(f, dd{PI32_HI, PI32_MID});
