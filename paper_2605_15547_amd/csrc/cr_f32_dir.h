@@ -263,9 +263,7 @@ __device__ __noinline__ AccResult rsqrt_dir(float xf) {
 }
 
 // ------------------------------------------------------------------- trig
-// Fast path.  sin and cos: below 512 ulps for results of at least 2^-12
-// (round_trig_fast); tan: the absolute bound of tan_value_fast, both ends
-// truncated.  |x| < 2^-12: sin x lies below x in magnitude and tan x above it, by
+// Fast path, within 512 ulps (round_trig_fast).  |x| < 2^-12: sin x lies below x in magnitude and tan x above it, by
 // less than 2^-25.5 |x|, and cos x below 1 by less than 2^-25, on this side of
 // the next binary32 number.
 template <int KIND, int RM>
@@ -278,7 +276,7 @@ __device__ __forceinline__ bool trig_special_dir(float xf, float& res) {
 }
 template <int RM>
 __device__ __forceinline__ float trig_round_dir(double y, bool& ok) {
-  ok = dir_certain<512>(y) && fabs(y) >= 0x1p-12;
+  ok = dir_certain<TRIG_TEST_E>(y);
   return dir_round<RM, false>(y);
 }
 template <int KIND, int RM>
@@ -291,10 +289,7 @@ __device__ __forceinline__ float trig_fast_dir(float xf, const TrigTab& tb, bool
   } else if (KIND == TRIGK_SIN) {
     r = trig_round_dir<RM>(flip(F.s, F.ss ^ xs), ok);
   } else {
-    double e;
-    const double t = flip(tan_value_fast(F, e), F.ss ^ F.sc ^ xs);
-    ok = f32_bits(f32_trunc(t - e)) == f32_bits(f32_trunc(t + e));
-    r = dir_round<RM, false>(t);
+    r = trig_round_dir<RM>(flip(div_fast(F.s, F.c), F.ss ^ F.sc ^ xs), ok);
   }
   float v;
   const bool sp = trig_special_dir<KIND, RM>(xf, v);

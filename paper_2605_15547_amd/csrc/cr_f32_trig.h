@@ -1,10 +1,17 @@
 // cr_f32_trig.h -- correctly rounded sinf, cosf, sincosf, tanf (device).
 //
 // Paper, Sec. II-A: the trigonometric kernels branch only for large-argument
-// reduction.  On the GPU every lane runs the same reduction, branch-free:
-// Payne-Hanek (Payne and Hanek, SIGNUM Newsletter 18(1), 1983) in 32-bit
-// integer arithmetic for every |x| >= pi/64.
+// reduction.  Here every lane runs the same reduction, branch-free, whatever the
+// size of its argument: N = x 32/pi, k = nearest(N), f = N - k in [-1/2, 1/2],
+// r = f pi/32, |r| <= pi/64, and q = k mod 64.
 //
+// Fast path: binary64, with the idea of Payne and Hanek (SIGNUM Newsletter 18(1),
+// 1983) that the leading bits of 32/pi only add multiples of 64 to N: they are
+// dropped from a constant chosen by the argument's exponent (16 rows for groups of
+// 8 exponents), whose first two 29-bit parts give exact products with the 24-bit
+// argument (trig_fast_core).
+//
+// Accurate path: Payne-Hanek in 32-bit integer arithmetic.
 //   x = M 2^E (M a 24-bit integer).  N = x 32/pi = M 2^(E+4) sum_i g_i 2^-i
 //   with g_i the bits of 2/pi.  Bits with i <= E - 2 only add multiples of 64
 //   to N, so a 160-bit window W of 2/pi starting at bit E - 1 suffices:
@@ -14,8 +21,6 @@
 //   154.  The zero words let the window start before the binary point, so the
 //   reduction is also right for small arguments (down to 2^-37).
 //
-//   k = nearest(N), q = k mod 64, f = N - k in [-1/2, 1/2) (64 fraction bits
-//   for the fast path, 128 for the accurate path), r = f pi/32, |r| <= pi/64.
 //   With theta = q pi/32 = quad pi/2 + j pi/32 (j = q mod 16), a 16-entry table
 //   gives sin and cos of j pi/32 (double-double); quadrant symmetries give
 //   sin/cos theta, and
@@ -33,11 +38,15 @@ enum { TRIGK_SIN = 0, TRIGK_COS = 1, TRIGK_TAN = 2, TRIGK_SINCOS = 3 };
 
 struct TrigTab {
   double4 sc[16];
+  double4 red[16];
   unsigned w[11];
 };
 
 __device__ __forceinline__ void trig_tab_load(TrigTab& t, int tid) {
-  if (tid < 16) t.sc[tid] = SINCOS_T[tid];
+  if (tid < 16) {
+    t.sc[tid] = SINCOS_T[tid];
+    t.red[tid] = TRIG_RED[tid];
+  }
   if (tid < 11) t.w[tid] = TWO_OVER_PI_W[tid];
 }
 
@@ -101,39 +110,6 @@ __device__ __forceinline__ Reduced payne_hanek(uint32_t ax, const unsigned* w) {
   return R;
 }
 
-// The fast path's form of the same reduction: only the 96 leading bits of the
-// window (W0, W1, W2), so P' = M (W >> 64) takes three multiply-adds instead
-// of five.  P' is bits 64.. of P less the carry of M (W mod 2^64) < 2^88 out
-// of the dropped low part, i.e. less than 2^-66 in units of N; the 64
-// fraction bits of f (bits 153..90 of P) come out low by at most one unit of
-// 2^-64 (the high word R.fhi only; R.flo is not formed).
-__device__ __forceinline__ Reduced payne_hanek_fast(uint32_t ax, const unsigned* w) {
-  // the window of payne_hanek from the exponent field directly: with the
-  // field clamped below at 90 (E = field - 150 >= -60; the field is at most
-  // 255, so the upper clamp never applies), the window starts at
-  // sp = field - 88, so b = ((field - 57) >> 5) - 1 and c = (88 - field) mod 32
-  const int fe = max((int)(ax >> 23), 90);
-  const Window win = {((fe - 57) >> 5) - 1, (unsigned)(88 - fe)};  // c: low 5 bits used
-  uint32_t M = (ax & 0x007fffffu) | 0x00800000u;
-  const unsigned* t = w + win.b;
-  uint32_t W0 = window_word(t[0], t[1], win.c);
-  uint32_t W1 = window_word(t[1], t[2], win.c);
-  uint32_t W2 = window_word(t[2], t[3], win.c);
-  uint64_t a = (uint64_t)M * W2;
-  uint32_t p2 = (uint32_t)a;
-  a = (uint64_t)M * W1 + (a >> 32);
-  uint32_t p3 = (uint32_t)a;
-  a = (uint64_t)M * W0 + (a >> 32);
-  uint32_t p4 = (uint32_t)a;
-  Reduced R;
-  // k mod 64 = (bits 159..153 of P, plus 1) >> 1: the same as (p4 + 2^25) >> 26,
-  // where a carry out of bit 31 would only add 64
-  R.q = (int)((p4 + 0x02000000u) >> 26);
-  R.fhi = (long long)(((uint64_t)funnel(p4, p3, 26) << 32) | funnel(p3, p2, 26));
-  R.flo = 0;
-  return R;
-}
-
 // sin/cos of theta = q pi/32 as double-doubles, from the table and the quadrant
 struct SinCosTheta {
   double sh, sl, ch, cl;
@@ -190,54 +166,43 @@ __device__ __forceinline__ double flip(double v, uint32_t m) {
   return __hiloint2double(__double2hiint(v) ^ (int)(m & 0x80000000u), __double2loint(v));
 }
 
-// Fast path: binary64 sin and cos of |x| up to the quadrant's signs, with
-// absolute error bounds: sin |x| is s with its sign flipped by the mask ss
-// (bit 31), cos |x| is c flipped by sc.
+// Fast path: binary64 sin and cos of |x| up to the quadrant's signs: sin |x| is s
+// with its sign flipped by the mask ss (bit 31), cos |x| is c flipped by sc.
 struct TrigFast {
-  double s, c, es, ec;  // values and error bounds
-  uint32_t ss, sc;      // sign masks
+  double s, c;
+  uint32_t ss, sc;  // sign masks
 };
 
+// Bound by VALU issue.  The reduction takes 8 binary64 operations and two LDS reads
+// for every argument; it replaced an integer Payne-Hanek reduction on 96 bits of 2/pi
+// (three 64-bit multiply-adds, five funnel shifts, two conversions) with a branch to a
+// three-part Cody-Waite form for waves whose arguments all lay below 2^23 (14
+// operations), each with an absolute error that sent results below 2^-12 to the
+// accurate path.  Measured at 2^24 elements, arguments of every magnitude: sinf 47.6 ->
+// 37.5 us, cosf 48.4 -> 38.7, tanf 56.1 -> 44.3, sincosf 58.8 -> 50.2; in (0.05, 0.95):
+// sinf 34.2 -> 31.2, tanf 42.0 -> 34.9, sincosf 42.0 -> 38.8.
 __device__ __forceinline__ TrigFast trig_fast_core(float xf, const TrigTab& tb) {
-  uint32_t ax = f32_bits(xf) & 0x7fffffffu;
-  double axd = (double)bits_f32(ax);
-  double r;
-  int q;
-  // The one branch of the method is on the size of the argument (the paper
-  // keeps Payne-Hanek for large arguments only): when every lane of the wave
-  // has |x| < 2^23, the wave takes a Cody-Waite reduction in binary64
-  // instead, k = nearest(|x| 32/pi) (|k| < 2^26.4), r = ((|x| - k C1) - k C2)
-  // - k C3 with C1 on 26 bits (k C1 exact, and |x| - k C1 exact: a multiple
-  // of 2^-29 below 2^-4) and k C2 as an exact product: r within
-  // 2^-53 |r| + 2^-105 of |x| - k pi/32 (the final addition's rounding and
-  // the terms below 2^-57), inside the bound below; for |x| < pi/64, k = 0
-  // and r = |x| exactly.  The branch is wave-uniform, so it costs no
-  // divergence; the result is certified by the same test either way, so it
-  // does not depend on which branch runs.  Payne-Hanek is right down to
-  // |x| = 2^-37; smaller arguments are special cases (|x| < 2^-12).
-  if (__all(ax < 0x4b000000u)) {
-    const double kd = rint(axd * INV_PI32);
-    const double r1 = fma(-kd, PI32_CW1, axd);
-    const dd p = two_prod(kd, PI32_CW2);
-    const dd t = two_sum(r1, -p.hi);
-    r = t.hi + (fma(-kd, PI32_CW3, t.lo) - p.lo);
-    q = (int)kd & 63;
-  } else {
-    Reduced R = payne_hanek_fast(ax, tb.w);
-    // f = fhi 2^-64 (the reduction leaves it low by less than 2^-64; the bits
-    // below are not formed), as the exact sum of its signed high and
-    // unsigned low 32-bit halves; their weights 2^-32 and 2^-64 are folded
-    // into the constants (exact scalings)
-    double fh = (double)(int)(R.fhi >> 32);
-    double fl = (double)(uint32_t)R.fhi;
-    r = fma(fh, PI32_HI * 0x1p-32, fma(fh, PI32_MID * 0x1p-32, fl * (PI32_HI * 0x1p-64)));
-    q = R.q;
-  }
-  double r2 = r * r;
-  double ps = fma(fma(SIN_S2[2], r2, SIN_S2[1]), r2, SIN_S2[0]);
-  double pc = fma(fma(COS_C2[2], r2, COS_C2[1]), r2, COS_C2[0]);
-  double sr = fma(r * r2, ps, r);  // sin r
-  double cm1 = r2 * pc;            // cos r - 1
+  const uint32_t ax = f32_bits(xf) & 0x7fffffffu;
+  const double a = (double)bits_f32(ax);
+  // Row g of the table serves |x| in [2^(8g+1), 2^(8g+9)), row 0 all smaller
+  // arguments too (the exponent field is at most 255: g <= 15).  With c1 + c2 + c3 =
+  // 32/pi less the bits that only add multiples of 64 to N:
+  //  * a c1 < 2^37 is an exact product (24 + 29 bits), a multiple of 2^-23, and a c2 <
+  //    2^8 is exact too; their sum is rounded by at most 2^-17, and adding 1.5 2^52
+  //    rounds it to the integer k, whose low bits are the low word of t;
+  //  * a c1 - k is exact (below 2^8 + 1 in magnitude, a multiple of 2^-23);
+  //  * f = (a c1 - k) + a c2 + a c3, |f| <= 1/2 + 2^-17, carries two roundings
+  //    relative to the sums themselves and the rounding of c3 times a: f is within
+  //    2^-52 |f| + 2^-74 of N - k (mod 64).
+  const double4& w = tb.red[max(ax >> 26, 16u) - 16u];
+  const double p2 = a * w.y;
+  const double t = fma(a, w.x, p2) + 0x1.8p52;
+  const double f = fma(a, w.z, fma(a, w.x, -(t - 0x1.8p52)) + p2);
+  const uint32_t q = (uint32_t)__double2loint(t);  // bits 0..5 are used
+  // r = f pi/32; the polynomials are in f
+  const double f2 = f * f;
+  const double sr = f * fma(fma(fma(SIN_F[3], f2, SIN_F[2]), f2, SIN_F[1]), f2, SIN_F[0]);  // sin r
+  const double cm1 = f2 * fma(fma(COS_F[2], f2, COS_F[1]), f2, COS_F[0]);  // cos r - 1
   // theta = q pi/32 = quad pi/2 + j pi/32, with T1, T2 = sin, cos of j pi/32
   // (the high parts of table row j) swapped in odd quadrants: an offset of
   // the two reads, from bit 4 of q.  Then
@@ -246,44 +211,39 @@ __device__ __forceinline__ TrigFast trig_fast_core(float xf, const TrigTab& tb) 
   // with sr' = sin r negated in odd quadrants and the outer signs given by
   // bit 5 of q (sin) and bit 4 xor bit 5 (cos).
   const double* row = reinterpret_cast<const double*>(&tb.sc[q & 15]);
-  const int sw = (q >> 3) & 2;
+  const uint32_t sw = (q >> 3) & 2;
   const double T1 = row[sw], T2 = row[sw ^ 2];
-  const uint32_t q32 = (uint32_t)q;
-  const double srq = flip(sr, q32 << 27);
+  const double srq = flip(sr, q << 27);
   TrigFast o;
   o.s = T1 + fma(T1, cm1, T2 * srq);
   o.c = T2 + fma(T2, cm1, -(T1 * srq));
-  o.ss = q32 << 26;
-  o.sc = (q32 ^ (q32 << 1)) << 26;
-  // Error bounds, absolute: r within 2^-52 |r| + 2^-66.35 (reduction, f to
-  // 2^-63 in units of N; exact when the Cody-Waite branch has k = 0); the
-  // degree-2 corrections within 2^-50.1 (cos) and 2^-57.6 (sin) -- the bound
-  // tests re-derive both; the table entries within 2^-54 each; three
-  // roundings of terms below 0.05 and the final one of y.  With |sin x|,
-  // |cos x| >= 0.049 unless j = 0 this is below 2^-49.95 absolute, i.e.
-  // 2^-45.6 |y|.  For j = 0 the table terms are exactly 0 and 1 and y is
-  // +-sin r (within 2^-57.6 + 2^-51.9 |y| + 2^-66.35) or +-cos r (within
-  // 2^-50.1, |y| > 0.99).  Bound used: 2^-45 |y| + 2^-57.
-  o.es = fma(fabs(o.s), 0x1p-45, 0x1p-57);
-  o.ec = fma(fabs(o.c), 0x1p-45, 0x1p-57);
+  o.ss = q << 26;
+  o.sc = (q ^ (q << 1)) << 26;
+  // Errors: sin r within 2^-50.8 |r| + 2^-77 (the reduction, pi/32 to 2^-54, the
+  // polynomial's last addition and the product; its approximation and its other
+  // coefficients far below), cos r - 1 within 2^-56 (the bound tests re-derive both
+  // approximation errors); the table entries within 2^-54 each; three roundings of
+  // terms below 0.05 and the final one of y.  With |sin x|, |cos x| >= 0.049 unless
+  // j = 0 this is below 2^-52 absolute, i.e. 2^-47 |y|.  For j = 0 the table terms are
+  // exactly 0 and 1 and y is +-sin r or +-cos r; no binary32 x lies closer than
+  // 2^-30 to a multiple of pi/2, other than below pi/64 itself, so sin r is within
+  // 2^-46 |y| there.  Bound used: 2^-45 |y|.
   return o;
 }
 
 // bit 31 set when x is negative
 __device__ __forceinline__ uint32_t sign_mask(float xf) { return f32_bits(xf); }
 
-// The rounding test of the sin and cos fast paths, read off the bits of yh:
-// for |yh| >= 2^-12 the bound above is below 2^-44 |yh| (the absolute term is
-// then below 2^-45 |yh|), i.e. below 512 ulps of yh (ulps of 2^-53 |yh| and
-// up), so a binary32 midpoint can lie within the error only when the 29 low
-// bits of yh come within 512 of the midpoint pattern 2^28 (cr_round.h,
-// round_f32_bits).  Results below 2^-12 in magnitude (x within about 2^-12 of
-// a zero of sin or cos: about 1.5 10^-4 of random arguments) go to the
-// accurate path.
+// The rounding test of the sin and cos fast paths, read off the bits of yh: the bound
+// above is below 256 ulps of yh (ulps of 2^-53 |yh| and up), below 512 when yh falls
+// just below a power of two, so a binary32 midpoint can lie within the error only when
+// the 29 low bits of yh come within 512 of the midpoint pattern 2^28 (cr_round.h,
+// round_f32_bits).  All results are normal numbers (tiny arguments are special cases).
+// tan x, a quotient of two such values within 2^-52 (div_fast), is within 2^-43.99 of
+// its value: the same test.
+constexpr unsigned TRIG_TEST_E = 512;
 __device__ __forceinline__ float round_trig_fast(double yh, bool& ok) {
-  float r = round_f32_bits<512>(yh, ok);
-  ok = ok && fabs(yh) >= 0x1p-12;
-  return r;
+  return round_f32_bits<TRIG_TEST_E>(yh, ok);
 }
 
 // ------------------------------------------------------------ accurate path
@@ -405,18 +365,6 @@ __device__ __noinline__ AccResult2 sincos_accurate(float xf, const TrigTab& tb) 
   return {rs, rc, (ok1 && ok2) ? 1 : 0};
 }
 
-// tan |x| up to its sign, and an absolute error bound: t = s / c from the
-// hardware reciprocal and two corrections by exact residuals (each squares the
-// relative error of the estimate), within 2^-52 |t|; then the absolute errors
-// of s and c magnified by 1/|c|:
-// |dt| <= |t| 2^-52 + (es + |t| ec) / |c| (bound with margins)
-__device__ __forceinline__ double tan_value_fast(const TrigFast& F, double& e) {
-  const double t = div_fast(F.s, F.c);
-  const double ic = __builtin_amdgcn_rcp(F.c);
-  e = fma(fabs(t), 0x1p-50, (F.es + fabs(t) * F.ec) * fabs(ic) * 2.0);
-  return t;
-}
-
 template <int KIND>
 __device__ __forceinline__ float trig_fast(float xf, const TrigTab& tb, bool& ok) {
   TrigFast F = trig_fast_core(xf, tb);
@@ -427,9 +375,7 @@ __device__ __forceinline__ float trig_fast(float xf, const TrigTab& tb, bool& ok
   } else if (KIND == TRIGK_SIN) {
     res = round_trig_fast(flip(F.s, F.ss ^ xs), ok);
   } else {
-    double e;
-    const double t = tan_value_fast(F, e);
-    res = round_f32_fast_abs(flip(t, F.ss ^ F.sc ^ xs), e, ok);
+    res = round_trig_fast(flip(div_fast(F.s, F.c), F.ss ^ F.sc ^ xs), ok);
   }
   float sp;
   if (trig_special_fast(xf, sp, KIND)) {

@@ -72,14 +72,6 @@ __device__ __forceinline__ float round_f32_bits(double yh, bool& ok) {
   return (float)yh;
 }
 
-// Same, with an absolute error bound instead of a count of ulps.
-__device__ __forceinline__ float round_f32_fast_abs(double yh, double err, bool& ok) {
-  float a = (float)(yh - err);
-  float b = (float)(yh + err);
-  ok = a == b;
-  return b;
-}
-
 // Round-to-odd of h + l into binary64, given h = RN(h + l).
 __device__ __forceinline__ double ro53(double h, double l) {
   long long b = __double_as_longlong(h);

@@ -325,18 +325,26 @@ def gen_trig():
     emit_const("PI32_MID", m1)
     emit_const("PI32_LO", l)
     emit_const("PI64", d(mp.pi / 64), "pi/64 (small-argument threshold)")
-    # Cody-Waite form of the reduction for |x| < 2^23 (|k| < 2^26.4): pi/32 in
-    # three parts, the first on 26 bits so that k CW1 is exact
+    # the fast path's reduction: row g serves |x| in [2^(8g+1), 2^(8g+9)) (row 0 all
+    # smaller ones too).  Such x are multiples of 2^(8g-22), so the bits of 32/pi of
+    # weight 2^(28-8g) and up add multiples of 64 to x 32/pi and are dropped; the
+    # rest in three parts, 29 bits, 29 bits and one rounded double: x c1 and x c2
+    # are exact for a 24-bit x
+    emit("// 32/pi less the multiples of 2^(28-8g), for |x| in [2^(8g+1), 2^(8g+9)) (g = 0: below too):")
+    emit("// {29 bits, the next 29 bits, the rest rounded, 0}")
+    emit("__device__ __constant__ const double4 TRIG_RED[16] = {")
     with mp.workprec(800):
-        c = mp.pi / 32
-        c1 = split_bits(c, 26)
-        rem = c - mp.mpf(c1)
-        c2 = float(rem)
-        c3 = float(rem - mp.mpf(c2))
-    emit_const("PI32_CW1", c1, "pi/32 rounded to 26 bits")
-    emit_const("PI32_CW2", c2)
-    emit_const("PI32_CW3", c3)
-    emit_const("INV_PI32", d(32 / mp.pi), "32/pi")
+        for g in range(16):
+            v = mp.fmod(32 / mp.pi, mp.mpf(2) ** (28 - 8 * g))
+            parts = []
+            for lsb in (-1 - 8 * g, -30 - 8 * g):
+                q = mp.mpf(2) ** lsb
+                p = mp.floor(v / q) * q
+                parts.append(float(p))
+                v -= p
+            parts.append(float(v))
+            emit("  {%s, %s, %s, 0.0}," % tuple(hexd(p) for p in parts))
+    emit("};")
     emit("// sin(j pi/32), cos(j pi/32) for j = 0..15, double-double: {s_hi, s_lo, c_hi, c_lo}")
     emit("__device__ __constant__ const double4 SINCOS_T[16] = {")
     for j in range(16):
@@ -361,6 +369,14 @@ def gen_trig():
              % ("sin r = r + r^3 S2(r^2)" if name == "SIN_S2" else "cos r - 1 = r^2 C2(r^2)",
                 log2_of(bound)))
         emit_arr(name, cd, "coefficients (degree 2 in r^2)")
+        # the same in f = r 32/pi: sin r = f (F0 + F1 f^2 + ...), cos r - 1 = f^2 (F0 + ...)
+        p = mp.pi / 32
+        if name == "SIN_S2":
+            emit_arr("SIN_F", [d(p)] + [d(mp.mpf(v) * p ** (2 * k + 3)) for k, v in enumerate(cd)],
+                     "sin r / f in powers of f^2, f = r 32/pi")
+        else:
+            emit_arr("COS_F", [d(mp.mpf(v) * p ** (2 * k + 2)) for k, v in enumerate(cd)],
+                     "(cos r - 1) / f^2 in powers of f^2, f = r 32/pi")
     # accurate path: Taylor coefficients (-1)^k / (2k+1)! and (-1)^k / (2k)!
     N = 9
     emit("#define TRIG_TAYLOR_N %d" % N)
