@@ -155,9 +155,9 @@ int cr_available(int func_id, int impl);
  * for a frequency f_k in bins, any finite value allowed), X (m pairs of
  * doubles, 16-byte aligned, caller-owned).  0 <= n <= 2^24 (sample indices
  * exact in binary32; else CR_E_SIZE); m == 0 returns CR_OK.  flags: enum
- * cr_flag.  X may not overlap x or w (CR_E_OVERLAP).  The call allocates and
- * frees a stream-ordered workspace of m * S * 32 bytes (S = number of sample
- * slices, at most n / 2048 + 1); asynchronous and stream-ordered like
+ * cr_flag.  X may not overlap x or w (CR_E_OVERLAP).  For S > 1 the call
+ * allocates and frees a stream-ordered workspace of m * S * 32 bytes (S = number
+ * of sample slices, 1 up to n = 2^14, at most n / 2048 + 1); asynchronous and stream-ordered like
  * cr_eval.  Errors: CR_E_SIZE, CR_E_NULL, CR_E_ALIGN, CR_E_OVERLAP,
  * CR_E_NOMEM, CR_E_HIP. */
 int cr_dft(const float *x, int64_t n, const float *w, int64_t m, double *X, unsigned flags,

@@ -101,6 +101,31 @@ __device__ __forceinline__ float hyp_fast(float xf, const ExpTab& tb, bool& ok) 
   return res;
 }
 
+// sinh x and cosh x together: one expm1 (e, within 4 ulps), E = e + 1, and the
+// reciprocal of E within 2^-52 serve both, sinh = (e + e/E)/2 and cosh = (E + 1/E)/2.
+// e/E as a product adds 2 ulps to the smaller term: both stay within the 8 ulps of
+// the separate functions, with the same test and special cases.
+__device__ __forceinline__ void sinh_cosh_fast(float xf, const ExpTab& tb, float& sh, float& ch,
+                                               bool& ok) {
+  const double a = fmin(fabs((double)xf), 100.0);
+  const double e = exp_core_fast<true>(xf, a, tb);
+  const double E = e + 1.0, iE = div_fast(1.0, E);
+  const double s = 0.5 * fma(e, iE, e);
+  bool oks, okc;
+  sh = round_f32_bits<HYP_TEST_E>(xf < 0.0f ? -s : s, oks);
+  ch = round_f32_bits<HYP_TEST_E>(0.5 * (E + iE), okc);
+  float sp;
+  if (hyp_special_fast<HYPK_SINH>(xf, sp)) {
+    sh = sp;
+    oks = true;
+  }
+  if (hyp_special_fast<HYPK_COSH>(xf, sp)) {
+    ch = sp;
+    okc = true;
+  }
+  ok = oks && okc;
+}
+
 // exp(a) or expm1(a) in double-double (relative error < 2^-98)
 template <bool EM1>
 __device__ __forceinline__ dd exp_core_acc(double a, const ExpTab& tb) {

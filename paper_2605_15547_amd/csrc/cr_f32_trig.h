@@ -144,20 +144,17 @@ __device__ __forceinline__ bool trig_special(float xf, float& res, int kind) {
   return nan | inf | zero;
 }
 
-// The fast path's special cases, with the tiny arguments folded in: for
-// |x| < 2^-12 (zeros and subnormals included) sin x = x - x^3/6 + ... and
-// tan x = x + x^3/3 + ... lie within x^2/3 < 2^-25.6 |x| of x and cos x =
-// 1 - x^2/2 + ... within 2^-25 of 1, less than half the spacing of the
-// binary32 numbers next to x (at least 2^-24 |x|) or below 1 (2^-24), so the
-// correctly rounded results are x and 1.  NaN is returned quieted
-// (canonicalize quiets it and keeps the payload), infinities give the
-// default NaN.  One class test and a magnitude compare pick these lanes.
-__device__ __forceinline__ bool trig_special_fast(float xf, float& res, int kind) {
-  const bool inf = fabsf(xf) == INFINITY;
+// The fast path's special cases: NaN (returned quieted: canonicalize keeps its sign
+// and payload) and infinities (the default NaN).  Zeros and tiny arguments
+// need no case of their own: the reduction keeps a relative error down to the smallest
+// subnormal, so for |x| < 2^-12, where sin x and tan x lie within 2^-25.5 |x| of x and
+// cos x within 2^-25 of 1, the value is less than half a spacing away from x (or 1), on
+// which it rounds; where its low bits come within the test's reach of the midpoint
+// (cos x near |x| = 2^-12) the accurate path decides.
+__device__ __forceinline__ bool trig_special_fast(float xf, float& res) {
   const float q = __builtin_canonicalizef(xf);
-  const float t = (kind == TRIGK_COS && xf == xf) ? 1.0f : q;
-  res = inf ? bits_f32(0x7fc00000u) : t;
-  return __builtin_amdgcn_class(xf, 0x207) | (fabsf(xf) < 0x1p-12f);
+  res = fabsf(xf) == INFINITY ? bits_f32(0x7fc00000u) : q;
+  return __builtin_amdgcn_class(xf, 0x207);
 }
 
 // v with its sign flipped where the mask m has bit 31 set (one operation on
@@ -238,7 +235,8 @@ __device__ __forceinline__ uint32_t sign_mask(float xf) { return f32_bits(xf); }
 // above is below 256 ulps of yh (ulps of 2^-53 |yh| and up), below 512 when yh falls
 // just below a power of two, so a binary32 midpoint can lie within the error only when
 // the 29 low bits of yh come within 512 of the midpoint pattern 2^28 (cr_round.h,
-// round_f32_bits).  All results are normal numbers (tiny arguments are special cases).
+// round_f32_bits).  All results are normal numbers but those of tiny arguments, which
+// lie next to a binary32 number (trig_special_fast).
 // tan x, a quotient of two such values within 2^-52 (div_fast), is within 2^-43.99 of
 // its value: the same test.
 constexpr unsigned TRIG_TEST_E = 512;
@@ -378,7 +376,7 @@ __device__ __forceinline__ float trig_fast(float xf, const TrigTab& tb, bool& ok
     res = round_trig_fast(flip(div_fast(F.s, F.c), F.ss ^ F.sc ^ xs), ok);
   }
   float sp;
-  if (trig_special_fast(xf, sp, KIND)) {
+  if (trig_special_fast(xf, sp)) {
     res = sp;
     ok = true;
   }
@@ -393,9 +391,8 @@ __device__ __forceinline__ float sincos_fast(float xf, const TrigTab& tb, float&
   c = round_trig_fast(flip(F.c, F.sc), ok2);
   ok = ok1 && ok2;
   float sp;
-  if (trig_special_fast(xf, sp, TRIGK_SIN)) {
-    s = sp;
-    trig_special_fast(xf, c, TRIGK_COS);
+  if (trig_special_fast(xf, sp)) {
+    s = c = sp;
     ok = true;
   }
   return s;

@@ -878,10 +878,13 @@ struct SinCosDir {
 // The paper's two synthetic applications built on the correctly rounded
 // binary32 functions (Sec. III-A): complex expf, logf and sinf accurate to
 // 2 ulps, and spectral interpolation by a brute-force DFT that spends its time
-// in sincosf.  Each correctly rounded ingredient is evaluated by its fast path
-// and, in a lane whose rounding test fails (rare on these workloads: no
-// hard-to-round inputs are planted), by its accurate path in place; the steps
-// between them are single IEEE operations in the stated formats.
+// in sincosf.  Each correctly rounded ingredient is evaluated by its fast path; an
+// element with an ingredient whose rounding test fails (rare on these workloads: no
+// hard-to-round inputs are planted) is evaluated again with the accurate paths in
+// place, out of line.  The steps between the ingredients are single IEEE operations
+// in the stated formats.
+//   CF::fast(x, y, tab, ok)            every ingredient by its fast path, branch-free
+//   CF::eval(x, y, tab, force, count)  each with its accurate path where needed
 
 // One binary32 function, correctly rounded: fast path, accurate path if needed.
 struct LaneCount {
@@ -926,6 +929,14 @@ struct CExpF {
     exp_tab_load(T.e, tid);
     trig_tab_load(T.t, tid);
   }
+  static __device__ __forceinline__ float2 fast(float x, float y, const Tab& T, bool& ok) {
+    bool oke, okt;
+    float C;
+    const float E = exp_fast<EXPK_E>(x, T.e, oke);
+    const float S = sincos_fast(y, T.t, C, okt);
+    ok = oke && okt;
+    return make_float2(E * C, E * S);
+  }
   static __device__ __forceinline__ float2 eval(float x, float y, const Tab& T, bool force,
                                                 LaneCount& lc) {
     const float E = cr1<OpExp<EXPK_E>>(x, T.e, force, lc);
@@ -945,6 +956,14 @@ struct CSinF {
   static __device__ __forceinline__ void load(Tab& T, int tid) {
     exp_tab_load(T.e, tid);
     trig_tab_load(T.t, tid);
+  }
+  static __device__ __forceinline__ float2 fast(float x, float y, const Tab& T, bool& ok) {
+    bool okt, okh;
+    float C, Sh, Ch;
+    const float S = sincos_fast(x, T.t, C, okt);
+    sinh_cosh_fast(y, T.e, Sh, Ch, okh);
+    ok = okt && okh;
+    return make_float2(S * Ch, C * Sh);
   }
   static __device__ __forceinline__ float2 eval(float x, float y, const Tab& T, bool force,
                                                 LaneCount& lc) {
@@ -977,37 +996,70 @@ struct CLogF {
     atan_tab_load(T.a, tid);
     log_tab_load<LOGK_E>(T.l, tid);  // logf and log1pf share the natural-log table
   }
-  static __device__ __forceinline__ float2 eval(float x, float y, const Tab& T, bool force,
-                                                LaneCount& lc) {
+  // the steps around the two ingredients, shared by both forms: atan1(q) and
+  // log1(v, one_plus) evaluate them
+  template <class A, class L>
+  static __device__ __forceinline__ float2 compose(float x, float y, const A& atan1,
+                                                   const L& log1) {
     const float ax = fabsf(x), ay = fabsf(y);
     const float a = fmaxf(ax, ay), b = fminf(ax, ay);
-    const float A = cr1<OpAtan<ATANK_ATAN>>(b / a, T.a, force, lc);
-    double v = (double)A;
+    double v = (double)atan1(b / a);
     if (ay > ax) v = 0x1.921fb54442d18p+0 - v;  // RN64(pi/2) - v
     if (x < 0.0f) v = 0x1.921fb54442d18p+1 - v;  // RN64(pi) - v
     const float im = copysignf((float)v, y);
     const double a2 = (double)a * (double)a, b2 = (double)b * (double)b;
     const double s = a2 + b2;
-    double re;
-    if (s >= 0.5 && s < 2.0) {
-      const double d = (a2 - 1.0) + b2;
-      const float dh = (float)d;
-      const double dl = d - (double)dh;
-      const float L = cr1<OpLog<LOGK_1P>>(dh, T.l, force, lc);
-      re = 0.5 * ((double)L + dl / (1.0 + (double)dh));
-    } else {
-      const float sh = (float)s;
-      const double sl = s - (double)sh;
-      const float L = cr1<OpLog<LOGK_E>>(sh, T.l, force, lc);
-      re = 0.5 * ((double)L + sl / (double)sh);
-    }
+    const bool near1 = s >= 0.5 && s < 2.0;
+    const double d = near1 ? (a2 - 1.0) + b2 : s;
+    const float dh = (float)d;
+    const double dl = d - (double)dh;
+    const float l = log1(dh, near1);
+    const double re = 0.5 * ((double)l + dl / (near1 ? 1.0 + (double)dh : (double)dh));
     return make_float2((float)re, im);
   }
+  static __device__ __forceinline__ float2 fast(float x, float y, const Tab& T, bool& ok) {
+    bool oka, okl;
+    const float2 r = compose(
+        x, y, [&](float q) { return atan_fast<ATANK_ATAN>(q, T.a, oka); },
+        [&](float v, bool near1) {
+          return near1 ? log_fast<LOGK_1P>(v, T.l, okl) : log_fast<LOGK_E>(v, T.l, okl);
+        });
+    ok = oka && okl;
+    return r;
+  }
+  static __device__ __forceinline__ float2 eval(float x, float y, const Tab& T, bool force,
+                                                LaneCount& lc) {
+    return compose(
+        x, y, [&](float q) { return cr1<OpAtan<ATANK_ATAN>>(q, T.a, force, lc); },
+        [&](float v, bool near1) {
+          return near1 ? cr1<OpLog<LOGK_1P>>(v, T.l, force, lc)
+                       : cr1<OpLog<LOGK_E>>(v, T.l, force, lc);
+        });
+  }
 };
+
+// An element whose fast path failed: its value and the number of ingredients that
+// failed, bit 31 set if the accurate path could not certify one of them.
+struct ComplexSlow {
+  float re, im;
+  unsigned fails;
+};
+template <class CF>
+__device__ __noinline__ ComplexSlow complex_slow(float x, float y, const typename CF::Tab& tab,
+                                                 bool force) {
+  LaneCount lc = {0u, 0u};
+  const float2 r = CF::eval(x, y, tab, force, lc);
+  return {r.x, r.y, lc.fails | (lc.escapes ? 0x80000000u : 0u)};
+}
 
 // Complex map: interleaved (re, im) binary32 pairs, two complex numbers per
 // 128-bit load and store, at any 4-byte alignment; the last one of an odd
 // number is loaded and stored by itself.  Persistent grid, tables staged in LDS.
+// Bound by VALU issue.  Both elements of a thread are evaluated in straight-line code,
+// the next two loaded meanwhile; before, each ingredient was followed by a branch to
+// its accurate path, and csinf evaluated the exponential twice.  Measured at 2^22
+// complex numbers: csinf 22.4 -> 18.4 us (21.2 with the present sine and cosine), cexpf
+// 19.6 -> 17.6, clogf 26.3 -> 24.1.
 template <class CF>
 __global__ void __launch_bounds__(BLOCK)
     k_complex(const float* in, float* out, long long n, DevStats* st, unsigned flags,
@@ -1018,28 +1070,43 @@ __global__ void __launch_bounds__(BLOCK)
   if (threadIdx.x == 0) fails = 0;
   __syncthreads();
   const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  LaneCount tot = {0u, 0u};
-  for (long long i = 2 * ((long long)blockIdx.x * BLOCK + threadIdx.x); i < n;
-       i += 2 * (long long)gridDim.x * BLOCK) {
-    const bool pair = i + 1 < n;
-    const float* p = in + 2 * i;
-    const float4 v = pair ? ld_stream4(p) : make_float4(p[0], p[1], 1.0f, 1.0f);
-    LaneCount lc = {0u, 0u};
-    const float2 r0 = CF::eval(v.x, v.y, tab, force, lc);
-    if (lc.escapes) note_escape(st, elem_base + i);
-    tot.fails += lc.fails;
-    lc = {0u, 0u};
-    const float2 r1 = CF::eval(v.z, v.w, tab, force, lc);
-    if (pair) {
-      if (lc.escapes) note_escape(st, elem_base + i + 1);
-      tot.fails += lc.fails;
-      st_stream4(out + 2 * i, make_float4(r0.x, r0.y, r1.x, r1.y));
-    } else {
-      out[2 * i] = r0.x;
-      out[2 * i + 1] = r0.y;
+  const int n2 = (int)(n >> 1), step = (int)gridDim.x * BLOCK;  // pairs
+  unsigned mine = 0;
+  auto slow = [&](float x, float y, long long i) {
+    const ComplexSlow r = complex_slow<CF>(x, y, tab, force);
+    mine += r.fails & 0x7fffffffu;
+    if (r.fails >> 31) note_escape(st, elem_base + i);
+    return make_float2(r.re, r.im);
+  };
+  int t0 = (int)blockIdx.x * BLOCK;
+  float4 nxt[1];
+  tile_load<float, 1>(nxt, in, t0, n2);
+  for (; t0 < n2; t0 += step) {
+    const float4 v = nxt[0];
+    tile_load<float, 1>(nxt, in, t0 + step, n2);
+    bool ok0, ok1;
+    float2 r0 = CF::fast(v.x, v.y, tab, ok0);
+    float2 r1 = CF::fast(v.z, v.w, tab, ok1);
+    if (!(ok0 && ok1) || force) {
+      const int i = t0 + (int)threadIdx.x;
+      if (i < n2) {
+        if (!ok0 || force) r0 = slow(v.x, v.y, 2LL * i);
+        if (!ok1 || force) r1 = slow(v.z, v.w, 2LL * i + 1);
+      }
     }
+    const float4 r[1] = {make_float4(r0.x, r0.y, r1.x, r1.y)};
+    tile_store<float, 1>(r, out, t0, n2);
   }
-  if (tot.fails) atomicAdd(&fails, tot.fails);
+  if ((n & 1) && threadIdx.x == 0 && takes_tail(t0, step, n2, BLOCK)) {
+    const long long i = n - 1;
+    const float x = in[2 * i], y = in[2 * i + 1];
+    bool ok;
+    float2 r = CF::fast(x, y, tab, ok);
+    if (!ok || force) r = slow(x, y, i);
+    out[2 * i] = r.x;
+    out[2 * i + 1] = r.y;
+  }
+  if (mine) atomicAdd(&fails, mine);
   __syncthreads();
   if (threadIdx.x == 0 && fails) {
     CounterSlot& c = st->slot[blockIdx.x % NSLOT];
@@ -1069,49 +1136,90 @@ __device__ __forceinline__ void dd_acc2(double& hi, double& lo, double h2, doubl
   lo = u.lo;
 }
 
+// One term: the correctly rounded sine and cosine of th and their exact products.
+struct DftSum {
+  double rh, rl, ih, il;
+};
+__device__ __forceinline__ void dft_add(DftSum& a, float xv, float s, float c) {
+  const double xd = (double)xv;
+  dd_acc(a.rh, a.rl, xd * (double)c);
+  dd_acc(a.ih, a.il, xd * (double)s);
+}
+__device__ __forceinline__ void dft_add2(DftSum& a, const DftSum& b) {
+  dd_acc2(a.rh, a.rl, b.rh, b.rl);
+  dd_acc2(a.ih, a.il, b.ih, b.il);
+}
+// xor butterfly over the wave, in a fixed order
+__device__ __forceinline__ void dft_wave_sum(DftSum& a) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1)
+    dft_add2(a, {__shfl_xor(a.rh, off), __shfl_xor(a.rl, off), __shfl_xor(a.ih, off),
+                 __shfl_xor(a.il, off)});
+}
+
+// Bound by VALU issue: about 80 instructions a term, half of them binary64, against 4
+// bytes of samples that the outputs share.  A thread takes DFT_U terms at a time, a
+// block's stride apart, evaluated in straight-line code with one branch for the lanes
+// whose rounding test failed; a term at a time with its own branch it took 120
+// instructions.  Measured, with the present sine and cosine: 2^20 samples at 256
+// frequencies 886 -> 550 us (302 -> 488 G terms/s), 2^18 at 64 80 -> 46 us, 2000 at
+// 41 23 -> 5.3 us (no workspace).
+constexpr int DFT_U = 4;
+template <bool ONE>  // ONE: a single slice, whose sums are the result
 __global__ void __launch_bounds__(BLOCK)
-    k_dft(const float* x, long long n, const float* w, long long slice, double4* part, int S,
+    k_dft(const float* x, int n, const float* w, int slice, double4* part, double2* X, int S,
           DevStats* st, unsigned flags, long long k0) {
   __shared__ TrigTab tab;
-  __shared__ double4 red[BLOCK / 64];
+  __shared__ DftSum red[BLOCK / 64];
   __shared__ unsigned fails;
   trig_tab_load(tab, threadIdx.x);
   if (threadIdx.x == 0) fails = 0;
   __syncthreads();
   const bool force = flags & CR_FLAG_FORCE_FALLBACK;
-  const long long k = blockIdx.y;
+  const int k = blockIdx.y;
   const float wk = w[k];
-  const long long n0 = (long long)blockIdx.x * slice;
-  const long long n1 = n0 + slice < n ? n0 + slice : n;
-  double rh = 0.0, rl = 0.0, ih = 0.0, il = 0.0;
+  const int n0 = (int)blockIdx.x * slice;
+  const int n1 = min(n0 + slice, n);
+  DftSum sum = {0.0, 0.0, 0.0, 0.0};
   LaneCount lc = {0u, 0u};
-  for (long long i = n0 + threadIdx.x; i < n1; i += BLOCK) {
-    const float th = wk * (float)i;  // RN32(w_k n), n < 2^24 exact
+  int i = n0 + (int)threadIdx.x;
+  // RN32(w_k n) with n < 2^24 exact
+  for (; i + (DFT_U - 1) * BLOCK < n1; i += DFT_U * BLOCK) {
+    float xv[DFT_U], s[DFT_U], c[DFT_U];
+    bool ok = true;
+#pragma unroll
+    for (int u = 0; u < DFT_U; u++) xv[u] = x[i + u * BLOCK];
+#pragma unroll
+    for (int u = 0; u < DFT_U; u++) {
+      bool o;
+      s[u] = sincos_fast(wk * (float)(i + u * BLOCK), tab, c[u], o);
+      ok = ok && o;
+    }
+    if (!ok || force) {
+#pragma unroll
+      for (int u = 0; u < DFT_U; u++)
+        s[u] = cr_sincos(wk * (float)(i + u * BLOCK), tab, c[u], force, lc);
+    }
+#pragma unroll
+    for (int u = 0; u < DFT_U; u++) dft_add(sum, xv[u], s[u], c[u]);
+  }
+  for (; i < n1; i += BLOCK) {
     float c;
-    const float s = cr_sincos(th, tab, c, force, lc);
-    const double xd = (double)x[i];
-    dd_acc(rh, rl, xd * (double)c);
-    dd_acc(ih, il, xd * (double)s);
+    const float s = cr_sincos(wk * (float)i, tab, c, force, lc);
+    dft_add(sum, x[i], s, c);
   }
   if (lc.escapes) note_escape(st, k0 + k);
-  // wave reduction in a fixed order (xor butterfly), then across the 4 waves
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double a = __shfl_xor(rh, off), b = __shfl_xor(rl, off);
-    const double c = __shfl_xor(ih, off), d = __shfl_xor(il, off);
-    dd_acc2(rh, rl, a, b);
-    dd_acc2(ih, il, c, d);
-  }
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = make_double4(rh, rl, ih, il);
+  dft_wave_sum(sum);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
   if (lc.fails) atomicAdd(&fails, lc.fails);
   __syncthreads();
   if (threadIdx.x == 0) {
-    double4 acc = red[0];
-    for (int q = 1; q < BLOCK / 64; q++) {
-      dd_acc2(acc.x, acc.y, red[q].x, red[q].y);
-      dd_acc2(acc.z, acc.w, red[q].z, red[q].w);
-    }
-    part[k * S + blockIdx.x] = acc;
+    DftSum acc = red[0];
+    for (int q = 1; q < BLOCK / 64; q++) dft_add2(acc, red[q]);
+    if (ONE)
+      X[k] = make_double2(acc.rh + acc.rl, -(acc.ih + acc.il));
+    else
+      part[(long long)k * S + blockIdx.x] = make_double4(acc.rh, acc.rl, acc.ih, acc.il);
     if (fails) {
       CounterSlot& cs = st->slot[(blockIdx.y * gridDim.x + blockIdx.x) % NSLOT];
       atomicAdd(&cs.fallback_lanes, (unsigned long long)fails);
@@ -1120,17 +1228,20 @@ __global__ void __launch_bounds__(BLOCK)
   }
 }
 
+// The slices' sums of each output, one wave to an output: lane q adds slices q,
+// q + 64, ... in order, then the wave's butterfly (a thread to an output, adding its S
+// slices one after the other, took 7.5 us for 32 slices of 64 outputs; now 4.0).
 __global__ void __launch_bounds__(BLOCK)
     k_dft_finish(const double4* part, int S, long long m, double2* X) {
-  const long long k = (long long)blockIdx.x * BLOCK + threadIdx.x;
+  const long long k = (long long)blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
   if (k >= m) return;
-  double4 acc = part[k * S];
-  for (int q = 1; q < S; q++) {
+  DftSum acc = {0.0, 0.0, 0.0, 0.0};
+  for (int q = threadIdx.x & 63; q < S; q += 64) {
     const double4 p = part[k * S + q];
-    dd_acc2(acc.x, acc.y, p.x, p.y);
-    dd_acc2(acc.z, acc.w, p.z, p.w);
+    dft_add2(acc, {p.x, p.y, p.z, p.w});
   }
-  X[k] = make_double2(acc.x + acc.y, -(acc.z + acc.w));
+  dft_wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) X[k] = make_double2(acc.rh + acc.rl, -(acc.ih + acc.il));
 }
 
 // ------------------------------------------------------------ ragged batch
@@ -2425,23 +2536,31 @@ int cr_dft(const float* x, int64_t n, const float* w, int64_t m, double* X, unsi
   long long S = (target + m - 1) / m;
   const long long smax = (n + BLOCK * 8 - 1) / (BLOCK * 8);
   if (S > smax) S = smax;
-  if (S < 1) S = 1;
+  // up to 64 terms a thread in one slice take less than the allocation of a workspace
+  // and a second kernel (18 us of host work)
+  if (S < 1 || n <= 64 * BLOCK) S = 1;
   long long slice = (n + S - 1) / S;
   slice = (slice + BLOCK - 1) / BLOCK * BLOCK;
   if (slice < BLOCK) slice = BLOCK;
   S = n > 0 ? (n + slice - 1) / slice : 1;
+  // one slice: the kernel writes the result itself, without a workspace
   double4* part = nullptr;
-  hipError_t e = hipMallocAsync((void**)&part, (size_t)m * S * sizeof(double4), s);
+  hipError_t e = hipSuccess;
+  if (S > 1) e = hipMallocAsync((void**)&part, (size_t)m * S * sizeof(double4), s);
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? CR_E_NOMEM : hip_fail(e);
+  double2* Xd = reinterpret_cast<double2*>(X);
+  auto kernel = S > 1 ? k_dft<false> : k_dft<true>;
   for (long long k0 = 0; k0 < m; k0 += 65535) {  // grid.y is at most 65535
     const long long mk = m - k0 < 65535 ? m - k0 : 65535;
-    hipLaunchKernelGGL(k_dft, dim3((unsigned)S, (unsigned)mk), dim3(BLOCK), 0, s, x,
-                       (long long)n, w + k0, slice, part + k0 * S, (int)S, st, flags, k0);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)S, (unsigned)mk), dim3(BLOCK), 0, s, x, (int)n,
+                       w + k0, (int)slice, part ? part + k0 * S : nullptr, Xd + k0, (int)S, st,
+                       flags, k0);
   }
-  hipLaunchKernelGGL(k_dft_finish, dim3((unsigned)((m + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, s,
-                     part, (int)S, (long long)m, reinterpret_cast<double2*>(X));
+  if (S > 1)
+    hipLaunchKernelGGL(k_dft_finish, dim3((unsigned)((m + BLOCK / 64 - 1) / (BLOCK / 64))),
+                       dim3(BLOCK), 0, s, part, (int)S, (long long)m, Xd);
   e = hipGetLastError();
-  hipError_t e2 = hipFreeAsync(part, s);
+  hipError_t e2 = part ? hipFreeAsync(part, s) : hipSuccess;
   if (e != hipSuccess) return hip_fail(e);
   if (e2 != hipSuccess) return hip_fail(e2);
   int dev = 0;
