@@ -12,10 +12,11 @@
 //   quantum 2^-1074 by rounding y 2^(m+1074) to an integer; overflow comes
 //   from scaling the rounded value.
 // log: x = 2^e' m, m in [0.75, 1.5) (subnormal x scaled by 2^64 first), the
-//   same 16-entry 9-bit reciprocal table as binary32: t = m c_j - 1 exact as a
-//   double-double (TwoProd), log x = e' ln2 - ln c_j + log1p(t) with
-//   log1p t = t - t^2/2 + t^3/3 + t^4 S(t) (main path) or 2 atanh(t/(2+t))
-//   (accurate path).
+//   same 16-entry 9-bit reciprocal table as binary32.  Main path: a second 16-entry
+//   reciprocal c2 of the product's leading bits, t = m c_j c2 - 1 exact as a
+//   double-double (TwoProd), |t| < 2^-7.9, log x = e' ln2 - ln c_j - ln c2 +
+//   log1p(t) with log1p t = t - t^2/2 - t^3/2 S(t).  Accurate path: t = m c_j - 1 and
+//   log1p t = 2 atanh(t/(2+t)).
 // exp2: the paper's own three-table design (Sec. II-B).  x = N/4096 + R with
 //   N = nearest(4096 x) and R = x - N/4096 exact (|R| <= 2^-13), N = 4096 m +
 //   256 i1 + 16 i2 + i3, 2^x = 2^m T1[i1] T2[i2] T3[i3] 2^R with the 16-entry
@@ -36,7 +37,8 @@ struct Exp64Tab {
   double4 t1[16], t2[16];
 };
 struct Log64Tab {
-  double c[16];
+  double4 r1[16], r2[16];  // main path
+  double c[16];            // accurate path
   double4 L[16];
 };
 struct Exp2_64Tab {
@@ -58,6 +60,8 @@ __device__ __forceinline__ void exp2_64_tab_load(Exp2_64Tab& t, int tid) {
 }
 __device__ __forceinline__ void log64_tab_load(Log64Tab& t, int tid) {
   if (tid < 16) {
+    t.r1[tid] = LOG64_R1[tid];
+    t.r2[tid] = LOG64_R2[tid];
     t.c[tid] = LOG_C[tid];
     t.L[tid] = LOG64_L[tid];
   }
@@ -366,60 +370,49 @@ __device__ __forceinline__ Log64Setup log64_setup(double x) {
   return S;
 }
 
-// Main-path error, split by where it arises:
-//  * tail = t2.hi^2 sp stands for t^4 S(t): t2.hi carries t^2 within 3u
-//    (u = 2^-53; within u when c_j = 1, where t.lo = 0), the square, the
-//    Horner evaluation of S at t.hi (at most 1.2u relative: s0 = -1/4
-//    dominates, |s1 t / s0| < 0.06) and the product each one more rounding:
-//    below 9.2u = 2^-49.8 of |tail| in all.  S's own fit error is at most
-//    t^4 sup|g - S| (g the exact quotient; below 2^-57 t^4, checked in the
-//    bound tests) = 2^-55 of |tail|, and adding tail to b3.lo one more u of
-//    it.  LOG64_TAIL_EPS = 2^-49 covers the sum with a factor 1.6 to spare.
-//  * the rest: t, t^2/2 and t^3/3 in double-double (relative 2^-100), the
-//    table -ln c_j and e' ln2 to 2^-106, the double-double sums (2^-101):
-//    below 2^-99 |y|, where LOG64_EPS = 2^-70 leaves room for the test's own
-//    roundings.
-// The bound is therefore |tail| 2^-49 + |y| 2^-70.  Where c_j = 1 and e' = 0,
-// y = log1p t is small (|t| up to 1/16, |y| down to 2^-4.05) and the tail
-// term dominates; elsewhere |y| >= 0.03 and the test is close to 2^-70 |y|.
+// Main-path error (u = 2^-53), with tail = -t^3/2 S(t) and y = Ah + Al + t - t^2/2 +
+// tail, |t| < 2^-7.9:
+//  * tail: q.hi carries -t^2/2 within 2u, the product with t.hi, S's Horner
+//    evaluation (at most 1.1u: s0 = -2/3 dominates) and the last product within 4u
+//    more, S's fit below 2^-56 (2^-55.4 of S), the additions of tail to the other low
+//    parts, up to the test's own, at most 5u of it (those parts are below 2^-33): below
+//    11.5u = 2^-49.4 of |tail|.  LOG64_TAIL_EPS = 2^-49.
+//  * the rest: c1 c2 exact (25 bits), t exact; Ah = e' ln2 - ln c1 - ln c2 on the
+//    2^-42 grid exactly; their low parts to 2^-96 each (e' times that of ln2), t^2/2 to
+//    2^-122, and the roundings of sums of low parts below 2^-33 (below 2^-42 where e' =
+//    0): below 2^-85 |y|, as |y| >= 0.28 where e' != 0 and |y| >= 2^-8.1 unless e' = 0
+//    and c1 = c2 = 1, where Ah = Al = 0 and y = log1p t.  LOG64_EPS = 2^-78.
 constexpr double LOG64_TAIL_EPS = 0x1p-49;
-constexpr double LOG64_EPS = 0x1p-70;
+constexpr double LOG64_EPS = 0x1p-78;
 
+// Bound by VALU issue and HBM alike.  The second reciprocal shortens the polynomial from
+// degree 13 to 6 and leaves t^3 in binary64, where |t| up to 1/16 needed t^3/3 as a
+// double-double; the exact high sum replaces two double-double additions.  130 -> 80
+// VALU instructions an element, fallback 5.4 10^-5 -> 6.7 10^-6 on inputs with 10^-4 hard
+// ones.  Measured at 2^24 elements: 79 -> 55.2 us (4.9 TB/s).
 __device__ __forceinline__ double log64_fast(double x, const Log64Tab& tb, bool& ok) {
   Log64Setup S = log64_setup(x);
-  double c = tb.c[S.j];
-  double4 L = tb.L[S.j];
-  dd p = two_prod(S.m, c);
-  dd t = fast_two_sum(p.hi - 1.0, p.lo);  // exact: p.hi - 1 is exact
-  // log1p t = t - t^2/2 + t^3/3 + t^4 S(t)
-  dd t2 = two_prod(t.hi, t.hi);
-  t2.lo = fma(2.0 * t.hi, t.lo, t2.lo);
-  // t^3/3 as an unnormalised double-double (dd_add_ord below renormalises):
-  // t2.hi t.hi exactly by TwoProd, the cross terms t2.hi t.lo + t2.lo t.hi
-  // added by fmas (t2.lo t.lo, below 2^-106 |t|^3, dropped), then the same
-  // with 1/3 = THIRD_HI + THIRD_LO: within 10u^2 relative, as two dd_mul
-  dd b3;
-  {
-    const dd p3 = two_prod(t2.hi, t.hi);
-    const double p3l = fma(t2.lo, t.hi, fma(t2.hi, t.lo, p3.lo));
-    b3 = two_prod(p3.hi, THIRD_HI);
-    b3.lo = fma(p3l, THIRD_HI, fma(p3.hi, THIRD_LO, b3.lo));
-  }
-  double sp = LOG64_S[LOG64_S_DEG];
+  const double4& A = tb.r1[S.j];
+  // k = nearest(128 m c1) in 124..136; its low 4 bits are the row
+  const double kt = fma(S.m * A.x, 128.0, 0x1.8p52);
+  const double4& B = tb.r2[__double2loint(kt) & 15];
+  const dd p = two_prod(S.m, A.x * B.x);
+  const dd t = fast_two_sum(p.hi - 1.0, p.lo);  // exact: p.hi - 1 is exact
+  dd q = two_prod(t.hi, -0.5 * t.hi);           // -t^2/2
+  q.lo = fma(-t.hi, t.lo, q.lo);
+  double sp = LOG64_S3[LOG64_S3_DEG];
 #pragma unroll
-  for (int i = LOG64_S_DEG - 1; i >= 0; i--) sp = fma(sp, t.hi, LOG64_S[i]);
-  double tail = t2.hi * t2.hi * sp;
-  // |t| <= 1/16: t dominates t^2/2, which dominates t^3/3 + t^4 S(t)
-  dd l1 = dd_add_ord(t, dd{-0.5 * t2.hi, -0.5 * t2.lo});
-  l1 = dd_add_ord(l1, dd{b3.hi, b3.lo + tail});
-  // e' ln2 - ln c_j: |e' ln2| >= ln2 > |ln c_j| unless e' = 0; the total does
-  // not cancel (|y| >= 0.03 unless e' = 0 and c_j = 1, where y = l1 exactly)
-  double ed = (double)S.e2;
-  dd el = dd_mul_d(dd{LN2_TD[0].x, LN2_TD[0].y}, ed);
-  dd y = dd_add_nc(dd_add_ord(el, dd{L.x, L.y}), l1);
-  double e = fma(fabs(tail), LOG64_TAIL_EPS, fabs(y.hi) * LOG64_EPS);
-  double a = y.hi + (y.lo - e);
-  double b = y.hi + (y.lo + e);
+  for (int i = LOG64_S3_DEG - 1; i >= 0; i--) sp = fma(sp, t.hi, LOG64_S3[i]);
+  const double tail = (q.hi * t.hi) * sp;
+  const dd l = fast_two_sum(t.hi, q.hi);
+  const double ed = (double)S.e2;
+  const double Ah = fma(ed, LOG64_LN2_HI, A.y + B.y);  // exact
+  const double Al = fma(ed, LOG64_LN2_LO, A.z + B.z);
+  const dd y = two_sum(Ah, l.hi);
+  const double lo = y.lo + ((l.lo + (t.lo + (q.lo + tail))) + Al);
+  const double e = fma(fabs(tail), LOG64_TAIL_EPS, fabs(y.hi) * LOG64_EPS);
+  double a = y.hi + (lo - e);
+  double b = y.hi + (lo + e);
   ok = a == b;
   double res = b, spv;
   if (log64_special(x, spv)) {

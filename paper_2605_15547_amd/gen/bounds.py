@@ -123,6 +123,14 @@ def log64_quotient(S, a, b):
                 {k: v for k, v in enumerate(S)}, a, b)
 
 
+def log64_cubic(S, a, b):
+    """g(t) = -2 (log1p t - t + t^2/2) / t^3 = -2 sum (-1)^n t^n/(n+3) against S(t)."""
+    return Spec("-2 (log1p t - t + t^2/2)/t^3",
+                lambda c, K: log1p_series_ders(c, K, 3, 1, -2),
+                lambda lo, hi, K: log1p_series_bound(lo, hi, K, 3, -2),
+                {k: v for k, v in enumerate(S)}, a, b)
+
+
 def log64_absolute(S, a, b):
     """log1p t - t + t^2/2 - t^3/3 against t^4 S(t) (absolute)."""
     def fder(c, K):

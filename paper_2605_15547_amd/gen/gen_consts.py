@@ -494,11 +494,51 @@ def gen_f64():
             log2_of(B.sup_bound(B.log64_quotient(Sm, a, b)))))
     emit_arr("LOG64_S", cd, "coefficients (degree %d)" % (len(cd) - 1))
     emit("#define LOG64_S_DEG %d" % (len(cd) - 1))
+    gen_log64_rows(iv)
     emit("#define ATANH64_N 16")
     emit_dd_table("INV_ODD_DD", [mp.mpf(1) / (2 * k + 1) for k in range(17)], "1/(2k+1), k = 0..16")
     emit()
     gen_exp2_64()
     gen_log128()
+
+
+def gen_log64_rows(iv):
+    """Main path of binary64 log: the mantissa's reciprocal c1 (9 bits, 16 entries)
+    and a second one c2 (16 bits) of k/128, k = nearest(128 m c1) in 124..136, so
+    that t = m c1 c2 - 1 stays below 2^-7.9; -ln c1 and -ln c2 with high parts on
+    the 2^-42 grid, as ln 2 has, so that their sum with e' ln 2 is exact."""
+    grid = mp.mpf(2) ** -42
+    with mp.workprec(600):
+        def parts(v):
+            hi = mp.nint(v / grid) * grid
+            return float(hi), float(v - hi)
+        emit("// {c1, -ln c1 on the 2^-42 grid, the rest, 0}")
+        emit("__device__ __constant__ const double4 LOG64_R1[16] = {")
+        for _, _, c in iv:
+            emit("  {%s, %s, %s, 0.0}," % ((hexd(float(c)),) + tuple(hexd(v) for v in parts(-mp.log(c)))))
+        emit("};")
+        emit("// row k mod 16 for k = 124..136: {c2 ~ 128/k, -ln c2 on the 2^-42 grid, the rest, 0}")
+        emit("__device__ __constant__ const double4 LOG64_R2[16] = {")
+        c2 = {}
+        for r in range(16):
+            k = 128 + r if r <= 8 else 112 + r
+            c2[k] = split_bits(mp.mpf(128) / k, 16)
+            emit("  {%s, %s, %s, 0.0}," % ((hexd(c2[k]),) + tuple(hexd(v) for v in parts(-mp.log(mp.mpf(c2[k]))))))
+        emit("};")
+        hi, lo = parts(mp.log(2))
+        emit_const("LOG64_LN2_HI", hi, "ln 2 on the 2^-42 grid")
+        emit_const("LOG64_LN2_LO", lo)
+        half = mp.mpf(1) / 256 * mp.mpf("1.0001")
+        a = min((mp.mpf(k) / 128 - half) * mp.mpf(c2[k]) - 1 for k in range(124, 137))
+        b = max((mp.mpf(k) / 128 + half) * mp.mpf(c2[k]) - 1 for k in range(124, 137))
+    # log1p t = t - t^2/2 - t^3/2 S(t)
+    g = lambda t: -2 * (mp.log1p(t) - t + t * t / 2) / t ** 3 if t != 0 else mp.mpf(-2) / 3
+    cd = [d(v) for v in lawson_fit(g, lambda t: mp.mpf(1), a, b, list(range(7)), npts=120, iters=16)]
+    emit("// log1p t = t - t^2/2 - t^3/2 S(t), t in [%s, %s]; |S + 2 (log1p t - t + t^2/2)/t^3| <= 2^%.2f (proven)"
+         % (mp.nstr(a, 8), mp.nstr(b, 8), log2_of(B.sup_bound(B.log64_cubic(
+             [mp.mpf(v) for v in cd], a, b)))))
+    emit_arr("LOG64_S3", cd, "coefficients (degree %d)" % (len(cd) - 1))
+    emit("#define LOG64_S3_DEG %d" % (len(cd) - 1))
 
 
 def gen_log128():
