@@ -1614,15 +1614,20 @@ struct DevState {
   unsigned char* scratch;
 };
 DevState g_state[MAX_DEV];
-bool g_state_ok[MAX_DEV];
+std::atomic<bool> g_state_ok[MAX_DEV];
 
-int get_state(DevState** out) {
+int get_state(DevState** out, int* device = nullptr) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e);
   if (dev < 0 || dev >= MAX_DEV) return CR_E_HIP;
+  if (device) *device = dev;
+  if (g_state_ok[dev].load(std::memory_order_acquire)) {  // every call but the first
+    *out = &g_state[dev];
+    return CR_OK;
+  }
   std::lock_guard<std::mutex> lk(g_mu);
-  if (!g_state_ok[dev]) {
+  if (!g_state_ok[dev].load(std::memory_order_relaxed)) {
     void* ps = nullptr;
     void* pb = nullptr;
     e = hipGetSymbolAddress(&ps, HIP_SYMBOL(g_dev_stats));
@@ -1632,7 +1637,7 @@ int get_state(DevState** out) {
     if (!ps || !pb) return CR_E_HIP;
     g_state[dev].stats = static_cast<DevStats*>(ps);
     g_state[dev].scratch = static_cast<unsigned char*>(pb);
-    g_state_ok[dev] = true;
+    g_state_ok[dev].store(true, std::memory_order_release);
   }
   *out = &g_state[dev];
   return CR_OK;
@@ -1646,16 +1651,17 @@ int get_stats(DevStats** out) {
   return CR_OK;
 }
 
-int g_cus = 0;  // compute units of the current device (cached on first use)
+std::atomic<int> g_cus{0};  // compute units of the current device (cached on first use)
 
 int num_cus() {
-  if (!g_cus) {
+  int n = g_cus.load(std::memory_order_relaxed);
+  if (!n) {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess)
       (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    g_cus = cus > 0 ? cus : 256;
+    g_cus = n = cus > 0 ? cus : 256;
   }
-  return g_cus;
+  return n;
 }
 
 // default workgroups per compute unit of the persistent grids
@@ -1719,9 +1725,16 @@ constexpr int NVARIANT = 7;
 constexpr int VARIANTS[NVARIANT][3] = {{2, 1, 0}, {1, 1, 0}, {4, 1, 0}, {2, 0, 0},
                                        {4, 0, 0}, {1, 0, 0}, {2, 1, 1}};
 
+// Arrays that give the compute units fewer than four workgroups of the smallest tile
+// (1024 elements) each take that tile, and no prefetch, whatever the configured variant
+// of the LDS tables: each workgroup has one tile, and its length is the call's.  Graph
+// launches back to back, variant 0 (2048 elements) against it: expf of 10^3 to 10^5
+// elements 3.3 -> 2.5 us, of 3 10^5 3.3 -> 2.8, of 10^6 3.7 -> 3.5, of 3 10^6 6.2 -> 7.4;
+// sinf 4.2 -> 2.9, 5.4 -> 4.5, 6.5 -> 5.8, 10.1 -> 10.2.
 template <class Op>
 int launch_variant(const float* in, float* out, size_t n, hipStream_t s, unsigned flags,
                    DevStats* st, int variant, int grid) {
+  if (n <= (size_t)num_cus() * 4096 && VARIANTS[variant][2] == 0) variant = 5;
   switch (variant) {
     case 0: return launch_map_f32<Op, 2, 1, 0>(in, out, n, s, flags, st, grid);
     case 1: return launch_map_f32<Op, 1, 1, 0>(in, out, n, s, flags, st, grid);
@@ -1937,9 +1950,11 @@ int num_variants_of(int f) {
 
 int eval_cfg(int func_id, int impl, unsigned flags, const void* in, void* out, size_t n,
              hipStream_t s, int variant, int bpc) {
-  DevStats* st = nullptr;
-  int rc = get_stats(&st);
+  DevState* ds = nullptr;
+  int dev = 0;
+  int rc = get_state(&ds, &dev);
   if (rc) return rc;
+  DevStats* const st = ds->stats;
   const int g = num_cus() * (bpc > 0 ? bpc : default_bpc());
   const int mode = (int)((flags & CR_FLAG_ROUND_MASK) >> CR_FLAG_ROUND_SHIFT);
   if (mode != RM_RN)
@@ -1962,11 +1977,7 @@ int eval_cfg(int func_id, int impl, unsigned flags, const void* in, void* out, s
     rc = launch_complex<CSinF>((const float*)in, (float*)out, n, s, flags, st, g);
   else
     rc = launch_variant64<OpLog64>((const double*)in, (double*)out, n, s, flags, st, variant, g);
-  if (rc == CR_OK) {
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    g_elems[dev] += n;
-  }
+  if (rc == CR_OK) g_elems[dev] += n;
   return rc;
 }
 
