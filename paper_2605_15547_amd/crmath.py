@@ -6,6 +6,7 @@ in-tree paper_2605_15547_amd/libcr.so and fails loudly if it is missing.
 """
 import ctypes
 import os
+import struct
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "libcr.so")
@@ -120,20 +121,37 @@ def _fid(func):
     return FUNC_ID[func] if isinstance(func, str) else int(func)
 
 
+_torch = None  # the module, imported on first use: only tensors and streams need it
+
+
+def _get_torch():
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def available(func, impl=IMPL_AUTO):
     return bool(lib().cr_available(_fid(func), impl))
 
 
+def _raw_stream(stream):
+    """The HIP stream as an integer: the given stream's, or the current stream of the
+    current device (read without building a stream object: 0.3 us instead of 2)."""
+    if stream is not None:
+        return stream.cuda_stream
+    C = (_torch or _get_torch())._C
+    return C._cuda_getCurrentRawStream(C._cuda_getDevice())
+
+
 def _stream_ptr(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return ctypes.c_void_p(_raw_stream(stream))
 
 
 def eval_ptr(func, in_ptr, out_ptr, n, impl=IMPL_AUTO, flags=0, stream_ptr=None):
     """Raw call: device pointers (ints), element count, HIP stream pointer."""
-    rc = lib().cr_eval_ex(_fid(func), impl, flags, ctypes.c_void_p(in_ptr),
-                          ctypes.c_void_p(out_ptr), n, stream_ptr)
+    rc = (_lib or lib()).cr_eval_ex(_fid(func), impl, flags, in_ptr, out_ptr, n, stream_ptr)
     if rc != CR_OK:
         raise CrError(rc, "cr_eval_ex(%s)" % func)
 
@@ -142,23 +160,30 @@ def evaluate(func, x, out=None, impl=IMPL_AUTO, flags=0, stream=None):
     """Correctly rounded func(x) for a contiguous CUDA tensor x (float32 for the
     binary32 functions, float64 for exp/log/exp2; complex functions take
     interleaved (re, im) float32 pairs).  sincosf returns shape (2, n)."""
-    import torch
+    torch = _torch or _get_torch()
     fid = _fid(func)
     want = torch.float64 if 64 <= fid < 80 else torch.float32
     if x.dtype != want or not x.is_cuda or not x.is_contiguous():
         raise ValueError("expected a contiguous CUDA %s tensor" % want)
-    n = x.numel() // 2 if fid >= 80 else x.numel()
-    nout = 2 * n if fid == FUNC_ID["sincosf"] or fid >= 80 else n
+    n = x.numel()
+    shape = x.shape
+    if fid == 11:  # sincosf
+        shape = (2, n)
+    elif fid >= 80:
+        n //= 2
     if out is None:
-        out = torch.empty(nout, dtype=want, device=x.device)
-    eval_ptr(fid, x.data_ptr(), out.data_ptr(), n, impl, flags, _stream_ptr(stream))
-    return out.view(2, n) if fid == FUNC_ID["sincosf"] else out.view(x.shape)
+        # in its final shape (a complex function writes 2n floats: view raises for an odd one)
+        out = torch.empty(shape if fid < 80 else 2 * n, dtype=want, device=x.device)
+    rc = (_lib or lib()).cr_eval_ex(fid, impl, flags, x.data_ptr(), out.data_ptr(), n,
+                                    _raw_stream(stream))
+    if rc != CR_OK:
+        raise CrError(rc, "cr_eval_ex(%s)" % fid)
+    return out if out.shape == shape else out.view(shape)
 
 
 def dft_ptr(x_ptr, n, w_ptr, m, out_ptr, flags=0, stream_ptr=None):
     """Raw cr_dft call: device pointers (ints), sample and frequency counts."""
-    rc = lib().cr_dft(ctypes.c_void_p(x_ptr), n, ctypes.c_void_p(w_ptr), m,
-                      ctypes.c_void_p(out_ptr), flags, stream_ptr)
+    rc = (_lib or lib()).cr_dft(x_ptr, n, w_ptr, m, out_ptr, flags, stream_ptr)
     if rc != CR_OK:
         raise CrError(rc, "cr_dft")
 
@@ -166,19 +191,31 @@ def dft_ptr(x_ptr, n, w_ptr, m, out_ptr, flags=0, stream_ptr=None):
 def dft(x, w, out=None, flags=0, stream=None):
     """cr_dft on CUDA float32 tensors x (samples) and w (angles per output):
     returns an (m, 2) float64 tensor of (re, im)."""
-    import torch
+    torch = _torch or _get_torch()
     for t in (x, w):
         if t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous():
             raise ValueError("expected contiguous CUDA float32 tensors")
     m = w.numel()
     if out is None:
         out = torch.empty((m, 2), dtype=torch.float64, device=w.device)
-    dft_ptr(x.data_ptr(), x.numel(), w.data_ptr(), m, out.data_ptr(), flags, _stream_ptr(stream))
+    dft_ptr(x.data_ptr(), x.numel(), w.data_ptr(), m, out.data_ptr(), flags, _raw_stream(stream))
     return out
 
 
 def _requests(reqs):
     """reqs: list of (func, in_ptr, out_ptr, n[, impl]) -> ctypes array"""
+    # all of them at once, in the layout of Request (48 requests: 36 -> 12 us)
+    try:
+        flat = []
+        for r in reqs:
+            func, ip, op, n = r[:4]
+            flat.extend((FUNC_ID[func] if func.__class__ is str else _fid(func),
+                         r[4] if len(r) > 4 else IMPL_AUTO, ip, op, n))
+        if flat:
+            return (Request * len(reqs)).from_buffer(
+                bytearray(struct.pack("@" + "iiPPq" * len(reqs), *flat)))
+    except struct.error:  # values that only ctypes converts
+        pass
     arr = (Request * max(1, len(reqs)))()
     for i, r in enumerate(reqs):
         func, ip, op, n = r[:4]
@@ -198,7 +235,7 @@ class BatchPlan:
             raise CrError(rc, "cr_batch_plan_create")
 
     def launch(self, stream=None):
-        rc = lib().cr_batch_plan_launch(self.handle, _stream_ptr(stream))
+        rc = (_lib or lib()).cr_batch_plan_launch(self.handle, _raw_stream(stream))
         if rc != CR_OK:
             raise CrError(rc, "cr_batch_plan_launch")
 
@@ -216,7 +253,7 @@ class BatchPlan:
 
 def eval_batch(reqs, stream=None):
     arr = _requests(reqs)
-    rc = lib().cr_eval_batch(arr, len(reqs), _stream_ptr(stream))
+    rc = (_lib or lib()).cr_eval_batch(arr, len(reqs), _raw_stream(stream))
     if rc != CR_OK:
         raise CrError(rc, "cr_eval_batch")
 
@@ -224,7 +261,7 @@ def eval_batch(reqs, stream=None):
 def eval_batch_noalloc(reqs, stream=None):
     """cr_eval_batch_noalloc: the batch with its tables in static scratch."""
     arr = _requests(reqs)
-    rc = lib().cr_eval_batch_noalloc(arr, len(reqs), _stream_ptr(stream))
+    rc = (_lib or lib()).cr_eval_batch_noalloc(arr, len(reqs), _raw_stream(stream))
     if rc != CR_OK:
         raise CrError(rc, "cr_eval_batch_noalloc")
 
