@@ -77,13 +77,16 @@ constexpr int QFLUSH = QCAP / 2;            // flush when the queue is fuller th
 //
 // Tiles of the map kernels.  T is float or double, VN elements make a 128-bit
 // vector, and a tile is U vectors per thread (vector u of thread t is vector
-// t + u BLOCK of the tile); nv = n / VN whole vectors.  A tile is accessed through
-// a buffer descriptor whose base is the tile's first vector and whose size ends at
-// nv, built by scalar instructions from the tile's number: the hardware drops
-// stores past the end and returns 0 for loads there, so the ragged last tile takes
-// the same instructions as any other and no lane computes a 64-bit address or a
-// bounds check (expf 4% faster than with per-lane addresses at 2^24 elements,
-// binary64 log 4%, sincosf 3%).
+// t + u BLOCK of the tile); nv = n / VN whole vectors.  The BLOCK vectors u of a tile
+// are accessed through a buffer descriptor of their own, whose base is the first of
+// them and whose size ends at nv, built by scalar instructions from the tile's
+// number: the hardware drops stores past the end and returns 0 for loads there, so
+// the ragged last tile takes the same instructions as any other and no lane computes
+// a 64-bit address or a bounds check (expf 4% faster than with per-lane addresses at
+// 2^24 elements, binary64 log 4%, sincosf 3%).  One descriptor for the tile and u in
+// the access's scalar offset would save a few scalar instructions, but the builtins
+// exclude the scalar offset from the range check: it is always 0 here, and the vector
+// offset alone, 16 bytes times the thread, is what the hardware checks.
 // gfx950 takes 128-bit accesses at any 4-byte address, so a slice of an array, a
 // cosine block behind an odd number of sines and an aligned buffer all run the
 // same kernel.  The n % VN elements after the last vector are evaluated one to a
@@ -105,37 +108,38 @@ struct Vec<double> {
   static constexpr int N = 2;
 };
 
-// The tile of tv vectors that starts at vector t0 of the nv vectors at p (counts
-// of vectors fit in 32 bits: LAUNCH_ELEMS elements a launch).
-template <class T>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const T* p, int t0, int nv, int tv) {
+// Vectors u, one a thread, of the tile of BLOCK U vectors that starts at vector t0 of
+// the nv vectors at p (counts of vectors fit in 32 bits: LAUNCH_ELEMS elements a
+// launch).
+template <class T, int U>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const T* p, int t0, int nv, int u) {
   // the same in every lane: scalar registers (and past the end: an empty tile)
   t0 = min(__builtin_amdgcn_readfirstlane(t0), nv);
-  const int left = min(nv - t0, tv);
+  const int left = 16 * min(nv - t0, BLOCK * U);
+  char* base = (char*)const_cast<T*>(p) + 16 * (size_t)(unsigned)t0;
   // 0x00020000: raw buffer, 32-bit data format, bounds checked by the byte
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p) + (size_t)Vec<T>::N * (unsigned)t0,
-                                           0, 16 * left, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(base + 16 * BLOCK * u, 0, max(left - 16 * BLOCK * u, 0),
+                                           0x00020000);
 }
 template <class T, int U>
 __device__ __forceinline__ void tile_load(typename Vec<T>::type (&v)[U], const T* in, int t0,
                                           int nv) {
-  const __amdgpu_buffer_rsrc_t r = tile_rsrc(in, t0, nv, BLOCK * U);
 #pragma unroll
   for (int u = 0; u < U; u++) {
-    const v4u_t x = __builtin_amdgcn_raw_buffer_load_b128(r, 16 * threadIdx.x, 16 * BLOCK * u,
-                                                          CR_NT ? 2 : 0);
+    const v4u_t x = __builtin_amdgcn_raw_buffer_load_b128(tile_rsrc<T, U>(in, t0, nv, u),
+                                                          16 * threadIdx.x, 0, CR_NT ? 2 : 0);
     __builtin_memcpy(&v[u], &x, 16);
   }
 }
 template <class T, int U>
 __device__ __forceinline__ void tile_store(const typename Vec<T>::type (&v)[U], T* out, int t0,
                                            int nv) {
-  const __amdgpu_buffer_rsrc_t r = tile_rsrc(out, t0, nv, BLOCK * U);
 #pragma unroll
   for (int u = 0; u < U; u++) {
     v4u_t x;
     __builtin_memcpy(&x, &v[u], 16);
-    __builtin_amdgcn_raw_buffer_store_b128(x, r, 16 * threadIdx.x, 16 * BLOCK * u, CR_NT ? 2 : 0);
+    __builtin_amdgcn_raw_buffer_store_b128(x, tile_rsrc<T, U>(out, t0, nv, u), 16 * threadIdx.x, 0,
+                                           CR_NT ? 2 : 0);
   }
 }
 // Bit VN u + c is set where vector u of the tile lies below nv.
@@ -782,7 +786,7 @@ __global__ void __launch_bounds__(BLOCK)
     double2 v[U];
     tile_load<double, U>(v, in, t0, n2);
     if (SL) {
-      // slots past the end hold 1.0: evaluated, never stored or queued
+      // slots past the end hold 0: evaluated, never stored or queued
       double xin[2 * U];
       unsigned fail = 0;
 #pragma unroll
