@@ -271,9 +271,14 @@ int cr_stats_read(void *stream, cr_stats *out);
  * before the next; 1, 2, 3 = 2, 4, 8 doubles per thread, all elements of the
  * tile evaluated in straight-line code before the failing ones are queued.
  * cr_tune_variant_info describes the binary32 variants.
+ * The default of the binary32 functions (but sincosf), in force until a
+ * configuration is set, loaded or tuned, is variant 0 (which cr_tune_get
+ * reports and cr_tune_save writes), and variant 5 for arrays of at most 4096
+ * elements per compute unit (2^20 on MI355X) when the grid covers them with
+ * tiles of 1024 elements.  A configuration that is set holds for every length.
  * Configurations are process-wide host state shared by all devices. */
 typedef struct {
-  int32_t variant;       /* 0 .. cr_tune_num_variants()-1; 0 is the default */
+  int32_t variant;       /* 0 .. cr_tune_num_variants()-1 */
   int32_t blocks_per_cu; /* 1..64; 0 (set only) = the library default (16) */
 } cr_tune_cfg;
 

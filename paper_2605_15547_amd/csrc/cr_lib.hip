@@ -1729,17 +1729,24 @@ constexpr int NVARIANT = 7;
 constexpr int VARIANTS[NVARIANT][3] = {{2, 1, 0}, {1, 1, 0}, {4, 1, 0}, {2, 0, 0},
                                        {4, 0, 0}, {1, 0, 0}, {2, 1, 1}};
 
-// Arrays that give the compute units fewer than four workgroups of the smallest tile
-// (1024 elements) each take that tile, and no prefetch, whatever the configured variant
-// of the LDS tables: each workgroup has one tile, and its length is the call's.  Graph
-// launches back to back, variant 0 (2048 elements) against it: expf of 10^3 to 10^5
-// elements 3.3 -> 2.5 us, of 3 10^5 3.3 -> 2.8, of 10^6 3.7 -> 3.5, of 3 10^6 6.2 -> 7.4;
-// sinf 4.2 -> 2.9, 5.4 -> 4.5, 6.5 -> 5.8, 10.1 -> 10.2.
+// The variant of a function whose configuration is not set (DEFAULT_VARIANT).  Arrays
+// that give the compute units at most four workgroups of the smallest tile (1024
+// elements) each take that tile, and no prefetch: each workgroup has one tile, and
+// its length is the call's.  Graph launches back to back, variant 0 (2048 elements,
+// prefetch) against it, at 10^3, 3 10^5 and 2^20 elements of the benchmark's inputs:
+// expf 2.44 -> 2.14 us, 3.82 -> 3.52, 4.77 -> 4.46; tanf 3.08 -> 2.51, 5.36 -> 4.64,
+// 6.67 -> 5.76; binary32-only expf 5.23 -> 4.35, 6.09 -> 5.41, 7.35 -> 6.72, tanf
+// 5.22 -> 3.55, 8.57 -> 7.06, 10.75 -> 9.60; no function slower at any of the three.
+// Beyond, at 3 10^6, expf 6.2 -> 7.4, sinf 10.1 -> 10.2.  A configuration that was set
+// is launched as it is.
+constexpr int DEFAULT_VARIANT = -1;
+int default_variant(size_t n, int grid) {
+  return n <= (size_t)num_cus() * 4096 && n <= (size_t)grid * 1024 ? 5 : 0;
+}
 template <class Op>
 int launch_variant(const float* in, float* out, size_t n, hipStream_t s, unsigned flags,
                    DevStats* st, int variant, int grid) {
-  if (n <= (size_t)num_cus() * 4096 && VARIANTS[variant][2] == 0) variant = 5;
-  switch (variant) {
+  switch (variant == DEFAULT_VARIANT ? default_variant(n, grid) : variant) {
     case 0: return launch_map_f32<Op, 2, 1, 0>(in, out, n, s, flags, st, grid);
     case 1: return launch_map_f32<Op, 1, 1, 0>(in, out, n, s, flags, st, grid);
     case 2: return launch_map_f32<Op, 4, 1, 0>(in, out, n, s, flags, st, grid);
@@ -1790,7 +1797,7 @@ constexpr int NVARIANT64 = 4;
 template <class Op>
 int launch_variant64(const double* in, double* out, size_t n, hipStream_t s, unsigned flags,
                      DevStats* st, int variant, int grid) {
-  switch (variant) {
+  switch (variant == DEFAULT_VARIANT ? 0 : variant) {
     case 0: return launch_map_f64<Op, 4, 0>(in, out, n, s, flags, st, grid);
     case 1: return launch_map_f64<Op, 1, 1>(in, out, n, s, flags, st, grid);
     case 2: return launch_map_f64<Op, 2, 1>(in, out, n, s, flags, st, grid);
@@ -1936,7 +1943,7 @@ int dispatch_dir(int mode, int f, const float* in, float* out, size_t n, hipStre
 // the split one; functions 0..18, then the ids of EXTRA_FUNCS.
 constexpr int EXTRA_FUNCS[] = {CR_EXP, CR_LOG, CR_EXP2, CR_CEXPF, CR_CLOGF, CR_CSINF};
 constexpr int NFUNC_IDX = CR_NUM_F32 + (int)(sizeof(EXTRA_FUNCS) / sizeof(EXTRA_FUNCS[0]));
-std::atomic<int> g_cfg_variant[2][NFUNC_IDX];
+std::atomic<int> g_cfg_variant[2][NFUNC_IDX];  // the variant + 1, 0: not set
 std::atomic<int> g_cfg_bpc[2][NFUNC_IDX];  // 0: the default
 
 int fidx(int f) {
@@ -2299,7 +2306,7 @@ int cr_eval_ex(int func_id, int impl, unsigned flags, const void* in, void* out,
     return CR_E_IMPL;  // directed modes: the binary32 functions, binary64-internal
   const int ii = iidx(impl), fi = fidx(func_id);
   return eval_cfg(func_id, impl, flags, in, out, n, (hipStream_t)stream,
-                  g_cfg_variant[ii][fi].load(), g_cfg_bpc[ii][fi].load());
+                  g_cfg_variant[ii][fi].load() - 1, g_cfg_bpc[ii][fi].load());
 }
 
 // ------------------------------------------------------------------ tuning
@@ -2327,7 +2334,7 @@ int cr_tune_get(int func_id, int impl, cr_tune_cfg* cfg) {
   if (!impl_valid(impl)) return CR_E_IMPL;
   if (!cfg) return CR_E_NULL;
   const int ii = iidx(impl), fi = fidx(func_id);
-  cfg->variant = g_cfg_variant[ii][fi].load();
+  cfg->variant = std::max(g_cfg_variant[ii][fi].load() - 1, 0);
   int b = g_cfg_bpc[ii][fi].load();
   cfg->blocks_per_cu = b > 0 ? b : default_bpc();
   return CR_OK;
@@ -2337,7 +2344,7 @@ int cr_tune_set(int func_id, int impl, const cr_tune_cfg* cfg) {
   int rc = tune_check(func_id, impl, cfg);
   if (rc) return rc;
   const int ii = iidx(impl), fi = fidx(func_id);
-  g_cfg_variant[ii][fi] = cfg->variant;
+  g_cfg_variant[ii][fi] = cfg->variant + 1;
   g_cfg_bpc[ii][fi] = cfg->blocks_per_cu;
   return CR_OK;
 }
@@ -2375,8 +2382,8 @@ int cr_tune_save(const char* path) {
   for (int i = 0; i < 2; i++)
     for (int f = 0; f < NFUNC_IDX; f++) {
       int b = g_cfg_bpc[i][f].load();
-      fprintf(fp, "%s %s %d %d\n", FUNC_NAMES[f], i ? "split" : "f64", g_cfg_variant[i][f].load(),
-              b > 0 ? b : default_bpc());
+      fprintf(fp, "%s %s %d %d\n", FUNC_NAMES[f], i ? "split" : "f64",
+              std::max(g_cfg_variant[i][f].load() - 1, 0), b > 0 ? b : default_bpc());
     }
   for (int i = 0; i < 2; i++)
     fprintf(fp, "batch %s 0 %d\n", i ? "split" : "f64", g_batch_bpc[i].load());
@@ -2430,7 +2437,7 @@ int cr_tune_load(const char* path) {
       g_batch_bpc[iidx(e.impl)] = e.bpc;
       continue;
     }
-    g_cfg_variant[iidx(e.impl)][fidx(e.func)] = e.variant;
+    g_cfg_variant[iidx(e.impl)][fidx(e.func)] = e.variant + 1;
     g_cfg_bpc[iidx(e.impl)][fidx(e.func)] = e.bpc;
   }
   return CR_OK;
@@ -2513,7 +2520,7 @@ int cr_autotune(int func_id, int impl, const void* in, void* out, size_t n, int 
   (void)hipEventDestroy(e1);
   if (rc) return rc;
   const int ii = iidx(impl), fi = fidx(func_id);
-  g_cfg_variant[ii][fi] = best_v;
+  g_cfg_variant[ii][fi] = best_v + 1;
   g_cfg_bpc[ii][fi] = best_b;
   if (best_gelem_s) *best_gelem_s = best_ms > 0 ? (double)n * reps / (best_ms * 1e-3) / 1e9 : 0.0;
   return CR_OK;

@@ -76,3 +76,39 @@ def test_binary64_variants(oracle, func, variant, per_thread):
 def test_directed_modes(oracle, func, mode):
     _need_gpu()
     check(oracle, func, crmath.IMPL_F64_INTERNAL, 8, crmath.ROUND_FLAGS[mode], mode)
+
+
+VARIANTS = list(enumerate(crmath.tune_variants()))
+
+
+@pytest.mark.parametrize("func,impl", [("log1pf", crmath.IMPL_F64_INTERNAL),
+                                       ("sinf", crmath.IMPL_F64_INTERNAL),
+                                       ("expf", crmath.IMPL_SPLIT_F32)])
+@pytest.mark.parametrize("variant,per_thread", [(v, s[0]) for v, s in VARIANTS])
+def test_binary32_variants(oracle, func, impl, variant, per_thread):
+    _need_gpu()
+    crmath.tune_set(func, impl, variant, 16)
+    check(oracle, func, impl, per_thread)
+
+
+@pytest.mark.parametrize("impl", [crmath.IMPL_F64_INTERNAL, crmath.IMPL_SPLIT_F32])
+@pytest.mark.parametrize("variant,per_thread", [(v, s[0]) for v, s in VARIANTS])
+def test_the_variant_that_is_set_runs(variant, per_thread, impl):
+    """Of a forced call each workgroup that has a tile queues 512 elements, 8 waves of
+    them, at its end, so the counted waves tell the tile's size; the array is shorter
+    than the length up to which the default is the smallest tile."""
+    _need_gpu()
+    n, tile = 300_000, 256 * per_thread
+    x = torch.rand(n, device="cuda")
+    out = torch.empty_like(x)
+
+    def waves():
+        crmath.stats_reset()
+        crmath.eval_ptr("expf", x.data_ptr(), out.data_ptr(), n, impl,
+                        crmath.FLAG_FORCE_FALLBACK, crmath._stream_ptr(None))
+        return crmath.stats_read()["fallback_waves"]
+
+    crmath.tune_set("expf", impl, variant, 16)
+    assert waves() == 8 * -(-n // tile)
+    crmath.tune_reset()
+    assert waves() == 8 * -(-n // 1024)
