@@ -202,20 +202,22 @@ int cr_batch_plan_launch(cr_batch_plan *plan, void *stream);
 /* Release the plan (synchronises with its last launch first). */
 int cr_batch_plan_destroy(cr_batch_plan *plan);
 /* Evaluate the requests without a plan.  Batches of up to a few hundred requests
- * go to the kernel as its arguments (up to four launches): nothing is allocated
- * or copied and the call does not wait.  For larger ones, and on a stream that is
- * being captured, the request and tile tables are allocated and freed
- * stream-ordered, and the call synchronises the stream once, after copying the
- * tables from host memory and before the launch. */
+ * (96 of one implementation a launch, up to four launches) go to the kernel as
+ * its arguments: nothing is allocated or copied, the call does not wait, and it
+ * can be captured (the graph holds the requests; their buffers must stay valid
+ * while it is replayed).  For larger ones the request and tile tables are
+ * allocated and freed stream-ordered, and the call synchronises the stream once,
+ * after copying the tables from host memory and before the launch; on a stream
+ * that is being captured it returns CR_E_HIP before anything is enqueued. */
 int cr_eval_batch(const cr_request *reqs, int32_t num, void *stream);
 
-/* For callers that cannot allocate device memory (code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * evaluation as cr_eval_batch, with the same request conventions, results
- * and errors, but the tables of a batch too large to go as kernel arguments
- * are put into a fixed scratch array in the library's static device memory
- * instead of stream-ordered allocations.  The call makes no hipMalloc/hipFree or other allocating
- * device call.  The scratch holds at most CR_NOALLOC_MAX_REQUESTS requests and
+/* For callers that cannot allocate device memory (tight serving loops,
+ * harnesses that forbid hipMalloc): the same evaluation as cr_eval_batch, with
+ * the same request conventions, results and errors (under capture too), but the
+ * tables of a batch too large to go as kernel arguments are put into a fixed
+ * scratch array in the library's static device memory instead of stream-ordered
+ * allocations.  The call makes no hipMalloc/hipFree or other allocating device
+ * call.  The scratch holds at most CR_NOALLOC_MAX_REQUESTS requests and
  * CR_NOALLOC_MAX_TILES tiles, where a request of n elements takes
  * ceil(n / 4096) tiles (about 2 10^9 elements in all); larger batches return
  * CR_E_SCRATCH before anything is copied or launched.  Each device holds one

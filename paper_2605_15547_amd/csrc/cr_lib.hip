@@ -2256,16 +2256,19 @@ hipError_t launch_batch_args(const BatchTables& T, DevStats* st, unsigned flags,
 // Whether a batch goes by kernel arguments: a launch costs about 4.5 us here, the
 // allocation and copy of the tables and the wait for it about 35 us more than that
 // (200 requests, three launches: 18 us; 512 requests by tables: 44 us), so up to
-// ARGS_LAUNCHES launches.  A stream being captured keeps to the tables.
+// ARGS_LAUNCHES launches.  They can be captured like any launch; the tables cannot
+// (the call waits for their copy), so a larger batch is refused on a stream that is
+// being captured before anything is enqueued there.
 constexpr int ARGS_LAUNCHES = 4;
-bool by_args(const BatchTables& T, hipStream_t s) {
-  if (args_launches(T) > ARGS_LAUNCHES) return false;
+hipError_t batch_route(const BatchTables& T, hipStream_t s, bool& args) {
+  args = args_launches(T) <= ARGS_LAUNCHES;
+  if (args) return hipSuccess;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
+    (void)hipGetLastError();  // the copies report what is wrong with the stream
+    return hipSuccess;
   }
-  return cs == hipStreamCaptureStatusNone;
+  return cs == hipStreamCaptureStatusNone ? hipSuccess : hipErrorStreamCaptureUnsupported;
 }
 
 }  // namespace
@@ -2698,11 +2701,14 @@ int cr_eval_batch(const cr_request* reqs, int32_t num, void* stream) {
   rc = get_stats(&st);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
-  if (by_args(T, s)) return run_batch(T, true, nullptr, nullptr, st, s);
+  bool args = false;
+  hipError_t e = batch_route(T, s, args);
+  if (e != hipSuccess) return hip_fail(e);
+  if (args) return run_batch(T, true, nullptr, nullptr, st, s);
   // one stream-ordered allocation for both tables
   const size_t rb = (T.reqs.size() * sizeof(BReq) + 255) / 256 * 256;
   unsigned char* d = nullptr;
-  hipError_t e = hipMallocAsync((void**)&d, rb + T.tile_req.size() * sizeof(unsigned), s);
+  e = hipMallocAsync((void**)&d, rb + T.tile_req.size() * sizeof(unsigned), s);
   if (e != hipSuccess) {
     t_last_hip = (int)e;
     return CR_E_NOMEM;
@@ -2727,9 +2733,12 @@ int cr_eval_batch_noalloc(const cr_request* reqs, int32_t num, void* stream) {
   rc = get_state(&ds);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
+  bool args = false;
+  const hipError_t e = batch_route(T, s, args);
+  if (e != hipSuccess) return hip_fail(e);
   // stream-ordered after earlier work on s (including an earlier call's kernels
   // still reading the tables)
-  return run_batch(T, by_args(T, s), reinterpret_cast<BReq*>(ds->scratch),
+  return run_batch(T, args, reinterpret_cast<BReq*>(ds->scratch),
                    reinterpret_cast<unsigned*>(ds->scratch + NOALLOC_REQ_BYTES), ds->stats, s);
 }
 
