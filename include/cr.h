@@ -197,9 +197,13 @@ int cr_batch_plan_create(const cr_request *reqs, int32_t num, unsigned flags,
  * implementation present, over all its requests (sorted by function when the
  * plan is made); for a plan of more than 2^26 elements a graph of one
  * persistent kernel per (implementation, function), spread over four parallel
- * branches that join before the launch completes. */
+ * branches that join before the launch completes.  On a stream that is being
+ * captured the one kernel per implementation is recorded, whatever the plan's
+ * size: it reads the plan's tables, so the plan must not be destroyed before
+ * the last replay of every graph that it was captured into has completed. */
 int cr_batch_plan_launch(cr_batch_plan *plan, void *stream);
-/* Release the plan (synchronises with its last launch first). */
+/* Release the plan (synchronises with its last launch first; captured launches
+ * are the caller's to wait for, see cr_batch_plan_launch). */
 int cr_batch_plan_destroy(cr_batch_plan *plan);
 /* Evaluate the requests without a plan.  Batches of up to a few hundred requests
  * (96 of one implementation a launch, up to four launches) go to the kernel as

@@ -225,7 +225,8 @@ def _requests(reqs):
 
 
 class BatchPlan:
-    """A cr_batch_plan: requests evaluated by one launch."""
+    """A cr_batch_plan: requests evaluated by one launch.  A graph that a launch was
+    captured into reads the plan's tables: keep the plan while it is replayed."""
 
     def __init__(self, reqs, flags=0):
         self._arr = _requests(reqs)

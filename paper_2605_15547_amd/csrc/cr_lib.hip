@@ -2253,6 +2253,13 @@ hipError_t launch_batch_args(const BatchTables& T, DevStats* st, unsigned flags,
   return hipGetLastError();
 }
 
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();  // what is wrong with the stream shows in the call that uses it
+  return false;
+}
+
 // Whether a batch goes by kernel arguments: a launch costs about 4.5 us here, the
 // allocation and copy of the tables and the wait for it about 35 us more than that
 // (200 requests, three launches: 18 us; 512 requests by tables: 44 us), so up to
@@ -2263,12 +2270,7 @@ constexpr int ARGS_LAUNCHES = 4;
 hipError_t batch_route(const BatchTables& T, hipStream_t s, bool& args) {
   args = args_launches(T) <= ARGS_LAUNCHES;
   if (args) return hipSuccess;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
-    (void)hipGetLastError();  // the copies report what is wrong with the stream
-    return hipSuccess;
-  }
-  return cs == hipStreamCaptureStatusNone ? hipSuccess : hipErrorStreamCaptureUnsupported;
+  return capturing(s) ? hipErrorStreamCaptureUnsupported : hipSuccess;
 }
 
 }  // namespace
@@ -2653,15 +2655,18 @@ int cr_batch_plan_launch(cr_batch_plan* plan, void* stream) {
   if (!plan) return CR_E_NULL;
   hipStream_t s = (hipStream_t)stream;
   if (!plan->tables.reqs.empty()) {
+    // Into a caller's capture go the kernels themselves (a graph launch leaves
+    // nothing there) and no event: `done` stands for the launches that run now.
+    const bool cap = capturing(s);
     hipError_t e = hipSuccess;
-    if (plan->exec)
+    if (plan->exec && !cap)
       e = hipGraphLaunch(plan->exec, s);
     else
       e = launch_batch(plan->d_reqs, plan->d_tile_req, plan->tables, plan->per, plan->stats,
                        plan->flags, s);
-    if (e == hipSuccess) e = hipEventRecord(plan->done, s);
+    if (e == hipSuccess && !cap) e = hipEventRecord(plan->done, s);
     if (e != hipSuccess) return hip_fail(e);
-    plan->launched = true;
+    if (!cap) plan->launched = true;
     g_elems[plan->device] += plan->tables.elems;
   }
   return CR_OK;

@@ -64,3 +64,50 @@ def test_a_batch_that_needs_tables_is_refused_under_capture(call):
     assert bool((y == 2.0).all())
     call(ptrs)  # and the call works again
     assert _same(out, want)
+
+
+def test_destroying_a_captured_plan_leaves_no_error():
+    """A plan launched eagerly and then into a capture: its destruction (after the
+    graph's) waits for the eager launch and nothing else, and the next calls work."""
+    _need_gpu()
+    ptrs, out, want, x = _batch(40, EDGES, 991)
+    plan = crmath.BatchPlan(ptrs)
+    before = crmath.lib().cr_last_hip_error()
+    plan.launch()
+    g = _graph(plan.launch)
+    out.fill_(-3.0)
+    g.replay()
+    assert _same(out, want)
+    plan.launch()
+    del g
+    plan.destroy()
+    y = crmath.evaluate("expf", x)
+    again = crmath.BatchPlan(ptrs)
+    out.fill_(-3.0)
+    again.launch()
+    assert _same(out, want)
+    again.destroy()
+    assert torch.equal(y, crmath.evaluate("expf", x))
+    assert crmath.lib().cr_last_hip_error() == before
+
+
+def test_captured_large_plan_replays():
+    """More than 2^26 elements: eagerly a graph of per-function kernels, in a capture
+    the kernels themselves."""
+    _need_gpu()
+    ptrs, out, want, _x = _batch(70, (1 << 20, (1 << 20) - 3), 992)
+    assert sum(p[3] for p in ptrs) > 1 << 26
+    plan = crmath.BatchPlan(ptrs)
+    plan.launch()
+    assert _same(out, want)
+    g = _graph(plan.launch)
+    for _ in range(3):
+        out.fill_(-3.0)
+        torch.cuda.synchronize()
+        g.replay()
+        assert _same(out, want)
+        out.fill_(-3.0)
+        plan.launch()
+        assert _same(out, want)
+    del g
+    plan.destroy()
