@@ -118,8 +118,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const T* p, int t0, 
   const int left = 16 * min(nv - t0, BLOCK * U);
   char* base = (char*)const_cast<T*>(p) + 16 * (size_t)(unsigned)t0;
   // 0x00020000: raw buffer, 32-bit data format, bounds checked by the byte
-  return __builtin_amdgcn_make_buffer_rsrc(base + 16 * BLOCK * u, 0, max(left - 16 * BLOCK * u, 0),
-                                           0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(
+      base + 16 * BLOCK * u, 0, u == 0 ? left : max(left - 16 * BLOCK * u, 0), 0x00020000);
 }
 template <class T, int U>
 __device__ __forceinline__ void tile_load(typename Vec<T>::type (&v)[U], const T* in, int t0,
