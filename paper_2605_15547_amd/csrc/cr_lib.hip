@@ -160,22 +160,6 @@ __device__ __forceinline__ bool takes_tail(int t0, int step, int nv, int tv) {
   return (d >= 0 && d < tv) || (e >= 0 && e < tv);
 }
 
-// One 128-bit access at any 4-byte address
-typedef float v4f_t __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ float4 ld_stream4(const float* p) {
-  const v4f_t* q = reinterpret_cast<const v4f_t*>(p);
-  v4f_t v = CR_NT ? __builtin_nontemporal_load(q) : *q;
-  return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void st_stream4(float* p, float4 a) {
-  v4f_t v = {a.x, a.y, a.z, a.w};
-  v4f_t* q = reinterpret_cast<v4f_t*>(p);
-  if (CR_NT)
-    __builtin_nontemporal_store(v, q);
-  else
-    *q = v;
-}
-
 // ------------------------------------------------------------ evaluators
 // Op::fast(x, tab, ok): binary64 fast path and rounding test (inlined).
 // Op::accurate(x, tab): double-double path from x alone (out of line).
@@ -1678,8 +1662,6 @@ int default_bpc() {
   }
   return per;
 }
-
-int grid_blocks() { return num_cus() * default_bpc(); }
 
 // The table copy read by the global-placement variants, filled once per device
 // (synchronously, on first use).

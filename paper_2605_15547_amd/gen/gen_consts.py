@@ -145,6 +145,13 @@ def emit_arr(name, vals, comment, ctype="double"):
          (ctype, name, len(vals), ", ".join(hexd(v) for v in vals)))
 
 
+def emit_proof_arr(name, vals, comment):
+    """Coefficients that a proof needs and no kernel evaluates: in a comment, where the
+    tests read them."""
+    emit("// " + comment)
+    emit("/* not compiled: %s[%d] = {%s}; */" % (name, len(vals), ", ".join(hexd(v) for v in vals)))
+
+
 def emit_const(name, v, comment=""):
     emit("#define %s (%s)%s" % (name, hexd(v), ("  /* " + comment + " */") if comment else ""))
 
@@ -368,7 +375,7 @@ def gen_trig():
         emit("// %s (fast path): |r| <= pi/64; |approximation error| <= 2^%.2f (absolute, proven)"
              % ("sin r = r + r^3 S2(r^2)" if name == "SIN_S2" else "cos r - 1 = r^2 C2(r^2)",
                 log2_of(bound)))
-        emit_arr(name, cd, "coefficients (degree 2 in r^2)")
+        emit_proof_arr(name, cd, "coefficients (degree 2 in r^2)")
         # the same in f = r 32/pi: sin r = f (F0 + F1 f^2 + ...), cos r - 1 = f^2 (F0 + ...)
         p = mp.pi / 32
         if name == "SIN_S2":
@@ -492,8 +499,8 @@ def gen_f64():
          "|S - (log1p t - t + t^2/2 - t^3/3)/t^4| <= 2^%.2f (both proven)"
          % (mp.nstr(a, 6), mp.nstr(b, 6), log2_of(B.sup_bound(B.log64_absolute(Sm, a, b))),
             log2_of(B.sup_bound(B.log64_quotient(Sm, a, b)))))
-    emit_arr("LOG64_S", cd, "coefficients (degree %d)" % (len(cd) - 1))
-    emit("#define LOG64_S_DEG %d" % (len(cd) - 1))
+    # (the form with one reciprocal; the main path evaluates LOG64_S3 below)
+    emit_proof_arr("LOG64_S", cd, "coefficients (degree %d)" % (len(cd) - 1))
     gen_log64_rows(iv)
     emit("#define ATANH64_N 16")
     emit_dd_table("INV_ODD_DD", [mp.mpf(1) / (2 * k + 1) for k in range(17)], "1/(2k+1), k = 0..16")
