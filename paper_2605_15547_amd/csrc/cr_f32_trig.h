@@ -221,10 +221,10 @@ __device__ __forceinline__ TrigFast trig_fast_core(float xf, const TrigTab& tb) 
   // coefficients far below), cos r - 1 within 2^-56 (the bound tests re-derive both
   // approximation errors); the table entries within 2^-54 each; three roundings of
   // terms below 0.05 and the final one of y.  With |sin x|, |cos x| >= 0.049 unless
-  // j = 0 this is below 2^-52 absolute, i.e. 2^-47 |y|.  For j = 0 the table terms are
+  // j = 0 this is below 2^-52 absolute, i.e. 2^-47.6 |y|.  For j = 0 the table terms are
   // exactly 0 and 1 and y is +-sin r or +-cos r; no binary32 x lies closer than
   // 2^-30 to a multiple of pi/2, other than below pi/64 itself, so sin r is within
-  // 2^-46 |y| there.  Bound used: 2^-45 |y|.
+  // 2^-46 |y| there, and cos r within 2^-52 |y|.  Bound used: 2^-45 |y|.
   return o;
 }
 
@@ -232,13 +232,14 @@ __device__ __forceinline__ TrigFast trig_fast_core(float xf, const TrigTab& tb) 
 __device__ __forceinline__ uint32_t sign_mask(float xf) { return f32_bits(xf); }
 
 // The rounding test of the sin and cos fast paths, read off the bits of yh: the bound
-// above is below 256 ulps of yh (ulps of 2^-53 |yh| and up), below 512 when yh falls
-// just below a power of two, so a binary32 midpoint can lie within the error only when
-// the 29 low bits of yh come within 512 of the midpoint pattern 2^28 (cr_round.h,
-// round_f32_bits).  All results are normal numbers but those of tiny arguments, which
+// above is below 256 ulps of yh, which are at least 2^-53 |yh| (just below a power of
+// two; 2^-52 |yh| at one), so a binary32 midpoint can lie within the error only when
+// the 29 low bits of yh come within 256 of the midpoint pattern 2^28 (cr_round.h,
+// round_f32_bits); 512 leaves a factor of 2.  All results are normal numbers but those of tiny arguments, which
 // lie next to a binary32 number (trig_special_fast).
-// tan x, a quotient of two such values within 2^-52 (div_fast), is within 2^-43.99 of
-// its value: the same test.
+// tan x is the quotient within 2^-52 (div_fast) of two such values: at j = 0 one within
+// 2^-46 and one within 2^-52 of theirs, elsewhere both within 2^-47.6.  2^-45.9 |yh| in
+// either case, again below 256 ulps: the same test.
 constexpr unsigned TRIG_TEST_E = 512;
 __device__ __forceinline__ float round_trig_fast(double yh, bool& ok) {
   return round_f32_bits<TRIG_TEST_E>(yh, ok);
