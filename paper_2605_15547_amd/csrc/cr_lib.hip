@@ -2546,7 +2546,10 @@ int cr_dft(const float* x, int64_t n, const float* w, int64_t m, double* X, unsi
   const long long smax = (n + BLOCK * 8 - 1) / (BLOCK * 8);
   if (S > smax) S = smax;
   // up to 64 terms a thread in one slice take less than the allocation of a workspace
-  // and a second kernel (18 us of host work)
+  // and a second kernel (18 us of host work), whatever the number of outputs.  A call,
+  // one slice at n = 2^14: 14.6 us for 1 output, 17.1 for 64, 42.8 for 1024; several
+  // slices at n = 20000: 27.4, 27.1, 54.4 (at n = 2^14, with the sine and cosine of
+  // before: 27.0, 26.0, 75.2).
   if (S < 1 || n <= 64 * BLOCK) S = 1;
   long long slice = (n + S - 1) / S;
   slice = (slice + BLOCK - 1) / BLOCK * BLOCK;
