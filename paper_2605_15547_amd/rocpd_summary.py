@@ -55,6 +55,10 @@ FUNCS["OpLog128"] = "log, 128-entry table"
 # the platform's ~1-ulp functions timed for the paper's ratio (libcr_ulpref.so)
 REF_IDS = {"0": "HIP expf", "4": "HIP logf", "11": "HIP sincosf", "64": "HIP exp", "65": "HIP log",
            "66": "HIP exp2"}
+# kernels of every function, by name and truth value of their template argument
+WHOLE = {("k_dft", "false"): "dft", ("k_dft", "true"): "dft, one slice",
+         ("k_batch", "false"): "batch", ("k_batch", "true"): "batch split",
+         ("k_batch_args", "false"): "batch", ("k_batch_args", "true"): "batch split"}
 
 
 def short(name):
@@ -63,7 +67,8 @@ def short(name):
     m = re.match(r"void (k_\w+)<(\w+(?:<\d+>)?)[ ,>]", name)
     if m:
         op = m.group(2)
-        what = REF_IDS.get(op, "?") if m.group(1).startswith("k_ref") else FUNCS.get(op, "?")
+        what = REF_IDS.get(op, "?") if m.group(1).startswith("k_ref") else \
+            WHOLE.get((m.group(1), op)) or FUNCS.get(op, "?")
         return "%s<%s> (%s)" % (m.group(1), op, what)
     return name.split("(")[0][:60]
 
@@ -189,8 +194,10 @@ def elems_of(kernel, batch):
     """elements per dispatch of bench.py's workloads, by kernel"""
     m = re.match(r"(k_\w+)(?:<\S+>)? \((.+)\)$", kernel)
     if not m:
-        return 268435456 if kernel == "k_dft" else None
+        return None
     k, what = m.group(1), m.group(2)
+    if k == "k_dft":
+        return 1 << 28  # terms: 2^20 samples at 256 frequencies
     if k in ("k_map_f32", "k_map_sincos", "k_ref32"):
         return 1 << 26
     if k in ("k_map_f64", "k_complex", "k_ref64"):
