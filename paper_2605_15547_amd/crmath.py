@@ -151,7 +151,10 @@ def _stream_ptr(stream):
 
 def eval_ptr(func, in_ptr, out_ptr, n, impl=IMPL_AUTO, flags=0, stream_ptr=None):
     """Raw call: device pointers (ints), element count, HIP stream pointer."""
-    rc = (_lib or lib()).cr_eval_ex(_fid(func), impl, flags, in_ptr, out_ptr, n, stream_ptr)
+    # c_void_p refuses what is no integer; an argument converted by the call itself may
+    # also be a host object (bytes, a ctypes array), whose address no kernel can read
+    rc = (_lib or lib()).cr_eval_ex(_fid(func), impl, flags, ctypes.c_void_p(in_ptr),
+                                    ctypes.c_void_p(out_ptr), n, stream_ptr)
     if rc != CR_OK:
         raise CrError(rc, "cr_eval_ex(%s)" % func)
 
@@ -183,7 +186,8 @@ def evaluate(func, x, out=None, impl=IMPL_AUTO, flags=0, stream=None):
 
 def dft_ptr(x_ptr, n, w_ptr, m, out_ptr, flags=0, stream_ptr=None):
     """Raw cr_dft call: device pointers (ints), sample and frequency counts."""
-    rc = (_lib or lib()).cr_dft(x_ptr, n, w_ptr, m, out_ptr, flags, stream_ptr)
+    rc = (_lib or lib()).cr_dft(ctypes.c_void_p(x_ptr), n, ctypes.c_void_p(w_ptr), m,
+                                ctypes.c_void_p(out_ptr), flags, stream_ptr)
     if rc != CR_OK:
         raise CrError(rc, "cr_dft")
 
@@ -198,7 +202,10 @@ def dft(x, w, out=None, flags=0, stream=None):
     m = w.numel()
     if out is None:
         out = torch.empty((m, 2), dtype=torch.float64, device=w.device)
-    dft_ptr(x.data_ptr(), x.numel(), w.data_ptr(), m, out.data_ptr(), flags, _raw_stream(stream))
+    rc = (_lib or lib()).cr_dft(x.data_ptr(), x.numel(), w.data_ptr(), m, out.data_ptr(), flags,
+                                _raw_stream(stream))
+    if rc != CR_OK:
+        raise CrError(rc, "cr_dft")
     return out
 
 
