@@ -8,8 +8,9 @@
  * sinhf, rsqrtf, tanf, tanhf) and double precision exp2 and log (the
  * functions the paper studies in Sec. II-B; exp2 with the paper's three
  * 16-entry tables) plus double precision exp.  "Correctly rounded" means the
- * result is RN(f(x)) for the exact real f(x) (paper, Sec. I).  Only round-to-nearest-even is provided,
- * as in the paper's GPU experiments (Sec. III-C).
+ * result is RN(f(x)) for the exact real f(x) (paper, Sec. I).  Rounding is to
+ * nearest even, as in the paper's GPU experiments (Sec. III-C); the directed
+ * modes are a flag for the single precision functions (enum cr_flag).
  *
  * Conventions shared by every entry point:
  *  - in/out are DEVICE pointers owned by the caller, on the current HIP
@@ -157,19 +158,19 @@ int cr_available(int func_id, int impl);
  * exact in binary32; else CR_E_SIZE); m == 0 returns CR_OK.  flags: enum
  * cr_flag.  X may not overlap x or w (CR_E_OVERLAP).  For S > 1 the call
  * allocates and frees a stream-ordered workspace of m * S * 32 bytes (S = number
- * of sample slices, 1 up to n = 2^14, at most n / 2048 + 1); asynchronous and stream-ordered like
- * cr_eval.  Errors: CR_E_SIZE, CR_E_NULL, CR_E_ALIGN, CR_E_OVERLAP,
- * CR_E_NOMEM, CR_E_HIP. */
+ * of sample slices, 1 up to n = 2^14, at most n / 2048 + 1); asynchronous and
+ * stream-ordered like cr_eval.  Errors: CR_E_SIZE, CR_E_NULL, CR_E_ALIGN,
+ * CR_E_OVERLAP, CR_E_NOMEM, CR_E_HIP. */
 int cr_dft(const float *x, int64_t n, const float *w, int64_t m, double *X, unsigned flags,
            void *stream);
 
 /* ------------------------------------------------------------------ batches
- * Many requests of mixed function and uneven length evaluated by ONE launch (the
- * batched form of the elementwise map; the paper's SIMD functions are called on vectors of
- * arbitrary length, Sec. III-A).  Requests follow the conventions above
- * (device pointers, element alignment, sincosf planar within its own output,
- * in place allowed except for sincosf); binary32 functions only (ids 0..18);
- * each request holds fewer than 2^31 elements.  Requests may not overlap
+ * Many requests of mixed function and uneven length evaluated by ONE launch
+ * (the batched form of the elementwise map; the paper's SIMD functions are
+ * called on vectors of arbitrary length, Sec. III-A).  Requests follow the
+ * conventions above (device pointers, element alignment, sincosf planar within
+ * its own output, in place allowed except for sincosf); binary32 functions only
+ * (ids 0..18); each request holds fewer than 2^31 elements.  Requests may not overlap
  * each other's outputs (not checked across requests).
  */
 typedef struct {
@@ -183,14 +184,14 @@ typedef struct {
 typedef struct cr_batch_plan cr_batch_plan; /* opaque, owned by the library */
 
 /* Validate the requests and upload the request and tile tables (for a plan of
- * more than 2^26 elements, also capture its launches in a HIP graph).  The plan keeps the request pointers: the buffers must stay
- * valid while the plan is launched.  flags: enum cr_flag (applied to every
- * request).  On success *plan receives a new plan (free it with
- * cr_batch_plan_destroy); on error *plan is NULL and nothing is allocated.
- * Errors: CR_E_NULL (reqs or plan NULL, or a NULL pointer in a request with
- * n > 0), CR_E_FUNC, CR_E_IMPL, CR_E_ALIGN, CR_E_OVERLAP (within a request),
- * CR_E_SIZE (num < 0 or a request with n < 0 or n >= 2^31), CR_E_NOMEM,
- * CR_E_HIP. */
+ * more than 2^26 elements, also capture its launches in a HIP graph).  The
+ * plan keeps the request pointers: the buffers must stay valid while the plan
+ * is launched.  flags: enum cr_flag (applied to every request).  On success
+ * *plan receives a new plan (free it with cr_batch_plan_destroy); on error
+ * *plan is NULL and nothing is allocated.  Errors: CR_E_NULL (reqs or plan
+ * NULL, or a NULL pointer in a request with n > 0), CR_E_FUNC, CR_E_IMPL,
+ * CR_E_ALIGN, CR_E_OVERLAP (within a request), CR_E_SIZE (num < 0 or a request
+ * with n < 0 or n >= 2^31), CR_E_NOMEM, CR_E_HIP. */
 int cr_batch_plan_create(const cr_request *reqs, int32_t num, unsigned flags,
                          cr_batch_plan **plan);
 /* Launch the plan on the stream (asynchronous, stream-ordered): one kernel per
@@ -205,31 +206,32 @@ int cr_batch_plan_launch(cr_batch_plan *plan, void *stream);
 /* Release the plan (synchronises with its last launch first; captured launches
  * are the caller's to wait for, see cr_batch_plan_launch). */
 int cr_batch_plan_destroy(cr_batch_plan *plan);
-/* Evaluate the requests without a plan.  Batches of up to a few hundred requests
- * (96 of one implementation a launch, up to four launches) go to the kernel as
- * its arguments: nothing is allocated or copied, the call does not wait, and it
- * can be captured (the graph holds the requests; their buffers must stay valid
- * while it is replayed).  For larger ones the request and tile tables are
- * allocated and freed stream-ordered, and the call synchronises the stream once,
- * after copying the tables from host memory and before the launch; on a stream
- * that is being captured it returns CR_E_HIP before anything is enqueued. */
+/* Evaluate the requests without a plan.  Batches of up to a few hundred
+ * requests (96 of one implementation a launch, up to four launches) go to the
+ * kernel as its arguments: nothing is allocated or copied, the call does not
+ * wait, and it can be captured (the graph holds the requests; their buffers
+ * must stay valid while it is replayed).  For larger ones the request and tile
+ * tables are allocated and freed stream-ordered, and the call synchronises the
+ * stream once, after copying the tables from host memory and before the
+ * launch; on a stream that is being captured it returns CR_E_HIP before
+ * anything is enqueued. */
 int cr_eval_batch(const cr_request *reqs, int32_t num, void *stream);
 
 /* For callers that cannot allocate device memory (tight serving loops,
  * harnesses that forbid hipMalloc): the same evaluation as cr_eval_batch, with
- * the same request conventions, results and errors (under capture too), but the
- * tables of a batch too large to go as kernel arguments are put into a fixed
- * scratch array in the library's static device memory instead of stream-ordered
- * allocations.  The call makes no hipMalloc/hipFree or other allocating device
- * call.  The scratch holds at most CR_NOALLOC_MAX_REQUESTS requests and
- * CR_NOALLOC_MAX_TILES tiles, where a request of n elements takes
+ * the same request conventions, results and errors (under capture too), but
+ * the tables of a batch too large to go as kernel arguments are put into a
+ * fixed scratch array in the library's static device memory instead of
+ * stream-ordered allocations.  The call makes no hipMalloc/hipFree or other
+ * allocating device call.  The scratch holds at most CR_NOALLOC_MAX_REQUESTS
+ * requests and CR_NOALLOC_MAX_TILES tiles, where a request of n elements takes
  * ceil(n / 4096) tiles (about 2 10^9 elements in all); larger batches return
  * CR_E_SCRATCH before anything is copied or launched.  Each device holds one
- * scratch (about 2.3 MiB, kept until the process ends) shared by every call
- * on that device: calls on one stream are ordered, but calls that overlap in
- * time on different streams of one device race on the tables and must not
- * be made.  Where cr_eval_batch copies its tables, this call copies them from
- * host memory and synchronises the stream once before launching. */
+ * scratch (about 2.3 MiB, kept until the process ends) shared by every call on
+ * that device: calls on one stream are ordered, but calls that overlap in time
+ * on different streams of one device race on the tables and must not be made.
+ * Where cr_eval_batch copies its tables, this call copies them from host
+ * memory and synchronises the stream once before launching. */
 #define CR_NOALLOC_MAX_REQUESTS 8192
 #define CR_NOALLOC_MAX_TILES (1 << 19)
 int cr_eval_batch_noalloc(const cr_request *reqs, int32_t num, void *stream);
@@ -299,9 +301,9 @@ int cr_tune_set(int func_id, int impl, const cr_tune_cfg *cfg);
 int cr_tune_reset(void);
 /* Grid of the batch kernels (cr_batch_plan_create, cr_eval_batch,
  * cr_eval_batch_noalloc): workgroups per compute unit of each per-function
- * kernel of a large plan's graph, and an eighth of those of the one kernel that
- * evaluates other batches, one setting per implementation (CR_IMPL_AUTO means
- * F64_INTERNAL), 1..64, default 4.  A plan keeps the value in force when it is
+ * kernel of a large plan's graph (the one kernel that evaluates other batches
+ * has up to eight times as many), one setting per implementation (CR_IMPL_AUTO
+ * means F64_INTERNAL), 1..64, default 4.  A plan keeps the value in force when it is
  * created.  Results never depend on it.  CR_E_IMPL / CR_E_NULL / CR_E_TUNE on
  * bad input. */
 int cr_tune_batch_get(int impl, int32_t *blocks_per_cu);

@@ -263,9 +263,9 @@ __device__ __noinline__ AccResult rsqrt_dir(float xf) {
 }
 
 // ------------------------------------------------------------------- trig
-// Fast path, within 512 ulps (round_trig_fast).  |x| < 2^-12: sin x lies below x in magnitude and tan x above it, by
-// less than 2^-25.5 |x|, and cos x below 1 by less than 2^-25, on this side of
-// the next binary32 number.
+// Fast path, within 256 ulps (round_trig_fast).  |x| < 2^-12: sin x lies below x in
+// magnitude and tan x above it, by less than 2^-25.5 |x|, and cos x below 1 by less
+// than 2^-25, on this side of the next binary32 number.
 template <int KIND, int RM>
 __device__ __forceinline__ bool trig_special_dir(float xf, float& res) {
   const bool inf = fabsf(xf) == INFINITY;

@@ -235,8 +235,8 @@ __device__ __forceinline__ uint32_t sign_mask(float xf) { return f32_bits(xf); }
 // above is below 256 ulps of yh, which are at least 2^-53 |yh| (just below a power of
 // two; 2^-52 |yh| at one), so a binary32 midpoint can lie within the error only when
 // the 29 low bits of yh come within 256 of the midpoint pattern 2^28 (cr_round.h,
-// round_f32_bits); 512 leaves a factor of 2.  All results are normal numbers but those of tiny arguments, which
-// lie next to a binary32 number (trig_special_fast).
+// round_f32_bits); 512 leaves a factor of 2.  All results are normal numbers but those
+// of tiny arguments, which lie next to a binary32 number (trig_special_fast).
 // tan x is the quotient within 2^-52 (div_fast) of two such values: at j = 0 one within
 // 2^-46 and one within 2^-52 of theirs, elsewhere both within 2^-47.6.  2^-45.9 |yh| in
 // either case, again below 256 ulps: the same test.

@@ -1145,7 +1145,7 @@ __device__ __forceinline__ void dft_wave_sum(DftSum& a) {
                  __shfl_xor(a.il, off)});
 }
 
-// Bound by VALU issue: about 80 instructions a term, half of them binary64, against 4
+// Bound by VALU issue: 77 instructions a term, half of them binary64, against 4
 // bytes of samples that the outputs share.  A thread takes DFT_U terms at a time, a
 // block's stride apart, evaluated in straight-line code with one branch for the lanes
 // whose rounding test failed; a term at a time with its own branch it took 120
@@ -2073,7 +2073,8 @@ int build_tables(const cr_request* reqs, int32_t num, BatchTables& T) {
 
 // Tiles per workgroup for a launch of nt tiles.
 int batch_per(long long nt, bool split) {
-  const long long grid = (long long)num_cus() * BATCH_GRID_SCALE * g_batch_bpc[split ? 1 : 0].load();
+  const long long grid =
+      (long long)num_cus() * BATCH_GRID_SCALE * g_batch_bpc[split ? 1 : 0].load();
   return (int)((nt + grid - 1) / grid);
 }
 
@@ -2083,10 +2084,12 @@ hipError_t launch_batch(const BReq* reqs, const unsigned* tile_req, const BatchT
   const int nt = (int)T.tile_req.size();
   if (T.split_tile > 0)
     hipLaunchKernelGGL(k_batch<false>, dim3((T.split_tile + per[0] - 1) / per[0]), dim3(BLOCK), 0,
-                       s, (BReqTab)reqs, (BTileTab)tile_req, 0, T.split_tile, per[0], T.tile, st, flags);
+                       s, (BReqTab)reqs, (BTileTab)tile_req, 0, T.split_tile, per[0], T.tile, st,
+                       flags);
   if (nt > T.split_tile)
     hipLaunchKernelGGL(k_batch<true>, dim3((nt - T.split_tile + per[1] - 1) / per[1]), dim3(BLOCK),
-                       0, s, (BReqTab)reqs, (BTileTab)tile_req, T.split_tile, nt, per[1], T.tile, st, flags);
+                       0, s, (BReqTab)reqs, (BTileTab)tile_req, T.split_tile, nt, per[1], T.tile,
+                       st, flags);
   return hipGetLastError();
 }
 
@@ -2094,7 +2097,8 @@ hipError_t launch_batch(const BReq* reqs, const unsigned* tile_req, const BatchT
 template <class E>
 void launch_tiles(const BReq* r, const unsigned* tr, int t0, int t1, int grid, int tile,
                   DevStats* st, unsigned flags, hipStream_t s) {
-  hipLaunchKernelGGL(k_tiles<E>, dim3(grid), dim3(BLOCK), 0, s, (BReqTab)r, (BTileTab)tr, t0, t1, tile, st, flags);
+  hipLaunchKernelGGL(k_tiles<E>, dim3(grid), dim3(BLOCK), 0, s, (BReqTab)r, (BTileTab)tr, t0, t1,
+                     tile, st, flags);
 }
 int launch_functions(const BReq* r, const unsigned* tr, const BatchTables& T, DevStats* st,
                      unsigned flags, hipStream_t* streams, int nstreams) {
